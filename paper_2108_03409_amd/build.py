@@ -24,6 +24,10 @@ ARCH = "gfx950"
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # accumulators of the matrix-core instructions in vector registers: with them
+    # in accumulation registers v_mfma_f64_16x16x4 issues at 50 instead of
+    # 78 TFLOP/s (register-only loop, 2 048 groups of 4 waves)
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-Wno-unused-but-set-variable",
     "-I", INCLUDE, "-I", CSRC,
 ]
