@@ -265,8 +265,11 @@ extern "C" int vmc_model_create_cnn(vmc_ctx* ctx, int Lx, int Ly, int channels, 
     try {
       m->params = (double2*)dmalloc(sizeof(double2) * m->K);
       VMC_HIP(hipMemsetAsync(m->params, 0, sizeof(double2) * m->K, ctx->stream));
+      m->cnn_frags = (double2*)dmalloc(sizeof(double2) * cnn_frag_count(m));
+      cnn_set_params(m);
     } catch (...) {
       if (m->params) (void)hipFree(m->params);
+      if (m->cnn_frags) (void)hipFree(m->cnn_frags);
       delete m;
       throw;
     }
@@ -446,6 +449,8 @@ extern "C" int vmc_model_set_params(vmc_model* m, const void* params_dev, int dt
       VMC_HIP(hipGetLastError());
     } else if (m->kind == MODEL_AR) {
       ar_set_params(m);
+    } else if (m->kind == MODEL_CNN) {
+      cnn_set_params(m);
     }
     m->version++;
   });
@@ -481,6 +486,7 @@ extern "C" int vmc_model_destroy(vmc_model* m) {
   (void)hipStreamSynchronize(m->ctx->stream);
   if (m->params) (void)hipFree(m->params);
   if (m->Wt) (void)hipFree(m->Wt);
+  if (m->cnn_frags) (void)hipFree(m->cnn_frags);
   rbm_lowp_free(m);
   ar_free(m);
   for (auto& t : m->tab) {

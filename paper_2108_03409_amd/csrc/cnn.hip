@@ -4,10 +4,11 @@
 //   z2[c,p] = b2_c + sum_{c',t} W2[c,c',t] a1[c',p + t],  log psi = sum logcosh(z2)
 // with p + t the periodic shift of position p by tap t = (dy, dx).
 //
-// Kernels (one 256-thread work-group per sample, activations in LDS):
-//   k_cnn_forward  log psi
-//   k_cnn_grad     O_k by the chain rule with recomputation of both layers
-//                  (no activations are stored between calls)
+// Kernels:
+//   k_cnn_net      log psi, O_k rows or the reverse-mode product: one 512-thread
+//                  work-group per sample, activations in LDS, the convolutions
+//                  as matrix products on the float64 matrix cores; both layers
+//                  recomputed per sample (no activations stored between calls)
 //   k_cnn_eloc     local energies of the TFIM: for a flip of site s only the
 //                  k x k layer-1 positions p with p + t = s change, and only the
 //                  (2k-1) x (2k-1) layer-2 positions that read them, so each
@@ -28,7 +29,18 @@ struct cnn_geom {
   const double2* b1;  // [C]
   const double2* W2;  // [C][C][k][k]
   const double2* b2;  // [C]
+  // matrix-core operands of the convolutions (k_cnn_frags)
+  const double2* F0;  // layer 1: [RT][KT][64]
+  const double2* F1;  // layer 2 forward: [RT][kk][KS][64]
+  const double2* F2;  // layer 2 backward: [RT][kk][KS][64]
+  int RT, KS, KT;     // row tiles ceil(C / 16), k steps ceil(C / 4), ceil(kk / 4)
+  float invLx;
 };
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ doublex4 mfma64(double a, double b, doublex4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
 
 __device__ __forceinline__ int shift_pos(const cnn_geom& g, int p, int dy, int dx) {
   const int y = p / g.Lx, x = p - y * g.Lx;
@@ -97,98 +109,347 @@ __device__ double2 block_sum(double2 v, double2* red) {
   return t;
 }
 
-__global__ __launch_bounds__(256) void k_cnn_forward(cnn_geom g, const uint64_t* __restrict__ s, int64_t B,
-                                                     double2* __restrict__ logpsi) {
-  extern __shared__ double2 sm[];
-  double2* a1 = sm;                 // [C][N]
-  double2* red = sm + g.C * g.N;    // [4]
-  const int64_t b = blockIdx.x;
-  if (b >= B) return;
-  const uint64_t* sb = s + b * g.W;
-  const int CN = g.C * g.N;
-  for (int e = threadIdx.x; e < CN; e += 256) a1[e] = clogcosh_pv(z1_at(g, sb, e / g.N, e % g.N));
-  __syncthreads();
-  double2 acc = make_double2(0.0, 0.0);
-  for (int e = threadIdx.x; e < CN; e += 256) acc = cadd(acc, clogcosh(z2_at(g, a1, e / g.N, e % g.N)));
-  acc = block_sum(acc, red);
-  if (threadIdx.x == 0) logpsi[b] = acc;
+// Weights in the operand layout of v_mfma_f64_16x16x4 (lane l holds A[l % 16][l / 16]
+// of each 16 x 4 operand), one complex entry per lane, zero outside the network:
+//   F0[rt][ks][l] = W1[16 rt + l % 16][tap 4 ks + l / 16]
+//   F1[rt][t][ks][l] = W2[16 rt + l % 16][4 ks + l / 16][t]     (rows: output channels)
+//   F2[rt][t][ks][l] = W2[4 ks + l / 16][16 rt + l % 16][t]     (rows: input channels)
+// so that a wave reads an operand as one contiguous kilobyte.
+__global__ void k_cnn_frags(cnn_geom g, double2* __restrict__ F, int64_t n0, int64_t n1, int64_t n) {
+  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (e >= n) return;
+  const int kk = g.k * g.k;
+  const int li = (int)(e & 15), lk = (int)((e >> 4) & 3);
+  double2 v = make_double2(0.0, 0.0);
+  if (e < n0) {
+    const int u = (int)(e >> 6), c = 16 * (u / g.KT) + li, t = 4 * (u % g.KT) + lk;
+    if (c < g.C && t < kk) v = g.W1[c * kk + t];
+  } else {
+    const bool back = e >= n1;
+    const int u = (int)((e - (back ? n1 : n0)) >> 6);
+    const int ks = u % g.KS, t = (u / g.KS) % kk, row = 16 * (u / g.KS / kk) + li, col = 4 * ks + lk;
+    if (row < g.C && col < g.C) v = g.W2[((back ? col * g.C + row : row * g.C + col)) * kk + t];
+  }
+  F[e] = v;
 }
 
-// O_k rows [W1 (C k k), b1 (C), W2 (C C k k), b2 (C)].  LDS: bufA [C][N] (a1, later
-// d log psi / d z1), bufB [C][N] (tanh z2).  Work-group x takes samples x,
-// x + gridDim.x, ...  With gv == NULL each O_k(s_b) is written to row b of O;
-// otherwise (reverse-mode product) the group accumulates g_b conj(O_k(s_b))
-// over its samples into row x of part, each entry by the one thread that
-// forms it, so no sample's O is stored.
-template <typename OutT>
-__global__ __launch_bounds__(256) void k_cnn_grad(cnn_geom g, const uint64_t* __restrict__ s, int64_t B, int64_t K,
-                                                  OutT* __restrict__ O, const double2* __restrict__ gv,
-                                                  double2* __restrict__ part) {
-  extern __shared__ double2 sm[];
-  const int CN = g.C * g.N, kk = g.k * g.k;
-  double2* A = sm;
-  double2* G2 = sm + CN;
-  for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
-  const uint64_t* sb = s + b * g.W;
-  OutT* row = gv ? nullptr : O + b * K;
-  const bool first = b == (int64_t)blockIdx.x;
-  const double2 gb = gv ? gv[b] : make_double2(0.0, 0.0);
-  auto put = [&](int64_t k, double2 v) {
-    if (gv) {
-      const double2 t = cmul(gb, cconj(v));
-      double2* q = part + (int64_t)blockIdx.x * K + k;
-      *q = first ? t : cadd(*q, t);
-    } else if constexpr (sizeof(OutT) == sizeof(double2)) {
-      row[k] = v;
-    } else {
-      row[k] = make_float2((float)v.x, (float)v.y);
+__device__ __forceinline__ void pos_yx(const cnn_geom& g, int p, int& y, int& x) {
+  y = (int)(((float)p + 0.5f) * g.invLx);  // exact for p < 4096: the fraction stays 0.5 / Lx away from an integer
+  x = p - y * g.Lx;
+}
+
+// Layer-1 pre-activations of row tile rt at the 16 positions of tile pt: register r
+// of lane l is channel 16 rt + l / 16 + 4 r at position 16 pt + l % 16 (the
+// accumulator layout of the float64 matrix cores).
+__device__ __forceinline__ void z1_tile(const cnn_geom& g, const uint64_t* s, int rt, int pt, int lane, doublex4& re,
+                                        doublex4& im) {
+  const int li = lane & 15, lk = lane >> 4, kk = g.k * g.k;
+  int y, x;
+  pos_yx(g, min(pt * 16 + li, g.N - 1), y, x);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const double2 b = g.b1[min(rt * 16 + lk + 4 * r, g.C - 1)];
+    re[r] = b.x;
+    im[r] = b.y;
+  }
+  for (int ks = 0; ks < g.KT; ++ks) {
+    const int t = min(4 * ks + lk, kk - 1), dy = t / g.k, dx = t - dy * g.k;
+    int yy = y + dy, xx = x + dx;
+    yy -= yy >= g.Ly ? g.Ly : 0;
+    xx -= xx >= g.Lx ? g.Lx : 0;
+    const double sg = sig_at(s, yy * g.Lx + xx);
+    const double2 w = g.F0[(size_t)(rt * g.KT + ks) * 64 + lane];  // 0 past the last tap
+    re = mfma64(w.x, sg, re);
+    im = mfma64(w.y, sg, im);
+  }
+}
+
+// NP tiles of 16 positions (tiles pt0 .. pt0 + NP - 1) of the layer-2 convolution of
+// X (LDS, [C][ld]) with the operands F: acc += sum_{t, c'} F[rt][t](row, c') X[c'][p +- t]
+// (SGN = 1: p + t, the forward convolution; SGN = -1: p - t, its transpose).
+template <int NP, int SGN>
+__device__ __forceinline__ void conv_tiles(const cnn_geom& g, const double2* __restrict__ F, const double2* X, int ld,
+                                           int rt, int pt0, int lane, doublex4 (&re)[NP], doublex4 (&im)[NP]) {
+  const int li = lane & 15, lk = lane >> 4, kk = g.k * g.k;
+  int py[NP], px[NP];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) pos_yx(g, min((pt0 + j) * 16 + li, g.N - 1), py[j], px[j]);
+  const double2* Fr = F + (size_t)rt * kk * g.KS * 64 + lane;
+  const int last = kk * g.KS - 1;
+  double2 a = Fr[0];
+  int u = 0;
+  for (int dy = 0; dy < g.k; ++dy)
+    for (int dx = 0; dx < g.k; ++dx) {
+      int q[NP];
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        int yy = py[j] + SGN * dy, xx = px[j] + SGN * dx;
+        if (SGN > 0) {
+          yy -= yy >= g.Ly ? g.Ly : 0;
+          xx -= xx >= g.Lx ? g.Lx : 0;
+        } else {
+          yy += yy < 0 ? g.Ly : 0;
+          xx += xx < 0 ? g.Lx : 0;
+        }
+        q[j] = yy * g.Lx + xx;
+      }
+      for (int ks = 0; ks < g.KS; ++ks, ++u) {
+        const double2 an = Fr[(size_t)min(u + 1, last) * 64];  // the next operand in flight
+        const double2* row = X + min(4 * ks + lk, g.C - 1) * ld;  // F is 0 past the last channel
+        double2 b[NP];
+#pragma unroll
+        for (int j = 0; j < NP; ++j) b[j] = row[q[j]];
+        const double na = -a.y;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+          re[j] = mfma64(a.x, b[j].x, re[j]);
+          im[j] = mfma64(a.x, b[j].y, im[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+          re[j] = mfma64(na, b[j].y, re[j]);
+          im[j] = mfma64(a.y, b[j].x, im[j]);
+        }
+        a = an;
+      }
     }
-  };
-  __syncthreads();  // the previous sample's last LDS reads are done
-  const int off_b1 = g.C * kk, off_W2 = off_b1 + g.C, off_b2 = off_W2 + g.C * g.C * kk;
-  for (int e = threadIdx.x; e < CN; e += 256) A[e] = clogcosh_pv(z1_at(g, sb, e / g.N, e % g.N));
-  __syncthreads();
-  for (int e = threadIdx.x; e < CN; e += 256) G2[e] = ctanh(z2_at(g, A, e / g.N, e % g.N));
-  __syncthreads();
-  // dW2[c][c'][t] = sum_p g2[c][p] a1[c'][p + t];  db2[c] = sum_p g2[c][p]
-  for (int e = threadIdx.x; e < g.C * g.C * kk; e += 256) {
-    const int c = e / (g.C * kk), r = e % (g.C * kk), ci = r / kk, t = r % kk;
-    const int dy = t / g.k, dx = t % g.k;
-    double2 acc = make_double2(0.0, 0.0);
-    for (int p = 0; p < g.N; ++p) acc = cadd(acc, cmul(G2[c * g.N + p], A[ci * g.N + shift_pos(g, p, dy, dx)]));
-    put(off_W2 + e, acc);
-  }
-  for (int c = threadIdx.x; c < g.C; c += 256) {
-    double2 acc = make_double2(0.0, 0.0);
-    for (int p = 0; p < g.N; ++p) acc = cadd(acc, G2[c * g.N + p]);
-    put(off_b2 + c, acc);
-  }
-  __syncthreads();
-  // d log psi / d a1[c'][P] = sum_{c,t} W2[c][c'][t] g2[c][P - t], times tanh(z1) -> A
-  for (int e = threadIdx.x; e < CN; e += 256) {
-    const int ci = e / g.N, P = e % g.N;
-    double2 acc = make_double2(0.0, 0.0);
-    for (int c = 0; c < g.C; ++c)
-      for (int dy = 0; dy < g.k; ++dy)
-        for (int dx = 0; dx < g.k; ++dx)
-          acc = cadd(acc, cmul(g.W2[((c * g.C + ci) * g.k + dy) * g.k + dx], G2[c * g.N + shift_pos(g, P, -dy, -dx)]));
-    A[e] = acc;  // each thread overwrites only its own entries; a1 is no longer read
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < CN; e += 256) A[e] = cmul(A[e], ctanh(z1_at(g, sb, e / g.N, e % g.N)));
-  __syncthreads();
-  // dW1[c][t] = sum_p g1[c][p] sigma[p + t];  db1[c] = sum_p g1[c][p]
-  for (int e = threadIdx.x; e < g.C * kk; e += 256) {
-    const int c = e / kk, t = e % kk, dy = t / g.k, dx = t % g.k;
-    double2 acc = make_double2(0.0, 0.0);
-    for (int p = 0; p < g.N; ++p) acc = cadd(acc, cscale(A[c * g.N + p], sig_at(sb, shift_pos(g, p, dy, dx))));
-    put(e, acc);
-  }
-  for (int c = threadIdx.x; c < g.C; c += 256) {
-    double2 acc = make_double2(0.0, 0.0);
-    for (int p = 0; p < g.N; ++p) acc = cadd(acc, A[c * g.N + p]);
-    put(off_b1 + c, acc);
-  }
+}
+
+constexpr int NET_NT = 512;
+constexpr int NET_NW = NET_NT / 64;
+enum { NET_LOGPSI = 0, NET_ROWS = 1, NET_VJP = 2 };
+
+// One sample per work-group, every contraction of the network as float64 matrix
+// products (16 x 16 blocks, four real products per complex term):
+//   layer 1       z1[c][p]        rows c, columns p, reduction over taps
+//   layer 2       z2[c][p]        rows c, columns p, reduction over (tap, c')
+//   dW2[c][c',t] = sum_p g2[c][p] a1[c'][p + t]     rows c, columns (c', t), reduction over p
+//   back[c'][p]  = sum_{c,t} W2[c][c'][t] g2[c][p - t]   (the forward product, transposed)
+//   dW1[c][t]    = sum_p g1[c][p] sigma[p + t]      rows c, columns t, reduction over p
+// with a1 = logcosh(z1), g2 = tanh(z2), g1 = back tanh(z1).  LDS: A [C][N + 1]
+// (a1, later g1), G2 [C][N + 1] (g2, later partial sums of dW1); the odd row
+// length spreads the rows over the banks where lanes run over channels.
+// Rows O_k = [W1 (C k k), b1 (C), W2 (C C k k), b2 (C)].  MODE NET_ROWS writes
+// O_k(s_b) to row b of O; NET_VJP accumulates g_b conj(O_k(s_b)) over the group's
+// samples x, x + gridDim.x, ... into row x of part, each entry by the one thread
+// that forms it; NET_LOGPSI stops after layer 2.
+//
+// Bound: the float64 matrix cores (12 C^2 k^2 N real multiply-adds for the three
+// layer-2 products: 83 us a sample and compute unit at C = 16, k = 4, N = 256 at
+// the full rate, 0.33 of the 0.60 ms below); the rest is the transcendental
+// functions of the two activations and the operand latency of two waves per SIMD
+// (four waves per SIMD spill at 128 registers: log psi 0.31 ms).  The loops over
+// taps and positions per output that this replaces spent their time on index
+// arithmetic and serial sums.
+// 1 024 samples, 16 x 16, C = 16, k = 4: log psi 1.53 -> 0.26 ms, O_k (complex64)
+// 7.92 -> 0.60 ms, reverse-mode product 7.86 -> 0.67 ms.
+template <int MODE, typename OutT>
+__global__ __launch_bounds__(NET_NT, 2) void k_cnn_net(
+    cnn_geom g, const uint64_t* __restrict__ s, int64_t B, int64_t K, OutT* __restrict__ O,
+    const double2* __restrict__ gv, double2* __restrict__ part, double2* __restrict__ logpsi) {
+  extern __shared__ double2 sm[];
+  __shared__ double2 red[NET_NW];
+  const int C = g.C, N = g.N, ld = N + 1, kk = g.k * g.k;
+  double2* A = sm;
+  double2* G2 = sm + C * ld;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int PT = (N + 15) / 16, PP = (PT + 1) / 2;  // position tiles, pairs of them
+  const int off_b1 = C * kk, off_W2 = off_b1 + C, off_b2 = off_W2 + C * C * kk;
+  for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
+    const uint64_t* sb = s + b * g.W;
+    const bool first = b == (int64_t)blockIdx.x;
+    const double2 gb = MODE == NET_VJP ? gv[b] : make_double2(0.0, 0.0);
+    auto put = [&](int64_t k, double2 v) {
+      if constexpr (MODE == NET_VJP) {
+        const double2 t = cmul(gb, cconj(v));
+        double2* q = part + (int64_t)blockIdx.x * K + k;
+        *q = first ? t : cadd(*q, t);
+      } else if constexpr (MODE == NET_ROWS) {
+        OutT* row = O + b * K;
+        if constexpr (sizeof(OutT) == sizeof(double2))
+          row[k] = v;
+        else
+          row[k] = make_float2((float)v.x, (float)v.y);
+      }
+    };
+    __syncthreads();  // the previous sample's last LDS reads are done
+    for (int u = wave; u < g.RT * PT; u += NET_NW) {
+      const int rt = u / PT, pt = u - rt * PT;
+      doublex4 re, im;
+      z1_tile(g, sb, rt, pt, lane, re, im);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = rt * 16 + lk + 4 * r, p = pt * 16 + li;
+        if (c < C && p < N) A[c * ld + p] = clogcosh_pv(make_double2(re[r], im[r]));
+      }
+    }
+    __syncthreads();
+    double2 lp = make_double2(0.0, 0.0);
+    for (int u = wave; u < g.RT * PP; u += NET_NW) {
+      const int rt = u / PP, pt = 2 * (u - rt * PP);
+      doublex4 re[2], im[2];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double2 b2 = g.b2[min(rt * 16 + lk + 4 * r, C - 1)];
+        re[0][r] = re[1][r] = b2.x;
+        im[0][r] = im[1][r] = b2.y;
+      }
+      conv_tiles<2, 1>(g, g.F1, A, ld, rt, pt, lane, re, im);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int c = rt * 16 + lk + 4 * r, p = (pt + j) * 16 + li;
+          if (c < C && p < N) {
+            const double2 z = make_double2(re[j][r], im[j][r]);
+            if constexpr (MODE == NET_LOGPSI)
+              lp = cadd(lp, clogcosh(z));
+            else
+              G2[c * ld + p] = ctanh(z);
+          }
+        }
+    }
+    if constexpr (MODE == NET_LOGPSI) {
+      lp = wave_sum(lp);
+      if (lane == 0) red[wave] = lp;
+      __syncthreads();
+      if (tid == 0) {
+        double2 t = make_double2(0.0, 0.0);
+        for (int w = 0; w < NET_NW; ++w) t = cadd(t, red[w]);
+        logpsi[b] = t;
+      }
+      continue;
+    }
+    __syncthreads();
+    // dW2: two tiles of 16 columns (c', t) share the rows g2
+    const int CT = (C * kk + 15) / 16, CP = (CT + 1) / 2;
+    for (int u = wave; u < g.RT * CP; u += NET_NW) {
+      const int rt = u / CP, ct = 2 * (u - rt * CP);
+      const double2* arow = G2 + min(rt * 16 + li, C - 1) * ld;
+      const double2* brow[2];
+      int dy[2], dx[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int n = min((ct + j) * 16 + li, C * kk - 1), ci = n / kk, t = n - ci * kk;
+        brow[j] = A + ci * ld;
+        dy[j] = t / g.k;
+        dx[j] = t - dy[j] * g.k;
+      }
+      doublex4 re[2], im[2];
+      re[0] = re[1] = im[0] = im[1] = doublex4{0.0, 0.0, 0.0, 0.0};
+      for (int p0 = 0; p0 < N; p0 += 4) {
+        const int p = min(p0 + lk, N - 1);
+        int y, x;
+        pos_yx(g, p, y, x);
+        double2 a = arow[p];
+        if (p0 + lk >= N) a = make_double2(0.0, 0.0);
+        double2 bv[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          int yy = y + dy[j], xx = x + dx[j];
+          yy -= yy >= g.Ly ? g.Ly : 0;
+          xx -= xx >= g.Lx ? g.Lx : 0;
+          bv[j] = brow[j][yy * g.Lx + xx];
+        }
+        const double na = -a.y;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          re[j] = mfma64(a.x, bv[j].x, re[j]);
+          im[j] = mfma64(a.x, bv[j].y, im[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          re[j] = mfma64(na, bv[j].y, re[j]);
+          im[j] = mfma64(a.y, bv[j].x, im[j]);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int c = rt * 16 + lk + 4 * r, n = (ct + j) * 16 + li;
+          if (c < C && n < C * kk) put(off_W2 + (int64_t)c * C * kk + n, make_double2(re[j][r], im[j][r]));
+        }
+    }
+    for (int c = wave; c < C; c += NET_NW) {
+      double2 acc = make_double2(0.0, 0.0);
+      for (int p = lane; p < N; p += 64) acc = cadd(acc, G2[c * ld + p]);
+      acc = wave_sum(acc);
+      if (lane == 0) put(off_b2 + c, acc);
+    }
+    __syncthreads();  // a1 is no longer read
+    // g1 = tanh(z1) d log psi / d a1 -> A
+    for (int u = wave; u < g.RT * PP; u += NET_NW) {
+      const int rt = u / PP, pt = 2 * (u - rt * PP);
+      doublex4 re[2], im[2];
+      re[0] = re[1] = im[0] = im[1] = doublex4{0.0, 0.0, 0.0, 0.0};
+      conv_tiles<2, -1>(g, g.F2, G2, ld, rt, pt, lane, re, im);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (pt + j >= PT) break;
+        doublex4 zr, zi;
+        z1_tile(g, sb, rt, pt + j, lane, zr, zi);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int c = rt * 16 + lk + 4 * r, p = (pt + j) * 16 + li;
+          if (c < C && p < N)
+            A[c * ld + p] = cmul(make_double2(re[j][r], im[j][r]), ctanh(make_double2(zr[r], zi[r])));
+        }
+      }
+    }
+    __syncthreads();
+    // dW1: tiles of (16 channels, 16 taps); the positions split over ns parts (as many as
+    // the waves and the partial sums in G2 allow), added in a fixed order
+    const int TT = (kk + 15) / 16, nt = g.RT * TT;
+    int ns = 1;
+    while (ns < NET_NW && 2 * ns * nt * 256 <= C * ld) ns *= 2;
+    const int per = ((N + ns - 1) / ns + 3) / 4 * 4;
+    for (int u = wave; u < nt * ns; u += NET_NW) {
+      const int tile = u / ns, z = u - tile * ns, rt = tile / TT, t0 = 16 * (tile - rt * TT);
+      const double2* arow = A + min(rt * 16 + li, C - 1) * ld;
+      const int t = min(t0 + li, kk - 1), dy = t / g.k, dx = t - dy * g.k;
+      doublex4 re = doublex4{0.0, 0.0, 0.0, 0.0}, im = re;
+      const int pe = min(N, (z + 1) * per);
+      for (int p0 = z * per; p0 < pe; p0 += 4) {
+        const int p = min(p0 + lk, N - 1);
+        int y, x;
+        pos_yx(g, p, y, x);
+        y += dy;
+        x += dx;
+        y -= y >= g.Ly ? g.Ly : 0;
+        x -= x >= g.Lx ? g.Lx : 0;
+        const double sg = p0 + lk < pe ? sig_at(sb, y * g.Lx + x) : 0.0;
+        const double2 a = arow[p];
+        re = mfma64(a.x, sg, re);
+        im = mfma64(a.y, sg, im);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = lk + 4 * r, c = rt * 16 + row;
+        if (ns > 1)
+          G2[(tile * ns + z) * 256 + row * 16 + li] = make_double2(re[r], im[r]);
+        else if (c < C && t0 + li < kk)
+          put(c * kk + t0 + li, make_double2(re[r], im[r]));
+      }
+    }
+    for (int c = wave; c < C; c += NET_NW) {
+      double2 acc = make_double2(0.0, 0.0);
+      for (int p = lane; p < N; p += 64) acc = cadd(acc, A[c * ld + p]);
+      acc = wave_sum(acc);
+      if (lane == 0) put(off_b1 + c, acc);
+    }
+    if (ns > 1) {
+      __syncthreads();
+      for (int e = tid; e < nt * 256; e += NET_NT) {
+        const int tile = e >> 8, rt = tile / TT, c = rt * 16 + ((e >> 4) & 15), t = 16 * (tile - rt * TT) + (e & 15);
+        if (c < C && t < kk) {
+          double2 acc = make_double2(0.0, 0.0);
+          for (int z = 0; z < ns; ++z) acc = cadd(acc, G2[(tile * ns + z) * 256 + (e & 255)]);
+          put(c * kk + t, acc);
+        }
+      }
+    }
   }
 }
 
@@ -424,6 +685,13 @@ cnn_geom geom(const vmc_model* m) {
   g.b1 = m->params + m->C * kk;
   g.W2 = g.b1 + m->C;
   g.b2 = g.W2 + m->C * m->C * kk;
+  g.RT = (m->C + 15) / 16;
+  g.KS = (m->C + 3) / 4;
+  g.KT = (kk + 3) / 4;
+  g.F0 = m->cnn_frags;
+  g.F1 = g.F0 + (size_t)g.RT * g.KT * 64;
+  g.F2 = g.F1 + (size_t)g.RT * kk * g.KS * 64;
+  g.invLx = 1.0f / (float)m->Lx;
   return g;
 }
 
@@ -437,32 +705,54 @@ void allow_lds(Kern k, size_t bytes) {
 
 }  // namespace
 
+size_t cnn_frag_count(const vmc_model* m) {
+  const size_t RT = (m->C + 15) / 16, KS = (m->C + 3) / 4, kk = (size_t)m->k * m->k, KT = (kk + 3) / 4;
+  return 64 * RT * (KT + 2 * kk * KS);
+}
+
+void cnn_set_params(vmc_model* m) {
+  const cnn_geom g = geom(m);
+  const int64_t n = (int64_t)cnn_frag_count(m), n0 = g.F1 - g.F0, n1 = g.F2 - g.F0;
+  k_cnn_frags<<<grid_for(n, 256), 256, 0, m->ctx->stream>>>(g, m->cnn_frags, n0, n1, n);
+  VMC_HIP(hipGetLastError());
+}
+
+namespace {
+size_t net_lds(const cnn_geom& g, int mode) {
+  return sizeof(double2) * (size_t)(mode == NET_LOGPSI ? 1 : 2) * g.C * (g.N + 1);
+}
+}  // namespace
+
 void cnn_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
   const cnn_geom g = geom(m);
-  const size_t lds = sizeof(double2) * ((size_t)g.C * g.N + 4);
-  allow_lds(k_cnn_forward, lds);
-  k_cnn_forward<<<(unsigned)B, 256, lds, m->ctx->stream>>>(g, s, B, logpsi);
+  const size_t lds = net_lds(g, NET_LOGPSI);
+  auto k = k_cnn_net<NET_LOGPSI, double2>;
+  allow_lds(k, lds);
+  k<<<(unsigned)B, NET_NT, lds, m->ctx->stream>>>(g, s, B, m->K, nullptr, nullptr, nullptr, logpsi);
   VMC_HIP(hipGetLastError());
 }
 
 void cnn_grad(vmc_model* m, const uint64_t* s, int64_t B, void* O, int dtype) {
   const cnn_geom g = geom(m);
-  const size_t lds = sizeof(double2) * 2 * (size_t)g.C * g.N;
+  const size_t lds = net_lds(g, NET_ROWS);
   if (dtype == VMC_DT_C128) {
-    allow_lds(k_cnn_grad<double2>, lds);
-    k_cnn_grad<double2><<<(unsigned)B, 256, lds, m->ctx->stream>>>(g, s, B, m->K, (double2*)O, nullptr, nullptr);
+    auto k = k_cnn_net<NET_ROWS, double2>;
+    allow_lds(k, lds);
+    k<<<(unsigned)B, NET_NT, lds, m->ctx->stream>>>(g, s, B, m->K, (double2*)O, nullptr, nullptr, nullptr);
   } else {
-    allow_lds(k_cnn_grad<float2>, lds);
-    k_cnn_grad<float2><<<(unsigned)B, 256, lds, m->ctx->stream>>>(g, s, B, m->K, (float2*)O, nullptr, nullptr);
+    auto k = k_cnn_net<NET_ROWS, float2>;
+    allow_lds(k, lds);
+    k<<<(unsigned)B, NET_NT, lds, m->ctx->stream>>>(g, s, B, m->K, (float2*)O, nullptr, nullptr, nullptr);
   }
   VMC_HIP(hipGetLastError());
 }
 
 void cnn_vjp_partial(vmc_model* m, const uint64_t* s, int64_t B, const double2* gv, int groups, double2* part) {
   const cnn_geom g = geom(m);
-  const size_t lds = sizeof(double2) * 2 * (size_t)g.C * g.N;
-  allow_lds(k_cnn_grad<double2>, lds);
-  k_cnn_grad<double2><<<(unsigned)groups, 256, lds, m->ctx->stream>>>(g, s, B, m->K, nullptr, gv, part);
+  const size_t lds = net_lds(g, NET_VJP);
+  auto k = k_cnn_net<NET_VJP, double2>;
+  allow_lds(k, lds);
+  k<<<(unsigned)groups, NET_NT, lds, m->ctx->stream>>>(g, s, B, m->K, nullptr, gv, part, nullptr);
   VMC_HIP(hipGetLastError());
 }
 

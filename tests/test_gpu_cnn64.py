@@ -1,0 +1,48 @@
+"""GPU parity of the float64 CNN kernels on the matrix cores at the edges of
+their 16 x 16 x 4 operands: channels and taps below, at and above a tile,
+positions that fill no whole tile."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import cnn as ocnn
+from gpu_common import dev_bits, dev_c128, assert_logpsi_close, flush
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2108_03409_amd import nqsvmc as V  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    return V.Context(0)
+
+
+def _cnn(ctx, Lx, Ly, C, k, std, seed):
+    p = si._normal_params(ocnn.num_params(C, k), std, True, seed=seed)
+    m = V.Model.cnn(ctx, Lx, Ly, C, k)
+    m.set_params(dev_c128(p))
+    return m, p
+
+
+# one channel and tap; two row tiles; 25 taps (two tap tiles); 33 channels on 9
+# positions (partial sums of dW1 do not fit beside them); the largest sample
+@pytest.mark.parametrize("Lx,Ly,C,k,B", [(5, 3, 1, 1, 7), (9, 7, 17, 2, 5), (11, 6, 5, 5, 4), (3, 3, 33, 3, 3),
+                                         (64, 64, 1, 2, 2), (13, 6, 64, 2, 2)])
+def test_net_tile_edges(ctx, Lx, Ly, C, k, B):
+    flush(f"cnn float64 network {Lx}x{Ly} C={C} k={k} B={B}")
+    m, p = _cnn(ctx, Lx, Ly, C, k, 0.3 / np.sqrt(C * k), seed=5 * Lx + C)
+    bits = si.random_bits(B, Lx * Ly, seed=6)
+    s = dev_bits(si.pack_bits(bits))
+    assert_logpsi_close(m.log_psi(s).cpu().numpy(), ocnn.log_psi(p, bits, Lx, Ly, C, k), 1e-10)
+    ref = ocnn.grad_log_psi(p, bits, Lx, Ly, C, k)
+    scale = max(1.0, np.abs(ref).max())
+    assert np.max(np.abs(m.grad_log_psi(s, torch.complex128).cpu().numpy() - ref)) <= 1e-10 * scale
+    rng = np.random.default_rng(7)
+    gv = rng.normal(size=B) + 1j * rng.normal(size=B)
+    out = m.log_psi_vjp(s, dev_c128(gv)).cpu().numpy()
+    assert np.max(np.abs(out - ref.conj().T @ gv)) <= 1e-10 * scale * np.abs(gv).sum()
