@@ -267,9 +267,15 @@ extern "C" int vmc_model_create_cnn(vmc_ctx* ctx, int Lx, int Ly, int channels, 
       VMC_HIP(hipMemsetAsync(m->params, 0, sizeof(double2) * m->K, ctx->stream));
       m->cnn_frags = (double2*)dmalloc(sizeof(double2) * cnn_frag_count(m));
       cnn_set_params(m);
+      const std::vector<int> units = cnn_eloc_units(m);
+      m->cnn_units = (int*)dmalloc(sizeof(int) * units.size());
+      VMC_HIP(hipMemcpyAsync(m->cnn_units, units.data(), sizeof(int) * units.size(), hipMemcpyHostToDevice,
+                             ctx->stream));
+      VMC_HIP(hipStreamSynchronize(ctx->stream));
     } catch (...) {
       if (m->params) (void)hipFree(m->params);
       if (m->cnn_frags) (void)hipFree(m->cnn_frags);
+      if (m->cnn_units) (void)hipFree(m->cnn_units);
       delete m;
       throw;
     }
@@ -487,6 +493,7 @@ extern "C" int vmc_model_destroy(vmc_model* m) {
   if (m->params) (void)hipFree(m->params);
   if (m->Wt) (void)hipFree(m->Wt);
   if (m->cnn_frags) (void)hipFree(m->cnn_frags);
+  if (m->cnn_units) (void)hipFree(m->cnn_units);
   rbm_lowp_free(m);
   ar_free(m);
   for (auto& t : m->tab) {

@@ -17,6 +17,10 @@
 //                  smaller tori re-evaluate layer 2 in full per slot).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
+#include <vector>
+
 #include "internal.h"
 
 using namespace dev;
@@ -453,6 +457,221 @@ __global__ __launch_bounds__(NET_NT, 2) void k_cnn_net(
   }
 }
 
+constexpr int EL_NT = 512;
+constexpr int EL_NW = EL_NT / 64;
+constexpr int EL_F = 16;  // flips per pass: the columns of one matrix-core operand
+
+// 1 + e^{-2 z~} with z~ = +-z, Re z~ >= 0 (cosh z = e^{z~} (1 + e^{-2 z~}) / 2); zt receives z~
+__device__ __forceinline__ double2 cosh_factor(double2 z, double2& zt) {
+  zt = z.x < 0.0 ? make_double2(-z.x, -z.y) : z;
+  const double e = exp(-2.0 * zt.x);
+  double s, c;
+  sincos(-2.0 * zt.y, &s, &c);
+  return make_double2(fma(e, c, 1.0), e * s);
+}
+
+// TFIM local energies on tori of at least 2k - 1 sites a side, matrix-core form.
+// For a flip of site f the layer-1 changes dA[c'][t1] sit at the positions f - t1 and
+// the layer-2 changes at f - e, e = t1 + t2:
+//   dZ[c][e] = sum_{t1 + t2 = e} sum_{c'} W2[c][c'][t2] dA[c'][t1].
+// A pass takes EL_F = 16 consecutive sites as the columns of the products: per window
+// offset e the rows are 16 output channels and the reduction runs over the pairs
+// (t1, t2) and c', so no entry of a product is padding (C a multiple of 16) and a
+// column's window is summed without leaving its lanes.  The (row tile, e) units are
+// shared out over the waves by cost on the host.  Each lane then multiplies
+//   cosh(z2 + dZ) / cosh(z2) = e^{z~' - z~} (1 + e^{-2 z~'}) / (1 + e^{-2 z~})
+// over its outputs as a product with a separate exponent and one logarithm per pass,
+// instead of a logarithm and an arctangent per output.
+// LDS: Z2 [C][N + 1], dA [C][kk][16] (before the passes: a1 [C][N + 1]); z1, a1 and
+// 1 / (1 + e^{-2 z~}) of the work-group's sample in global scratch.
+//
+// Bound: the float64 matrix cores and the float64 vector work of the factors, which
+// hardly overlap: the matrix pipe is busy 46% of the cycles (4 C^2 k^4 N real
+// multiply-adds a sample, 443 us a compute unit at C = 16, k = 4, N = 256), vector
+// issue takes 37% (counters).  512 samples of that network: 25.2 -> 2.13 ms.
+template <int KSC>
+__global__ __launch_bounds__(EL_NT, 2) void k_cnn_eloc64(cnn_geom g, const uint64_t* __restrict__ s, int64_t B,
+                                                         int nsplit, double J, double h,
+                                                         const int2* __restrict__ bonds, int n_bonds,
+                                                         const int* __restrict__ units, double2* __restrict__ scr,
+                                                         double2* __restrict__ eloc) {
+  extern __shared__ double2 sm[];
+  __shared__ double2 red[EL_NW][EL_F];
+  __shared__ int nal_s[EL_NW];
+  const int C = g.C, N = g.N, ld = N + 1, k = g.k, kk = k * k, win = 2 * k - 1;
+  const int CN = C * N;
+  const int KS = KSC ? KSC : g.KS;
+  double2* Z2 = sm;
+  double2* DA = sm + C * ld;
+  double2* z1g = scr + (size_t)blockIdx.x * 3 * CN;
+  double2* a1g = z1g + CN;
+  double2* iqg = a1g + CN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  const int PT = (N + 15) / 16, PP = (PT + 1) / 2;
+  const int npass = (N + EL_F - 1) / EL_F;
+  const int u0 = units[wave], u1 = units[wave + 1];
+  for (int64_t item = blockIdx.x; item < B * nsplit; item += gridDim.x) {
+    const int64_t b = item / nsplit;
+    const int sp = (int)(item - b * nsplit);
+    const uint64_t* sb = s + b * g.W;
+    __syncthreads();  // the previous sample's LDS and scratch reads are done
+    for (int u = wave; u < g.RT * PT; u += EL_NW) {
+      const int rt = u / PT, pt = u - rt * PT;
+      doublex4 re, im;
+      z1_tile(g, sb, rt, pt, lane, re, im);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = rt * 16 + lk + 4 * r, p = pt * 16 + li;
+        if (c < C && p < N) {
+          const double2 z = make_double2(re[r], im[r]), a = clogcosh_pv(z);
+          DA[c * ld + p] = a;
+          z1g[c * N + p] = z;
+          a1g[c * N + p] = a;
+        }
+      }
+    }
+    __syncthreads();
+    for (int u = wave; u < g.RT * PP; u += EL_NW) {
+      const int rt = u / PP, pt = 2 * (u - rt * PP);
+      doublex4 re[2], im[2];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double2 b2 = g.b2[min(rt * 16 + lk + 4 * r, C - 1)];
+        re[0][r] = re[1][r] = b2.x;
+        im[0][r] = im[1][r] = b2.y;
+      }
+      conv_tiles<2, 1>(g, g.F1, DA, ld, rt, pt, lane, re, im);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int c = rt * 16 + lk + 4 * r, p = (pt + j) * 16 + li;
+          if (c < C && p < N) {
+            const double2 z = make_double2(re[j][r], im[j][r]);
+            double2 zt;
+            const double2 q = cosh_factor(z, zt);
+            Z2[c * ld + p] = z;
+            iqg[c * N + p] = cdiv(make_double2(1.0, 0.0), q);
+          }
+        }
+    }
+    int n_al = 0;
+    if (sp == 0)
+      for (int q = tid; q < n_bonds; q += EL_NT) n_al += sig_at(sb, bonds[q].x) == sig_at(sb, bonds[q].y);
+    n_al = wave_isum_uniform(n_al);
+    if (lane == 0) nal_s[wave] = n_al;
+    __syncthreads();
+    double2 acc = make_double2(0.0, 0.0);  // threads 0..15: their column's sites
+    for (int ps = sp; ps < npass; ps += nsplit) {
+      // dA[c][t1][column]
+      for (int e = tid; e < C * kk * EL_F; e += EL_NT) {
+        const int f = min(ps * EL_F + (e & (EL_F - 1)), N - 1), r = e / EL_F, c = r / kk, t = r - c * kk;
+        const int dy = t / k, dx = t - dy * k;
+        int y, x;
+        pos_yx(g, f, y, x);
+        y -= dy;
+        x -= dx;
+        y += y < 0 ? g.Ly : 0;
+        x += x < 0 ? g.Lx : 0;
+        const int p = y * g.Lx + x;
+        const double ds = -2.0 * sig_at(sb, f);
+        const double2 z = z1g[c * N + p], w = g.W1[c * kk + t];
+        DA[e] = csub(clogcosh_pv(make_double2(fma(ds, w.x, z.x), fma(ds, w.y, z.y))), a1g[c * N + p]);
+      }
+      __syncthreads();
+      int fy, fx;
+      pos_yx(g, min(ps * EL_F + li, N - 1), fy, fx);
+      double2 P = make_double2(1.0, 0.0), lin = make_double2(0.0, 0.0);
+      int ex2 = 0;
+      for (int uu = u0; uu < u1; ++uu) {
+        const int un = __builtin_amdgcn_readfirstlane(units[uu]);
+        const int rt = un >> 16, ey = (un >> 8) & 255, ex = un & 255;
+        int qy = fy - ey, qx = fx - ex;
+        qy += qy < 0 ? g.Ly : 0;
+        qx += qx < 0 ? g.Lx : 0;
+        const int q = qy * g.Lx + qx;
+        double2 iq[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) iq[r] = iqg[min(rt * 16 + lk + 4 * r, C - 1) * N + q];
+        doublex4 re0 = doublex4{0.0, 0.0, 0.0, 0.0}, re1 = re0, im0 = re0, im1 = re0;
+        const int ylo = max(0, ey - k + 1), yhi = min(k - 1, ey), xlo = max(0, ex - k + 1), xhi = min(k - 1, ex);
+        const double2* Fr = g.F1 + (size_t)rt * kk * KS * 64 + lane;
+        for (int y2 = ylo; y2 <= yhi; ++y2)
+          for (int x2 = xlo; x2 <= xhi; ++x2) {
+            const double2* fa = Fr + (size_t)(y2 * k + x2) * KS * 64;
+            const double2* db = DA + ((ey - y2) * k + ex - x2) * EL_F + li;
+            auto step = [&](double2 a, double2 d) {
+              re0 = mfma64(a.x, d.x, re0);
+              im0 = mfma64(a.x, d.y, im0);
+              re1 = mfma64(-a.y, d.y, re1);
+              im1 = mfma64(a.y, d.x, im1);
+            };
+            if constexpr (KSC > 0) {
+              double2 a[KSC], d[KSC];
+#pragma unroll
+              for (int ks = 0; ks < KSC; ++ks) {
+                a[ks] = fa[ks * 64];
+                d[ks] = db[min(4 * ks + lk, C - 1) * kk * EL_F];
+              }
+#pragma unroll
+              for (int ks = 0; ks < KSC; ++ks) step(a[ks], d[ks]);
+            } else {
+              for (int ks = 0; ks < KS; ++ks) step(fa[ks * 64], db[min(4 * ks + lk, C - 1) * kk * EL_F]);
+            }
+          }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int c = rt * 16 + lk + 4 * r;
+          if (c >= C) continue;
+          const double2 z = Z2[c * ld + q], dz = make_double2(re0[r] + re1[r], im0[r] + im1[r]);
+          double2 zt;
+          const double2 f = cmul(cosh_factor(cadd(z, dz), zt), iq[r]);
+          const double sg = z.x < 0.0 ? -1.0 : 1.0;
+          lin = cadd(lin, csub(zt, cscale(z, sg)));
+          P = cmul(P, f);
+        }
+        const int e2 = __builtin_amdgcn_frexp_exp(fmax(fabs(P.x), fabs(P.y)));
+        P = make_double2(ldexp(P.x, -e2), ldexp(P.y, -e2));
+        ex2 += e2;
+      }
+      double2 L = clog(P);
+      L = make_double2(lin.x + (L.x + 0.69314718055994530942 * (double)ex2), lin.y + L.y);
+      L.x += __shfl_xor(L.x, 16, 64);
+      L.y += __shfl_xor(L.y, 16, 64);
+      L.x += __shfl_xor(L.x, 32, 64);
+      L.y += __shfl_xor(L.y, 32, 64);
+      if (lk == 0) red[wave][li] = L;
+      __syncthreads();
+      if (tid < EL_F && ps * EL_F + tid < N) {
+        double2 t = make_double2(0.0, 0.0);
+        for (int w = 0; w < EL_NW; ++w) t = cadd(t, red[w][tid]);
+        acc = cadd(acc, cscale(cexp(t), -h));
+      }
+    }
+    if (tid < 64) {  // lanes 16 .. 63 hold 0
+      acc = wave_sum(acc);
+      if (tid == 0) {
+        if (sp == 0) {
+          int nal = 0;
+          for (int w = 0; w < EL_NW; ++w) nal += nal_s[w];
+          acc.x += -J * (double)(nal - (n_bonds - nal));
+        }
+        eloc[item] = acc;
+      }
+    }
+  }
+}
+
+// eloc[b] = sum of the nsplit parts of sample b, in order
+__global__ void k_cnn_eloc_add(const double2* __restrict__ part, int64_t B, int nsplit, double2* __restrict__ eloc) {
+  const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (b >= B) return;
+  double2 acc = part[b * nsplit];
+  for (int q = 1; q < nsplit; ++q) acc = cadd(acc, part[b * nsplit + q]);
+  eloc[b] = acc;
+}
+
 // TFIM local energies.  LDS: z2 [C][N], lc2 = logcosh(z2) [C][N], da1 [C][k*k]
 // (the changed layer-1 values of the current flip), sigma words, reduction.
 __global__ __launch_bounds__(256) void k_cnn_eloc(cnn_geom g, const uint64_t* __restrict__ s, int64_t B, double J,
@@ -756,15 +975,104 @@ void cnn_vjp_partial(vmc_model* m, const uint64_t* s, int64_t B, const double2* 
   VMC_HIP(hipGetLastError());
 }
 
+// The (row tile, window offset) units of k_cnn_eloc64 shared out over its waves, the
+// costliest first to the least loaded wave: EL_NW + 1 offsets, then rt << 16 | ey << 8 | ex.
+// Cost: per pair of taps 4 matrix instructions of 64 cycles and KS steps, per unit about
+// 1 600 cycles of vector work.
+std::vector<int> cnn_eloc_units(const vmc_model* m) {
+  const int k = m->k, win = 2 * k - 1, RT = (m->C + 15) / 16, KS = (m->C + 3) / 4;
+  std::vector<std::pair<int, int>> all;
+  for (int rt = 0; rt < RT; ++rt)
+    for (int ey = 0; ey < win; ++ey)
+      for (int ex = 0; ex < win; ++ex) {
+        const int pairs = std::min(ey + 1, win - ey) * std::min(ex + 1, win - ex);
+        all.push_back({256 * KS * pairs + 1600, rt << 16 | ey << 8 | ex});
+      }
+  std::stable_sort(all.begin(), all.end(), [](auto& a, auto& b) { return a.first > b.first; });
+  std::vector<std::vector<int>> w(EL_NW);
+  std::vector<long> load(EL_NW, 0);
+  for (auto& u : all) {
+    const int q = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+    w[q].push_back(u.second);
+    load[q] += u.first;
+  }
+  std::vector<int> out(EL_NW + 1);
+  for (int q = 0; q < EL_NW; ++q) {
+    out[q] = (int)out.size();
+    out.insert(out.end(), w[q].begin(), w[q].end());
+  }
+  out[EL_NW] = (int)out.size();
+  return out;
+}
+
+namespace {
+size_t eloc64_lds(const cnn_geom& g) {
+  return sizeof(double2) * (size_t)g.C * ((g.N + 1) + std::max(g.N + 1, g.k * g.k * EL_F));
+}
+
+// Local energies through k_cnn_eloc64; false if the sample does not fit its LDS or
+// the workspace limit leaves no room for one work-group's scratch.
+bool eloc64_run(vmc_model* m, vmc_ham* H, const cnn_geom& g, const uint64_t* s, int64_t B, double2* eloc) {
+  vmc_ctx* ctx = m->ctx;
+  const size_t lds = eloc64_lds(g);
+  if (lds + 4096 > lds_limit()) return false;
+  const int ncu = cu_count(ctx), npass = (g.N + EL_F - 1) / EL_F;
+  // one work-group per compute unit; a sample's passes are split over several groups while
+  // that fills idle units: rounds of groups x (the forward pass, about one pass, + passes)
+  int nsplit = 1;
+  double best = INFINITY;
+  for (int q = 1; q <= npass; q *= 2) {
+    const double t = std::ceil((double)B * q / ncu) * (1.0 + (npass + q - 1) / q);
+    if (t < 0.95 * best) {
+      best = t;
+      nsplit = q;
+    }
+  }
+  const size_t per = ws_round(sizeof(double2) * 3 * (size_t)g.C * g.N);
+  const size_t parts = nsplit > 1 ? ws_round(sizeof(double2) * (size_t)B * nsplit) : 0;
+  int64_t groups = std::min<int64_t>(B * nsplit, ncu);
+  if (ctx->ws_limit) {
+    if (ctx->ws_limit < parts + per) return false;
+    groups = std::min<int64_t>(groups, (int64_t)((ctx->ws_limit - parts) / per));
+  }
+  ws_reserve(ctx, per * groups + parts);
+  double2* scr = (double2*)ws_take(ctx, per * groups);
+  double2* out = nsplit > 1 ? (double2*)ws_take(ctx, sizeof(double2) * (size_t)B * nsplit) : eloc;
+  auto launch = [&](auto kern) {
+    allow_lds(kern, lds);
+    kern<<<(unsigned)groups, EL_NT, lds, ctx->stream>>>(g, s, B, nsplit, H->J, H->h, H->bonds, H->n_bonds,
+                                                        m->cnn_units, scr, out);
+    VMC_HIP(hipGetLastError());
+  };
+  if (g.KS == 1)
+    launch(k_cnn_eloc64<1>);
+  else if (g.KS == 2)
+    launch(k_cnn_eloc64<2>);
+  else if (g.KS == 3)
+    launch(k_cnn_eloc64<3>);
+  else if (g.KS == 4)
+    launch(k_cnn_eloc64<4>);
+  else
+    launch(k_cnn_eloc64<0>);
+  if (nsplit > 1) {
+    k_cnn_eloc_add<<<grid_for(B, 256), 256, 0, ctx->stream>>>(out, B, nsplit, eloc);
+    VMC_HIP(hipGetLastError());
+  }
+  return true;
+}
+}  // namespace
+
 void cnn_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, double2* eloc) {
   VMC_REQUIRE(H->kind == HAM_TFIM, "the CNN local energy supports the transverse-field Ising model");
   VMC_REQUIRE(H->Lx == m->Lx && H->Ly == m->Ly, "lattice of the Hamiltonian differs from the CNN's");
   const cnn_geom g = geom(m);
+  const int64_t chunk = std::min<int64_t>(B, kChunk);
+  vmc_ctx* ctx = m->ctx;
+  if (ctx->ws_limit) ws_reserve(ctx, ws_round(sizeof(double2) * chunk * g.C * g.N));  // the limit of the general kernel
+  if (H->h != 0.0 && g.Lx >= 2 * g.k - 1 && g.Ly >= 2 * g.k - 1 && eloc64_run(m, H, g, s, B, eloc)) return;
   const int kk = g.k * g.k;
   const size_t lds = sizeof(double2) * (2 * (size_t)g.C * g.N + (size_t)g.C * kk + 4);
   allow_lds(k_cnn_eloc, lds);
-  vmc_ctx* ctx = m->ctx;
-  const int64_t chunk = std::min<int64_t>(B, kChunk);
   ws_reserve(ctx, ws_round(sizeof(double2) * chunk * g.C * g.N));
   double2* a1 = (double2*)ws_take(ctx, sizeof(double2) * chunk * g.C * g.N);
   for (int64_t b0 = 0; b0 < B; b0 += chunk) {

@@ -160,6 +160,7 @@ struct vmc_model {
   double2* Wt = nullptr;      // RBM: W transposed [N][N_h]
   rbm_move_tables tab[2];     // flip / exchange tables
   double2* cnn_frags = nullptr;  // CNN: weights in the operand layout of the float64 matrix cores (cnn.hip)
+  int* cnn_units = nullptr;      // CNN: work units of the local-energy kernel's waves (cnn.hip)
   // float32 / bfloat16 evaluation (RBM): parameters rounded to the precision,
   // stored as float32; rebuilt when the parameters or the precision change
   uint64_t lowp_version = 0;
@@ -455,6 +456,7 @@ void rbm_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, do
 void rbm_grad(vmc_model* m, const uint64_t* s, int64_t B, void* O, int dtype);
 // cnn.hip
 size_t cnn_frag_count(const vmc_model* m);  // double2 entries of cnn_frags
+std::vector<int> cnn_eloc_units(const vmc_model* m);
 void cnn_set_params(vmc_model* m);          // fills cnn_frags from the parameters
 void cnn_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi);
 void cnn_grad(vmc_model* m, const uint64_t* s, int64_t B, void* O, int dtype);

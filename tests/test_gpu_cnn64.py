@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import synth_inputs as si
-from oracle import cnn as ocnn
+from oracle import cnn as ocnn, lattice as olat
 from gpu_common import dev_bits, dev_c128, assert_logpsi_close, flush
 
 pytestmark = pytest.mark.gpu
@@ -46,3 +46,22 @@ def test_net_tile_edges(ctx, Lx, Ly, C, k, B):
     gv = rng.normal(size=B) + 1j * rng.normal(size=B)
     out = m.log_psi_vjp(s, dev_c128(gv)).cpu().numpy()
     assert np.max(np.abs(out - ref.conj().T @ gv)) <= 1e-10 * scale * np.abs(gv).sum()
+
+
+# 5 and 17 channels (a partial k step, two row tiles); smallest tori of the window
+# path; sites that fill no whole pass; 300 samples (a work-group takes two); one
+# sample (its passes split over work-groups); 25 taps
+@pytest.mark.parametrize("Lx,Ly,C,k,B", [(7, 5, 5, 3, 300), (9, 9, 17, 2, 3), (7, 7, 16, 4, 2), (16, 16, 4, 3, 1),
+                                         (1, 1, 3, 1, 4), (11, 9, 3, 5, 2)])
+def test_local_energy_window_products(ctx, Lx, Ly, C, k, B):
+    flush(f"cnn float64 local energies {Lx}x{Ly} C={C} k={k} B={B}")
+    m, p = _cnn(ctx, Lx, Ly, C, k, 0.4 / np.sqrt(C * k), seed=7 * Lx + C)
+    N = Lx * Ly
+    H = V.Hamiltonian.tfim(ctx, Lx, Ly, min(Lx, Ly) >= 3, 1.0, 3.0)
+    bits = si.random_bits(B, N, seed=8)
+    got = m.local_energy(H, dev_bits(si.pack_bits(bits))).cpu().numpy()
+    f = lambda b: ocnn.log_psi(p, b, Lx, Ly, C, k)
+    for b in list(range(min(B, 4))) + [B - 1]:
+        sp, mel, cnt = olat.connected("tfim", bits[b], Lx, Ly, min(Lx, Ly) >= 3, 1.0, 3.0)
+        terms = mel[:cnt] * np.exp(f(sp[:cnt]) - f(bits[b:b + 1])[0])
+        assert abs(got[b] - terms.sum()) <= 1e-10 * np.abs(terms).sum(), b
