@@ -466,7 +466,7 @@ __device__ __forceinline__ double2 cosh_factor(double2 z, double2& zt) {
   zt = z.x < 0.0 ? make_double2(-z.x, -z.y) : z;
   const double e = exp(-2.0 * zt.x);
   double s, c;
-  sincos(-2.0 * zt.y, &s, &c);
+  m64::fsincos(-2.0 * zt.y, &s, &c);
   return make_double2(fma(e, c, 1.0), e * s);
 }
 

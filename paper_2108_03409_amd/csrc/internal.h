@@ -14,6 +14,7 @@
 #include <utility>
 #include <vector>
 
+#include "math64.h"
 #include "nqsvmc.h"
 
 // ---------------------------------------------------------------- errors --
@@ -270,11 +271,11 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
 }
 __device__ __forceinline__ double2 cexp(double2 z) {
   double e = exp(z.x), s, c;
-  sincos(z.y, &s, &c);
+  m64::fsincos(z.y, &s, &c);
   return make_double2(e * c, e * s);
 }
 __device__ __forceinline__ double2 clog(double2 z) {
-  return make_double2(log(hypot(z.x, z.y)), atan2(z.y, z.x));
+  return make_double2(m64::flog(hypot(z.x, z.y)), m64::fatan2(z.y, z.x));
 }
 
 // log cosh z without overflow: with z~ = +-z such that Re z~ >= 0,
@@ -282,11 +283,11 @@ __device__ __forceinline__ double2 clog(double2 z) {
 __device__ __forceinline__ double2 clogcosh(double2 z) {
   if (z.x < 0.0) z = make_double2(-z.x, -z.y);
   double e = exp(-2.0 * z.x), s, c;
-  sincos(-2.0 * z.y, &s, &c);
+  m64::fsincos(-2.0 * z.y, &s, &c);
   double er = e * c, ei = e * s;  // e^{-2 z~}
   // log|1 + w| = 0.5 log1p(2 Re w + |w|^2)
-  double lr = 0.5 * log1p(2.0 * er + er * er + ei * ei);
-  double li = atan2(ei, 1.0 + er);
+  double lr = 0.5 * m64::flog1p(2.0 * er + er * er + ei * ei);
+  double li = m64::fatan2(ei, 1.0 + er);
   return make_double2(z.x - 0.69314718055994530942 + lr, z.y + li);
 }
 
@@ -295,7 +296,7 @@ __device__ __forceinline__ double2 clogcosh(double2 z) {
 // a shift by 2 pi i would change the result.
 __device__ __forceinline__ double2 clogcosh_pv(double2 z) {
   double2 r = clogcosh(z);
-  r.y = remainder(r.y, 6.283185307179586477);
+  r.y = m64::wrap_2pi(r.y);
   return r;
 }
 
@@ -304,7 +305,7 @@ __device__ __forceinline__ double2 ctanh(double2 z) {
   bool neg = z.x < 0.0;
   if (neg) z = make_double2(-z.x, -z.y);
   double e = exp(-2.0 * z.x), s, c;
-  sincos(-2.0 * z.y, &s, &c);
+  m64::fsincos(-2.0 * z.y, &s, &c);
   double2 w = make_double2(e * c, e * s);
   double2 r = cdiv(make_double2(1.0 - w.x, -w.y), make_double2(1.0 + w.x, w.y));
   return neg ? make_double2(-r.x, -r.y) : r;

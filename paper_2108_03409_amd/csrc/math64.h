@@ -1,0 +1,143 @@
+// Float64 elementary functions for kernels whose time is elementary functions:
+// straight-line code with fewer instructions than the device library's (float64
+// instructions: sincos 30 for 109, log 30 for 76, log1p 38 for 113, remainder by
+// 2 pi 3 for 29; atan2 as many but 82 for 105 in all).  Polynomials interpolate the reduced
+// functions at Chebyshev nodes (approximation error below 2e-17 of the result);
+// measured against 113-bit arithmetic over 4 million arguments: log 0.9 ulp, log1p
+// 1.3, atan2 2.2, sine and cosine 1.2e-16 absolute for |x| < 1e5.  Zeros, infinities and
+// NaN follow the C library; larger arguments of sincos go to the library.
+// log psi of an RBM (N = 64, N_h = 256, 16 384 samples, theta included) 88.7 -> 76.8 us,
+// CNN log psi (16 x 16, C = 16, k = 4, 1 024 samples) 258 -> 233 us, its local energies
+// (512 samples) 2.15 -> 2.07 ms.
+#pragma once
+
+#include <cmath>
+
+#ifdef __HIP_DEVICE_COMPILE__
+#define M64_MANT(x) __builtin_amdgcn_frexp_mant(x)
+#define M64_EXPO(x) __builtin_amdgcn_frexp_exp(x)
+#define M64_RCP(x) __builtin_amdgcn_rcp(x)
+#else
+inline double m64_mant_host(double x) { int e; return std::frexp(x, &e); }
+inline int m64_expo_host(double x) { int e; std::frexp(x, &e); return std::isfinite(x) ? e : 0; }
+#define M64_MANT(x) m64_mant_host(x)
+#define M64_EXPO(x) m64_expo_host(x)
+#define M64_RCP(x) ((double)(1.0f / (float)(x)))
+#endif
+#ifndef M64_FN
+#define M64_FN __host__ __device__ __forceinline__
+#endif
+
+namespace m64 {
+
+// a / b for b in the normal range and a quotient that neither over- nor
+// underflows: reciprocal refined by two Newton steps, one residual correction
+M64_FN double fdiv(double a, double b) {
+  double r = M64_RCP(b);
+  r = fma(fma(-b, r, 1.0), r, r);
+  r = fma(fma(-b, r, 1.0), r, r);
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
+}
+
+// sin and cos of x through r = x - n pi/2, |r| <= pi/4
+M64_FN void fsincos(double x, double* sp, double* cp) {
+  if (!(fabs(x) < 1e5)) {
+    ::sincos(x, sp, cp);
+    return;
+  }
+  const double n = rint(x * 0.63661977236758134);
+  double r = fma(n, -0x1.921fb54442d18p+0, x);
+  r = fma(n, -0x1.1a62633145c07p-54, r);
+  const double z = r * r;
+  double s = 0x1.5e0b05bff20f2p-33;
+  s = fma(s, z, -0x1.ae600aca92c64p-26);
+  s = fma(s, z, 0x1.71de379654304p-19);
+  s = fma(s, z, -0x1.a01a019e83816p-13);
+  s = fma(s, z, 0x1.1111111110bb2p-7);
+  s = fma(s, z, -0x1.5555555555555p-3);
+  s = fma(r * z, s, r);
+  double c = -0x1.907d8f29fe831p-37;
+  c = fma(c, z, 0x1.1eeb68cd22f56p-29);
+  c = fma(c, z, -0x1.27e4fa17bf139p-22);
+  c = fma(c, z, 0x1.a01a019f4e9b4p-16);
+  c = fma(c, z, -0x1.6c16c16c16967p-10);
+  c = fma(c, z, 0x1.5555555555555p-5);
+  const double h = fma(-0.5, z, 1.0);  // 1 - z/2 and its rounding error
+  c = h + fma(z * z, c, fma(-0.5, z, 1.0 - h));
+  const int q = (int)n;
+  const double a = (q & 1) ? c : s, b = (q & 1) ? s : c;
+  *sp = (q & 2) ? -a : a;
+  *cp = ((q + 1) & 2) ? -b : b;
+}
+
+// log(1 + f) + e ln 2 for 1 + f in [sqrt(1/2), sqrt(2)]: with s = f / (2 + f),
+// log(1 + f) = 2 atanh(s) = f - s (f - R(s^2)), R = 2 s^2 (1/3 + s^2 / 5 + ...)
+M64_FN double log_poly(double f, double e) {
+  const double s = fdiv(f, 2.0 + f), z = s * s;
+  double p = 0x1.2b5f6ba5f7c76p-3;
+  p = fma(p, z, 0x1.39fdccad06992p-3);
+  p = fma(p, z, 0x1.7462b91d6e050p-3);
+  p = fma(p, z, 0x1.c71c62d5dea59p-3);
+  p = fma(p, z, 0x1.2492492dfd8bfp-2);
+  p = fma(p, z, 0x1.9999999995273p-2);
+  p = fma(p, z, 0x1.5555555555558p-1);
+  const double t = fma(-s, fma(-p, z, f), e * 0x1.abc9e3b39803fp-56);
+  return fma(e, 0x1.62e42fefa39efp-1, f + t);
+}
+
+M64_FN double flog(double x) {
+  double m = M64_MANT(x);
+  int e = M64_EXPO(x);
+  const bool lo = m < 0.70710678118654752;
+  m = lo ? m + m : m;
+  e -= lo ? 1 : 0;
+  const double v = log_poly(m - 1.0, (double)e);
+  return x > 0.0 ? (x < INFINITY ? v : x) : (x == 0.0 ? -INFINITY : NAN);  // x NaN: not > 0, not == 0
+}
+
+// log(1 + t), t >= -1: the rounding error of 1 + t is carried into the reduced argument
+M64_FN double flog1p(double t) {
+  const double u = 1.0 + t, bp = u - 1.0, c = (1.0 - (u - bp)) + (t - bp);  // 1 + t = u + c
+  double m = M64_MANT(u);
+  int e = M64_EXPO(u);
+  const bool lo = m < 0.70710678118654752;
+  m = lo ? m + m : m;
+  e -= lo ? 1 : 0;
+  const double v = log_poly((m - 1.0) + ldexp(c, -e), (double)e);
+  return u > 0.0 ? (u < INFINITY ? v : u) : (u == 0.0 ? -INFINITY : NAN);
+}
+
+M64_FN double fatan2(double y, double x) {
+  const double ax = fabs(x), ay = fabs(y), mx = fmax(ax, ay), mn = fmin(ax, ay);
+  const bool hi = mn > 0.41421356237309503 * mx;  // beyond tan(pi/8): atan t = pi/4 + atan((t - 1) / (t + 1))
+  const int sc = -M64_EXPO(mx);                    // the quotient of scaled operands
+  const double sm = ldexp(mx, sc), sn = ldexp(mn, sc);
+  double t = fdiv(hi ? sn - sm : sn, hi ? sn + sm : sm);
+  t = mx == 0.0 ? 0.0 : t;
+  t = mn == INFINITY ? 0.0 : (mx == INFINITY ? 0.0 : t);  // both infinite: pi/4 exactly (hi is false, set below)
+  const double z = t * t;
+  double p = -0x1.3a2b6e74f00e0p-6;
+  p = fma(p, z, 0x1.4160318e023c6p-5);
+  p = fma(p, z, -0x1.a098b9c8d8226p-5);
+  p = fma(p, z, 0x1.dfe61e3086617p-5);
+  p = fma(p, z, -0x1.10fa753389c37p-4);
+  p = fma(p, z, 0x1.3b1262d901bc4p-4);
+  p = fma(p, z, -0x1.745d0b26b4a39p-4);
+  p = fma(p, z, 0x1.c71c718531360p-4);
+  p = fma(p, z, -0x1.24924924360c8p-3);
+  p = fma(p, z, 0x1.999999999934ap-3);
+  p = fma(p, z, -0x1.5555555555555p-2);
+  double a = fma(t * z, p, t);
+  const bool quarter = hi || (mn == INFINITY);
+  a = quarter ? 0.78539816339744831 + (a + 3.0616169978683830e-17) : a;
+  a = ay > ax ? 1.5707963267948966 - (a - 6.1232339957367660e-17) : a;
+  a = std::signbit(x) ? 3.1415926535897931 - (a - 1.2246467991473532e-16) : a;
+  a = copysign(a, y);
+  return (x != x || y != y) ? x + y : a;
+}
+
+// y - 2 pi rint(y / 2 pi) with 2 pi rounded to float64 (as remainder(y, 2 pi)), exact for |y| < 2^50
+M64_FN double wrap_2pi(double y) { return fma(-rint(y * 0.15915494309189535), 6.283185307179586477, y); }
+
+}  // namespace m64
