@@ -111,7 +111,7 @@ M64_FN double flog1p(double t) {
 M64_FN double fatan2(double y, double x) {
   const double ax = fabs(x), ay = fabs(y), mx = fmax(ax, ay), mn = fmin(ax, ay);
   const bool hi = mn > 0.41421356237309503 * mx;  // beyond tan(pi/8): atan t = pi/4 + atan((t - 1) / (t + 1))
-  const int sc = -M64_EXPO(mx);                    // the quotient of scaled operands
+  const int sc = 1 - M64_EXPO(mx);                 // the quotient of operands scaled to mx in [1, 2)
   const double sm = ldexp(mx, sc), sn = ldexp(mn, sc);
   double t = fdiv(hi ? sn - sm : sn, hi ? sn + sm : sm);
   t = mx == 0.0 ? 0.0 : t;
