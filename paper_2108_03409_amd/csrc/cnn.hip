@@ -221,6 +221,7 @@ __device__ __forceinline__ void conv_tiles(const cnn_geom& g, const double2* __r
 
 constexpr int NET_NT = 512;
 constexpr int NET_NW = NET_NT / 64;
+constexpr int NP = 2;  // tiles of a wave that share an operand
 enum { NET_LOGPSI = 0, NET_ROWS = 1, NET_VJP = 2 };
 
 // One sample per work-group, every contraction of the network as float64 matrix
@@ -242,13 +243,13 @@ enum { NET_LOGPSI = 0, NET_ROWS = 1, NET_VJP = 2 };
 // layer-2 products: 83 us a sample and compute unit at C = 16, k = 4, N = 256 at
 // the full rate, 0.33 of the 0.60 ms below); the rest is the transcendental
 // functions of the two activations and the operand latency of two waves per SIMD
-// (four waves per SIMD spill at 128 registers: log psi 0.31 ms).  The loops over
+// (16 waves a group with one tile each: 0.61 ms).  The loops over
 // taps and positions per output that this replaces spent their time on index
 // arithmetic and serial sums.
-// 1 024 samples, 16 x 16, C = 16, k = 4: log psi 1.53 -> 0.26 ms, O_k (complex64)
-// 7.92 -> 0.60 ms, reverse-mode product 7.86 -> 0.67 ms.
+// 1 024 samples, 16 x 16, C = 16, k = 4: log psi 1.53 -> 0.21 ms, O_k (complex64)
+// 7.92 -> 0.60 ms, reverse-mode product 7.86 -> 0.66 ms.
 template <int MODE, typename OutT>
-__global__ __launch_bounds__(NET_NT, 2) void k_cnn_net(
+__global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 4 : 2) void k_cnn_net(
     cnn_geom g, const uint64_t* __restrict__ s, int64_t B, int64_t K, OutT* __restrict__ O,
     const double2* __restrict__ gv, double2* __restrict__ part, double2* __restrict__ logpsi) {
   extern __shared__ double2 sm[];
@@ -258,7 +259,7 @@ __global__ __launch_bounds__(NET_NT, 2) void k_cnn_net(
   double2* G2 = sm + C * ld;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
-  const int PT = (N + 15) / 16, PP = (PT + 1) / 2;  // position tiles, pairs of them
+  const int PT = (N + 15) / 16, PP = (PT + NP - 1) / NP;  // position tiles, groups of them
   const int off_b1 = C * kk, off_W2 = off_b1 + C, off_b2 = off_W2 + C * C * kk;
   for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
     const uint64_t* sb = s + b * g.W;
@@ -285,32 +286,34 @@ __global__ __launch_bounds__(NET_NT, 2) void k_cnn_net(
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int c = rt * 16 + lk + 4 * r, p = pt * 16 + li;
-        if (c < C && p < N) A[c * ld + p] = clogcosh_pv(make_double2(re[r], im[r]));
+        if (c < C && p < N) A[c * ld + p] = clogcosh_pv<false>(make_double2(re[r], im[r]));
       }
     }
     __syncthreads();
     double2 lp = make_double2(0.0, 0.0);
     for (int u = wave; u < g.RT * PP; u += NET_NW) {
-      const int rt = u / PP, pt = 2 * (u - rt * PP);
-      doublex4 re[2], im[2];
+      const int rt = u / PP, pt = NP * (u - rt * PP);
+      doublex4 re[NP], im[NP];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const double2 b2 = g.b2[min(rt * 16 + lk + 4 * r, C - 1)];
-        re[0][r] = re[1][r] = b2.x;
-        im[0][r] = im[1][r] = b2.y;
+        for (int j = 0; j < NP; ++j) {
+          re[j][r] = b2.x;
+          im[j][r] = b2.y;
+        }
       }
-      conv_tiles<2, 1>(g, g.F1, A, ld, rt, pt, lane, re, im);
+      conv_tiles<NP, 1>(g, g.F1, A, ld, rt, pt, lane, re, im);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NP; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int c = rt * 16 + lk + 4 * r, p = (pt + j) * 16 + li;
           if (c < C && p < N) {
             const double2 z = make_double2(re[j][r], im[j][r]);
             if constexpr (MODE == NET_LOGPSI)
-              lp = cadd(lp, clogcosh(z));
+              lp = cadd(lp, clogcosh<false>(z));
             else
-              G2[c * ld + p] = ctanh(z);
+              G2[c * ld + p] = ctanh<false>(z);
           }
         }
     }
@@ -327,30 +330,30 @@ __global__ __launch_bounds__(NET_NT, 2) void k_cnn_net(
     }
     __syncthreads();
     // dW2: two tiles of 16 columns (c', t) share the rows g2
-    const int CT = (C * kk + 15) / 16, CP = (CT + 1) / 2;
+    const int CT = (C * kk + 15) / 16, CP = (CT + NP - 1) / NP;
     for (int u = wave; u < g.RT * CP; u += NET_NW) {
-      const int rt = u / CP, ct = 2 * (u - rt * CP);
+      const int rt = u / CP, ct = NP * (u - rt * CP);
       const double2* arow = G2 + min(rt * 16 + li, C - 1) * ld;
-      const double2* brow[2];
-      int dy[2], dx[2];
+      const double2* brow[NP];
+      int dy[NP], dx[NP];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < NP; ++j) {
         const int n = min((ct + j) * 16 + li, C * kk - 1), ci = n / kk, t = n - ci * kk;
         brow[j] = A + ci * ld;
         dy[j] = t / g.k;
         dx[j] = t - dy[j] * g.k;
       }
-      doublex4 re[2], im[2];
-      re[0] = re[1] = im[0] = im[1] = doublex4{0.0, 0.0, 0.0, 0.0};
+      doublex4 re[NP], im[NP];
+      for (int j = 0; j < NP; ++j) re[j] = im[j] = doublex4{0.0, 0.0, 0.0, 0.0};
       for (int p0 = 0; p0 < N; p0 += 4) {
         const int p = min(p0 + lk, N - 1);
         int y, x;
         pos_yx(g, p, y, x);
         double2 a = arow[p];
         if (p0 + lk >= N) a = make_double2(0.0, 0.0);
-        double2 bv[2];
+        double2 bv[NP];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NP; ++j) {
           int yy = y + dy[j], xx = x + dx[j];
           yy -= yy >= g.Ly ? g.Ly : 0;
           xx -= xx >= g.Lx ? g.Lx : 0;
@@ -358,18 +361,18 @@ __global__ __launch_bounds__(NET_NT, 2) void k_cnn_net(
         }
         const double na = -a.y;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NP; ++j) {
           re[j] = mfma64(a.x, bv[j].x, re[j]);
           im[j] = mfma64(a.x, bv[j].y, im[j]);
         }
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NP; ++j) {
           re[j] = mfma64(na, bv[j].y, re[j]);
           im[j] = mfma64(a.y, bv[j].x, im[j]);
         }
       }
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NP; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int c = rt * 16 + lk + 4 * r, n = (ct + j) * 16 + li;
@@ -385,12 +388,12 @@ __global__ __launch_bounds__(NET_NT, 2) void k_cnn_net(
     __syncthreads();  // a1 is no longer read
     // g1 = tanh(z1) d log psi / d a1 -> A
     for (int u = wave; u < g.RT * PP; u += NET_NW) {
-      const int rt = u / PP, pt = 2 * (u - rt * PP);
-      doublex4 re[2], im[2];
-      re[0] = re[1] = im[0] = im[1] = doublex4{0.0, 0.0, 0.0, 0.0};
-      conv_tiles<2, -1>(g, g.F2, G2, ld, rt, pt, lane, re, im);
+      const int rt = u / PP, pt = NP * (u - rt * PP);
+      doublex4 re[NP], im[NP];
+      for (int j = 0; j < NP; ++j) re[j] = im[j] = doublex4{0.0, 0.0, 0.0, 0.0};
+      conv_tiles<NP, -1>(g, g.F2, G2, ld, rt, pt, lane, re, im);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < NP; ++j) {
         if (pt + j >= PT) break;
         doublex4 zr, zi;
         z1_tile(g, sb, rt, pt + j, lane, zr, zi);
@@ -398,7 +401,7 @@ __global__ __launch_bounds__(NET_NT, 2) void k_cnn_net(
         for (int r = 0; r < 4; ++r) {
           const int c = rt * 16 + lk + 4 * r, p = (pt + j) * 16 + li;
           if (c < C && p < N)
-            A[c * ld + p] = cmul(make_double2(re[j][r], im[j][r]), ctanh(make_double2(zr[r], zi[r])));
+            A[c * ld + p] = cmul(make_double2(re[j][r], im[j][r]), ctanh<false>(make_double2(zr[r], zi[r])));
         }
       }
     }
@@ -457,7 +460,7 @@ __global__ __launch_bounds__(NET_NT, 2) void k_cnn_net(
   }
 }
 
-constexpr int EL_NT = 512;
+constexpr int EL_NT = 1024;
 constexpr int EL_NW = EL_NT / 64;
 constexpr int EL_F = 16;  // flips per pass: the columns of one matrix-core operand
 
@@ -466,7 +469,7 @@ __device__ __forceinline__ double2 cosh_factor(double2 z, double2& zt) {
   zt = z.x < 0.0 ? make_double2(-z.x, -z.y) : z;
   const double e = exp(-2.0 * zt.x);
   double s, c;
-  m64::fsincos(-2.0 * zt.y, &s, &c);
+  m64::fsincos<false>(-2.0 * zt.y, &s, &c);
   return make_double2(fma(e, c, 1.0), e * s);
 }
 
@@ -486,11 +489,12 @@ __device__ __forceinline__ double2 cosh_factor(double2 z, double2& zt) {
 // 1 / (1 + e^{-2 z~}) of the work-group's sample in global scratch.
 //
 // Bound: the float64 matrix cores and the float64 vector work of the factors, which
-// hardly overlap: the matrix pipe is busy 46% of the cycles (4 C^2 k^4 N real
+// hardly overlap: the matrix pipe is busy 50% of the cycles (4 C^2 k^4 N real
 // multiply-adds a sample, 443 us a compute unit at C = 16, k = 4, N = 256), vector
-// issue takes 37% (counters).  512 samples of that network: 25.2 -> 2.13 ms.
+// issue takes 44% (counters).  512 samples of that network: 25.2 -> 1.92 ms (2.03 ms
+// with 8 instead of 16 waves a group).
 template <int KSC>
-__global__ __launch_bounds__(EL_NT, 2) void k_cnn_eloc64(cnn_geom g, const uint64_t* __restrict__ s, int64_t B,
+__global__ __launch_bounds__(EL_NT, 4) void k_cnn_eloc64(cnn_geom g, const uint64_t* __restrict__ s, int64_t B,
                                                          int nsplit, double J, double h,
                                                          const int2* __restrict__ bonds, int n_bonds,
                                                          const int* __restrict__ units, double2* __restrict__ scr,
@@ -524,7 +528,7 @@ __global__ __launch_bounds__(EL_NT, 2) void k_cnn_eloc64(cnn_geom g, const uint6
       for (int r = 0; r < 4; ++r) {
         const int c = rt * 16 + lk + 4 * r, p = pt * 16 + li;
         if (c < C && p < N) {
-          const double2 z = make_double2(re[r], im[r]), a = clogcosh_pv(z);
+          const double2 z = make_double2(re[r], im[r]), a = clogcosh_pv<false>(z);
           DA[c * ld + p] = a;
           z1g[c * N + p] = z;
           a1g[c * N + p] = a;
@@ -533,17 +537,19 @@ __global__ __launch_bounds__(EL_NT, 2) void k_cnn_eloc64(cnn_geom g, const uint6
     }
     __syncthreads();
     for (int u = wave; u < g.RT * PP; u += EL_NW) {
-      const int rt = u / PP, pt = 2 * (u - rt * PP);
-      doublex4 re[2], im[2];
+      const int rt = u / PP, pt = NP * (u - rt * PP);
+      doublex4 re[NP], im[NP];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const double2 b2 = g.b2[min(rt * 16 + lk + 4 * r, C - 1)];
-        re[0][r] = re[1][r] = b2.x;
-        im[0][r] = im[1][r] = b2.y;
+        for (int j = 0; j < NP; ++j) {
+          re[j][r] = b2.x;
+          im[j][r] = b2.y;
+        }
       }
-      conv_tiles<2, 1>(g, g.F1, DA, ld, rt, pt, lane, re, im);
+      conv_tiles<NP, 1>(g, g.F1, DA, ld, rt, pt, lane, re, im);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NP; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int c = rt * 16 + lk + 4 * r, p = (pt + j) * 16 + li;
@@ -577,7 +583,7 @@ __global__ __launch_bounds__(EL_NT, 2) void k_cnn_eloc64(cnn_geom g, const uint6
         const int p = y * g.Lx + x;
         const double ds = -2.0 * sig_at(sb, f);
         const double2 z = z1g[c * N + p], w = g.W1[c * kk + t];
-        DA[e] = csub(clogcosh_pv(make_double2(fma(ds, w.x, z.x), fma(ds, w.y, z.y))), a1g[c * N + p]);
+        DA[e] = csub(clogcosh_pv<false>(make_double2(fma(ds, w.x, z.x), fma(ds, w.y, z.y))), a1g[c * N + p]);
       }
       __syncthreads();
       int fy, fx;

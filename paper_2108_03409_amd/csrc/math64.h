@@ -4,8 +4,8 @@
 // 2 pi 3 for 29; atan2 as many but 82 for 105 in all).  Polynomials interpolate the reduced
 // functions at Chebyshev nodes (approximation error below 2e-17 of the result);
 // measured against 113-bit arithmetic over 4 million arguments: log 0.9 ulp, log1p
-// 1.3, atan2 2.2, sine and cosine 1.2e-16 absolute for |x| < 1e5.  Zeros, infinities and
-// NaN follow the C library; larger arguments of sincos go to the library.
+// 1.3, atan2 2.2, sine and cosine 1.2e-16 absolute for |x| < 1e5 and 1.7e-16 for |x| < 2^53.  Zeros, infinities and
+// NaN follow the C library.
 // log psi of an RBM (N = 64, N_h = 256, 16 384 samples, theta included) 88.7 -> 76.8 us,
 // CNN log psi (16 x 16, C = 16, k = 4, 1 024 samples) 258 -> 233 us, its local energies
 // (512 samples) 2.15 -> 2.07 ms.
@@ -40,15 +40,32 @@ M64_FN double fdiv(double a, double b) {
   return fma(fma(-b, q, a), r, q);
 }
 
-// sin and cos of x through r = x - n pi/2, |r| <= pi/4
+// sin and cos of x through r = x - n pi/2, |r| <= pi/4, n = rint(2 x / pi).  x - n P1
+// with P1 = fl(pi/2) is exact (both are multiples of 2^-52 and the difference is below
+// 2), so the remaining error is that of n (pi/2 - P1).  From 1e5 on the rounding of
+// 2 x / pi can be off by an integer, which a second step takes back; LIB: from
+// 2^54 on the library's sincos (its reduction keeps many registers in use); otherwise, as
+// neighbouring arguments are then 4 or more apart, a multiple of pi/2 next to x stands for x.
+template <bool LIB = true>
 M64_FN void fsincos(double x, double* sp, double* cp) {
-  if (!(fabs(x) < 1e5)) {
-    ::sincos(x, sp, cp);
-    return;
-  }
-  const double n = rint(x * 0.63661977236758134);
+  double n = rint(x * 0.63661977236758134);
   double r = fma(n, -0x1.921fb54442d18p+0, x);
   r = fma(n, -0x1.1a62633145c07p-54, r);
+  int q = (int)n;
+  if (!(fabs(x) < 1e5)) {
+    r = fma(n, 0x1.f1976b7ed8fbcp-110, r);
+    const double n2 = rint(r * 0.63661977236758134);
+    r = fma(n2, -0x1.921fb54442d18p+0, r);
+    r = fma(n2, -0x1.1a62633145c07p-54, r);
+    if (!(fabs(x) < 0x1p54)) {
+      if (LIB) {
+        ::sincos(x, sp, cp);
+        return;
+      }
+      r = x - x;  // 0, or NaN for an infinite x
+    }
+    q = (int)(n - 4.0 * floor(0.25 * n)) + (int)n2;
+  }
   const double z = r * r;
   double s = 0x1.5e0b05bff20f2p-33;
   s = fma(s, z, -0x1.ae600aca92c64p-26);
@@ -65,7 +82,6 @@ M64_FN void fsincos(double x, double* sp, double* cp) {
   c = fma(c, z, 0x1.5555555555555p-5);
   const double h = fma(-0.5, z, 1.0);  // 1 - z/2 and its rounding error
   c = h + fma(z * z, c, fma(-0.5, z, 1.0 - h));
-  const int q = (int)n;
   const double a = (q & 1) ? c : s, b = (q & 1) ? s : c;
   *sp = (q & 2) ? -a : a;
   *cp = ((q + 1) & 2) ? -b : b;
