@@ -895,6 +895,277 @@ __global__ __launch_bounds__(256) void k_cnn_metropolis(cnn_geom g, int n_chains
   if (tid == 0) acc[c] = accepted;
 }
 
+constexpr int MH_NT = 512, MH_NW = MH_NT / 64;
+constexpr int MH_MT = 2;  // column tiles of 16 (tap, output channel) pairs per wave, at most
+constexpr int MH_KS = 4;  // k steps of 4 input channels, at most
+constexpr int MH_OUT = 2; // window outputs per thread, at most: C (2k-1)^2 <= 784
+
+// Metropolis chains for networks of at most 16 channels and 4 x 4 taps: one
+// work-group of eight waves per chain.  A proposal at site f changes z1 at f - t1 and
+// z2 at f - t1 - t2; its layer-2 change is one small matrix product
+//   P[t1][t2, c] = sum_{c'} dA[t1][c'] W2[c][c'][t2]
+// (rows t1, columns (t2, c), no entry wasted at 16 channels and 16 taps) on the float64
+// matrix cores, the weights held in registers for the whole launch, followed by the
+// window sums dz[c][e] = sum_{t1 + t2 = e} P[t1][t2, c] from LDS.  The acceptance uses
+//   Re(log psi' - log psi) = sum (|x'| - |x|) + log(prod q' / prod q) / 2,
+//   q = |1 + e^{-2 z~}|^2, z = x + iy, z~ = +-z with real part |x|,
+// one logarithm per thread instead of one per output.  State in global memory, channel
+// fastest: z1, a1, z2 and q per (position, channel); it is rebuilt from the
+// configuration at every launch.  LDS: P (or a1 while the state is built), dA, the
+// configuration, and sites and log u of 64 steps drawn at once.
+//
+// Bound: the latency of four barrier-separated phases per step, with two work-groups on
+// a compute unit (their 66 KB of P); the matrix pipe is busy 28% of the cycles, vector
+// issue takes 36% (counters).  1 024 chains x 256 steps, 16 x 16, C = 16, k = 4:
+// 84.6 -> 6.36 ms; with four waves a chain, whose weights and outputs do not fit their
+// registers, 9.1 ms.
+__global__ __launch_bounds__(MH_NT, 4) void k_cnn_mh64(cnn_geom g, int n_chains, int chain0, uint64_t* __restrict__ bits,
+                                                     uint2 key, uint64_t t0, int init, int64_t therm_steps,
+                                                     int64_t n_record, int sweep, uint64_t* __restrict__ s_out,
+                                                     double2* __restrict__ logpsi_out,
+                                                     unsigned long long* __restrict__ acc_out,
+                                                     double2* __restrict__ scr) {
+  extern __shared__ double2 sm[];
+  __shared__ double2 DAs[16 * 17];  // dA[t1][c'], rows of 17; zero outside the network
+  __shared__ double red[2][MH_NW];
+  __shared__ double2 red2[MH_NW];
+  __shared__ double lus[64];  // log u
+  __shared__ int sites[64];
+  __shared__ uint64_t cb[64];
+  const int C = g.C, N = g.N, k = g.k, kk = k * k, win = 2 * k - 1, CN = C * N, ld = N + 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  const int c = chain0 + (int)blockIdx.x;
+  const int M = C * kk, MT = (M + 15) / 16, PS = 16 * MT + 1, KS = g.KS;
+  double2* P = sm;
+  double2* Z1 = scr + (size_t)blockIdx.x * ((7 * (size_t)CN + 1) / 2);
+  double2* A1 = Z1 + CN;
+  double2* Z2 = A1 + CN;
+  double* Q = (double*)(Z2 + CN);
+  for (int e = tid; e < 16 * 17; e += MH_NT) DAs[e] = make_double2(0.0, 0.0);
+  if (init) {
+    if (tid == 0)
+      for (int w = 0; w < g.W; ++w) {
+        uint4 y = philox(make_uint4((uint32_t)c, (uint32_t)(w >> 1), 0u, 2u), key);
+        uint64_t word = (w & 1) ? ((uint64_t)y.z | ((uint64_t)y.w << 32)) : ((uint64_t)y.x | ((uint64_t)y.y << 32));
+        const int rem = N - 64 * w;
+        if (rem < 64) word &= (1ull << rem) - 1ull;
+        cb[w] = word;
+      }
+  } else {
+    for (int w = tid; w < g.W; w += MH_NT) cb[w] = bits[(int64_t)c * g.W + w];
+  }
+  __syncthreads();
+  // the state of the configuration
+  const int PT = (N + 15) / 16, PP = (PT + 1) / 2;
+  for (int pt = wave; pt < PT; pt += MH_NW) {
+    doublex4 re, im;
+    z1_tile(g, cb, 0, pt, lane, re, im);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int ch = lk + 4 * r, p = pt * 16 + li;
+      if (ch < C && p < N) {
+        const double2 z = make_double2(re[r], im[r]), a = clogcosh_pv<false>(z);
+        P[ch * ld + p] = a;
+        Z1[p * C + ch] = z;
+        A1[p * C + ch] = a;
+      }
+    }
+  }
+  __syncthreads();
+  for (int u = wave; u < PP; u += MH_NW) {
+    doublex4 re[2], im[2];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double2 b2 = g.b2[min(lk + 4 * r, C - 1)];
+      re[0][r] = re[1][r] = b2.x;
+      im[0][r] = im[1][r] = b2.y;
+    }
+    conv_tiles<2, 1>(g, g.F1, P, ld, 0, 2 * u, lane, re, im);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int ch = lk + 4 * r, p = (2 * u + j) * 16 + li;
+        if (ch < C && p < N) {
+          const double2 z = make_double2(re[j][r], im[j][r]);
+          double2 zt;
+          const double2 q = cosh_factor(z, zt);
+          Z2[p * C + ch] = z;
+          Q[p * C + ch] = fma(q.x, q.x, q.y * q.y);
+        }
+      }
+  }
+  // operand columns of this wave's tiles: W2[c][c'][t2] for column (t2, c) = 16 tile + li, c' = 4 ks + lk
+  double2 wb[MH_MT][MH_KS];
+#pragma unroll
+  for (int i = 0; i < MH_MT; ++i)
+#pragma unroll
+    for (int ks = 0; ks < MH_KS; ++ks) {
+      const int m = (wave + MH_NW * i) * 16 + li, t2 = m / C, co = m - t2 * C, ci = 4 * ks + lk;
+      wb[i][ks] = (m < M && ci < C) ? g.W2[(co * C + ci) * kk + t2] : make_double2(0.0, 0.0);
+    }
+  // layer-1 change of this thread: tap t1, channel c1
+  const int t1 = tid / C, c1 = tid - t1 * C, dy1 = t1 / k, dx1 = t1 - dy1 * k;
+  const bool has1 = tid < M;
+  const double2 w1 = has1 ? g.W1[c1 * kk + t1] : make_double2(0.0, 0.0);
+  // window outputs of this thread: offsets in the order of their term counts (largest
+  // first), so that the lanes of a wave run loops of similar length
+  int oe[MH_OUT];  // ey << 16 | ex << 8 | channel
+  bool on[MH_OUT]; // outputs past the last repeat it and are left out of the sums
+#pragma unroll
+  for (int q = 0; q < MH_OUT; ++q) {
+    const int o = min(tid + MH_NT * q, C * win * win - 1), r = o / C;
+    on[q] = tid + MH_NT * q < C * win * win;
+    oe[q] = -1;
+    int seen = 0;
+    for (int cnt = kk; cnt > 0 && oe[q] < 0; --cnt)
+      for (int e = 0; e < win * win; ++e) {
+        const int ey = e / win, ex = e - ey * win;
+        if (min(ey + 1, win - ey) * min(ex + 1, win - ex) != cnt) continue;
+        if (seen++ == r) {
+          oe[q] = ey << 16 | ex << 8 | (o - r * C);
+          break;
+        }
+      }
+  }
+  const double2* p0[MH_OUT];  // first term of the window sum; nx terms PS - C apart, ny rows
+  int nyx[MH_OUT];
+#pragma unroll
+  for (int q = 0; q < MH_OUT; ++q) {
+    const int ey = oe[q] >> 16, ex = (oe[q] >> 8) & 255;
+    const int ylo = max(0, ey - k + 1), yhi = min(k - 1, ey), xlo = max(0, ex - k + 1), xhi = min(k - 1, ex);
+    p0[q] = P + (ylo * k + xlo) * PS + ((ey - ylo) * k + ex - xlo) * C + (oe[q] & 255);
+    nyx[q] = (yhi - ylo + 1) << 8 | (xhi - xlo + 1);
+  }
+  __syncthreads();
+  unsigned long long accepted = 0;
+  const int64_t total = therm_steps + n_record * sweep;
+  for (int64_t step = 0; step < total; ++step) {
+    const int sl = (int)(step & 63);
+    if (sl == 0) {
+      if (tid < 64) {
+        const uint64_t t = t0 + (uint64_t)step + (uint64_t)tid;
+        const uint4 x = philox(make_uint4((uint32_t)c, (uint32_t)t, (uint32_t)(t >> 32), 0u), key);
+        sites[tid] = (int)to_index(x.x, (uint32_t)N);
+        lus[tid] = m64::flog(to_uniform(x.y, x.z));
+      }
+      __syncthreads();
+    }
+    const int site = __builtin_amdgcn_readfirstlane(sites[sl]);
+    const double lu = lus[sl];
+    const double ds = -2.0 * sig_at(cb, site);
+    int sy, sx;
+    pos_yx(g, site, sy, sx);
+    // the window's state, in flight over the products
+    double2 z2v[MH_OUT];
+    double qv[MH_OUT];
+    int at[MH_OUT];
+#pragma unroll
+    for (int q = 0; q < MH_OUT; ++q) {
+      int y = sy - (oe[q] >> 16), x = sx - ((oe[q] >> 8) & 255);
+      y += y < 0 ? g.Ly : 0;
+      x += x < 0 ? g.Lx : 0;
+      at[q] = (y * g.Lx + x) * C + (oe[q] & 255);
+      z2v[q] = Z2[at[q]];
+      qv[q] = Q[at[q]];
+    }
+    int at1 = 0;
+    double2 z1n = make_double2(0.0, 0.0), a1n = z1n;
+    if (has1) {
+      int y = sy - dy1, x = sx - dx1;
+      y += y < 0 ? g.Ly : 0;
+      x += x < 0 ? g.Lx : 0;
+      at1 = (y * g.Lx + x) * C + c1;
+      const double2 z = Z1[at1], a = A1[at1];
+      z1n = make_double2(fma(ds, w1.x, z.x), fma(ds, w1.y, z.y));
+      a1n = clogcosh_pv<false>(z1n);
+      DAs[t1 * 17 + c1] = csub(a1n, a);
+    }
+    __syncthreads();
+    {
+      double2 a[MH_KS];
+#pragma unroll
+      for (int ks = 0; ks < MH_KS; ++ks) a[ks] = DAs[li * 17 + 4 * ks + lk];
+#pragma unroll
+      for (int i = 0; i < MH_MT; ++i) {
+        const int tile = wave + MH_NW * i;
+        if (tile >= MT) break;
+        doublex4 re0 = doublex4{0.0, 0.0, 0.0, 0.0}, re1 = re0, im0 = re0, im1 = re0;
+#pragma unroll
+        for (int ks = 0; ks < MH_KS; ++ks) {
+          if (ks >= KS) break;
+          re0 = mfma64(a[ks].x, wb[i][ks].x, re0);
+          im0 = mfma64(a[ks].x, wb[i][ks].y, im0);
+          re1 = mfma64(-a[ks].y, wb[i][ks].y, re1);
+          im1 = mfma64(a[ks].y, wb[i][ks].x, im1);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (lk + 4 * r < kk)
+            P[(lk + 4 * r) * PS + tile * 16 + li] = make_double2(re0[r] + re1[r], im0[r] + im1[r]);
+      }
+    }
+    __syncthreads();
+    double2 zn[MH_OUT];
+#pragma unroll
+    for (int q = 0; q < MH_OUT; ++q) {
+      double2 dz = make_double2(0.0, 0.0);
+      const double2* row = p0[q];
+      for (int y = nyx[q] >> 8; y > 0; --y, row += k * (PS - C)) {
+        const double2* pp = row;
+        for (int x = nyx[q] & 255; x > 0; --x, pp += PS - C) dz = cadd(dz, *pp);
+      }
+      zn[q] = cadd(z2v[q], dz);
+    }
+    double lin = 0.0, num = 1.0, den = 1.0, qn[MH_OUT];
+#pragma unroll
+    for (int q = 0; q < MH_OUT; ++q) {
+      double2 zt;
+      const double2 f = cosh_factor(zn[q], zt);
+      qn[q] = fma(f.x, f.x, f.y * f.y);
+      lin += on[q] ? zt.x - fabs(z2v[q].x) : 0.0;
+      num *= on[q] ? qn[q] : 1.0;
+      den *= on[q] ? qv[q] : 1.0;
+    }
+    const double part = wave_sum_uniform(2.0 * lin + m64::flog(m64::fdiv(num, den)));
+    if (lane == 0) red[step & 1][wave] = part;
+    __syncthreads();
+    double r = 0.0;
+#pragma unroll
+    for (int w = 0; w < MH_NW; ++w) r += red[step & 1][w];
+    const bool accept = lu < r;  // r >= 0 or u < e^r
+    if (accept) {
+      ++accepted;
+#pragma unroll
+      for (int q = 0; q < MH_OUT; ++q) {
+        if (!on[q]) continue;
+        Z2[at[q]] = zn[q];
+        Q[at[q]] = qn[q];
+      }
+      if (has1) {
+        Z1[at1] = z1n;
+        A1[at1] = a1n;
+      }
+      if (tid == 0) cb[site >> 6] ^= 1ull << (site & 63);
+    }
+    __syncthreads();
+    if (step >= therm_steps && ((step - therm_steps + 1) % sweep) == 0) {
+      const int64_t kr = (step - therm_steps + 1) / sweep - 1;
+      const int64_t row = kr * n_chains + c;
+      for (int w = tid; w < g.W; w += MH_NT) s_out[row * g.W + w] = cb[w];
+      if (logpsi_out) {
+        double2 lp = make_double2(0.0, 0.0);
+        for (int e = tid; e < CN; e += MH_NT) lp = cadd(lp, clogcosh<false>(Z2[e]));
+        lp = block_sum(lp, red2);
+        if (tid == 0) logpsi_out[row] = lp;
+      }
+    }
+  }
+  for (int w = tid; w < g.W; w += MH_NT) bits[(int64_t)c * g.W + w] = cb[w];
+  if (tid == 0) acc_out[c] = accepted;
+}
+
 constexpr int64_t kChunk = 1 << 14;
 
 cnn_geom geom(const vmc_model* m) {
@@ -1096,17 +1367,42 @@ void cnn_sampler_run(vmc_sampler* S, int64_t n_per_chain, uint64_t* s_out, doubl
   VMC_REQUIRE(g.Lx >= 2 * g.k - 1 && g.Ly >= 2 * g.k - 1, "the CNN sampler needs Lx, Ly >= 2 kernel - 1");
   VMC_REQUIRE(g.C * (2 * g.k - 1) * (2 * g.k - 1) <= 8 * 256, "CNN window too large for the sampler");
   const int CN = g.C * g.N, kk = g.k * g.k;
-  const size_t lds = sizeof(double2) * ((size_t)CN + (CN + 1) / 2 + (size_t)g.C * kk + 4) + sizeof(uint64_t) * g.W;
-  allow_lds(k_cnn_metropolis, lds);
   vmc_ctx* ctx = S->ctx;
-  ws_reserve(ctx, ws_round(sizeof(double2) * (size_t)S->opts.n_chains * CN));
-  double2* a1 = (double2*)ws_take(ctx, sizeof(double2) * (size_t)S->opts.n_chains * CN);
+  const int nc = S->opts.n_chains;
   const int64_t therm = S->thermalized ? 0 : (int64_t)S->opts.therm_sweeps * S->opts.sweep_steps;
   const uint2 key = make_uint2((uint32_t)S->opts.seed, (uint32_t)(S->opts.seed >> 32));
-  k_cnn_metropolis<<<S->opts.n_chains, 256, lds, ctx->stream>>>(g, S->opts.n_chains, S->bits, key, S->t,
-                                                                 !S->bits_valid, therm, n_per_chain,
-                                                                 S->opts.sweep_steps, s_out, logpsi_out, S->acc, a1);
-  VMC_HIP(hipGetLastError());
+  const size_t lds0 = sizeof(double2) * ((size_t)CN + (CN + 1) / 2 + (size_t)g.C * kk + 4) + sizeof(uint64_t) * g.W;
+  VMC_REQUIRE(lds0 <= lds_limit(), "CNN too large for the per-sample LDS budget");
+  const size_t ws0 = ws_round(sizeof(double2) * (size_t)nc * CN);
+  if (ctx->ws_limit) ws_reserve(ctx, ws0);  // the limit of the general kernel
+  // Matrix-core chains: up to 16 channels and 4 x 4 taps (one row tile of taps, the weights
+  // in the registers of eight waves).  Their state takes 56 bytes per (position, channel), so
+  // chains run kMhBatch at a time (32 work-groups a compute unit), or as many as the
+  // workspace limit holds; below one, the general kernel, whose scratch is 16 bytes.
+  constexpr int64_t kMhBatch = 8192;
+  const int MT = (g.C * kk + 15) / 16;
+  const size_t lds = sizeof(double2) * std::max<size_t>((size_t)kk * (16 * MT + 1), (size_t)g.C * (g.N + 1));
+  const size_t per = sizeof(double2) * ((7 * (size_t)CN + 1) / 2);
+  int64_t batch = std::min<int64_t>(nc, kMhBatch);
+  if (ctx->ws_limit) batch = std::min<int64_t>(batch, (int64_t)(ctx->ws_limit / per) - 1);
+  if (g.C <= 16 && g.k <= 4 && lds + 8192 <= lds_limit() && batch >= 1) {
+    allow_lds(k_cnn_mh64, lds);
+    ws_reserve(ctx, ws_round(per * batch));
+    double2* scr = (double2*)ws_take(ctx, per * batch);
+    for (int64_t c0 = 0; c0 < nc; c0 += batch) {
+      k_cnn_mh64<<<(unsigned)std::min<int64_t>(batch, nc - c0), MH_NT, lds, ctx->stream>>>(
+          g, nc, (int)c0, S->bits, key, S->t, !S->bits_valid, therm, n_per_chain, S->opts.sweep_steps, s_out,
+          logpsi_out, S->acc, scr);
+      VMC_HIP(hipGetLastError());
+    }
+  } else {
+    allow_lds(k_cnn_metropolis, lds0);
+    ws_reserve(ctx, ws0);
+    double2* a1 = (double2*)ws_take(ctx, sizeof(double2) * (size_t)nc * CN);
+    k_cnn_metropolis<<<nc, 256, lds0, ctx->stream>>>(g, nc, S->bits, key, S->t, !S->bits_valid, therm, n_per_chain,
+                                                     S->opts.sweep_steps, s_out, logpsi_out, S->acc, a1);
+    VMC_HIP(hipGetLastError());
+  }
   S->t += (uint64_t)(therm + n_per_chain * S->opts.sweep_steps);
   S->thermalized = 1;
   S->bits_valid = 1;

@@ -6,7 +6,8 @@ import pytest
 
 import synth_inputs as si
 from oracle import cnn as ocnn, lattice as olat
-from gpu_common import dev_bits, dev_c128, assert_logpsi_close, flush
+from oracle import metropolis as omet
+from gpu_common import dev_bits, dev_c128, host_bits, assert_logpsi_close, flush
 
 pytestmark = pytest.mark.gpu
 
@@ -65,3 +66,53 @@ def test_local_energy_window_products(ctx, Lx, Ly, C, k, B):
         sp, mel, cnt = olat.connected("tfim", bits[b], Lx, Ly, min(Lx, Ly) >= 3, 1.0, 3.0)
         terms = mel[:cnt] * np.exp(f(sp[:cnt]) - f(bits[b:b + 1])[0])
         assert abs(got[b] - terms.sum()) <= 1e-10 * np.abs(terms).sum(), b
+
+
+def _sample(ctx, m, H, nc, per, limit=0):
+    ctx.set_workspace_limit(limit)
+    try:
+        S = V.Sampler(ctx, m, H, proposal=V.PROP_FLIP, n_chains=nc, therm_sweeps=1, seed=11)
+        parts = [S.sample(nc * per) for _ in range(2)]  # the second call restarts from the stored configurations
+    finally:
+        ctx.set_workspace_limit(0)
+    return [torch.cat(x) for x in ([p[0] for p in parts], [p[1] for p in parts])]
+
+
+# smallest torus of 4 x 4 taps; partial k step and row tile; one tap; 17 channels
+# and 5 x 5 taps (the general kernel)
+@pytest.mark.parametrize("Lx,Ly,C,k,nc", [(7, 7, 16, 4, 3), (9, 5, 5, 3, 5), (3, 5, 3, 1, 4), (11, 6, 12, 2, 3),
+                                          (5, 4, 17, 2, 3), (9, 9, 2, 5, 2)])
+def test_sampler_replays_oracle(ctx, Lx, Ly, C, k, nc):
+    flush(f"cnn float64 sampler replay {Lx}x{Ly} C={C} k={k} chains={nc}")
+    per = 2
+    m, p = _cnn(ctx, Lx, Ly, C, k, 0.6 / np.sqrt(C * k), seed=9 * Lx + C)
+    H = V.Hamiltonian.tfim(ctx, Lx, Ly, True, 1.0, 3.0)
+    s, lp = _sample(ctx, m, H, nc, per)
+    s = host_bits(s).reshape(2 * per, nc, -1)
+    ch = omet.Chains(lambda b: ocnn.log_psi(p, b, Lx, Ly, C, k), Lx * Ly, "flip", seed=11, chain_ids=np.arange(nc),
+                     therm_sweeps=1)
+    os_, ol = ch.sample(2 * per)
+    assert ch.near_ties == 0
+    for q in range(2 * per):
+        for c in range(nc):
+            assert np.array_equal(s[q, c], si.pack_bits(os_[q, c])[0]), (q, c)
+    assert_logpsi_close(lp.cpu().numpy(), ol.ravel(), 1e-9)
+
+
+def test_sampler_workspace_limits(ctx):
+    # chains in batches of three, and the general kernel below the state of one batch,
+    # give the chains of the unlimited call
+    flush("cnn float64 sampler under workspace limits")
+    Lx, Ly, C, k, nc = 8, 7, 6, 3, 7
+    m, _ = _cnn(ctx, Lx, Ly, C, k, 0.2, seed=77)
+    H = V.Hamiltonian.tfim(ctx, Lx, Ly, True, 1.0, 3.0)
+    s0, lp0 = _sample(ctx, m, H, nc, 2)
+    per = 56 * C * Lx * Ly
+    general = -(-16 * nc * C * Lx * Ly // 256) * 256
+    for limit in (4 * per + 256, general):
+        s1, lp1 = _sample(ctx, m, H, nc, 2, limit)
+        assert torch.equal(s0, s1), limit
+        assert_logpsi_close(lp1.cpu().numpy(), lp0.cpu().numpy(), 1e-10)
+    with pytest.raises(V.VMCError) as e:
+        _sample(ctx, m, H, nc, 2, general - 256)
+    assert e.value.name == "WORKSPACE"
