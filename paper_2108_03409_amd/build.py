@@ -32,10 +32,10 @@ FLAGS = [
     "-I", INCLUDE, "-I", CSRC,
 ]
 
-# per source: the float64 polynomials of cnn.hip's elementary functions are 64-bit
+# per source: the float64 polynomials of the elementary functions are 64-bit
 # literals, which loop-invariant code motion would keep in registers across the
 # main loops (k_cnn_net 195 instead of 121 registers, k_cnn_eloc64 224 instead of 139)
-FILE_FLAGS = {"cnn.hip": ["-mllvm", "-disable-machine-licm"]}
+FILE_FLAGS = {f: ["-mllvm", "-disable-machine-licm"] for f in ("cnn.hip", "arnqs.hip")}
 
 
 def hipcc() -> str:

@@ -26,6 +26,8 @@ using namespace dev;
 
 namespace {
 
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
 constexpr int AR_NT = 256;
 constexpr int AR_WAVES = AR_NT / 64;
 
@@ -193,173 +195,6 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The same local energies with both masked weight matrices held in LDS (staged
-// once per group) and one wave per configuration.  The connected moves are taken
-// AR_CM at a time and their (move, output) pairs -- output i >= min P of the
-// move -- are laid out over the lanes, so a wave instruction serves several
-// moves when their triangles are short: for each chunk the changes of the
-// hidden units (lanes over (move, unit)), then the new logit and its
-// log-likelihood term per pair, then per-move sums over 16-lane groups.  Moves
-// and pairs are summed in a fixed order (reproducible results).
-constexpr int AR_CM = 4;  // moves per chunk (64 / AR_CM lanes per move in the sums)
-
-template <int NT>
-__global__ __launch_bounds__(NT) void k_ar_eloc_tri(const uint64_t* __restrict__ s, int64_t B, int N, int H,
-                                                       int W, const double* __restrict__ W1mT,
-                                                       const double* __restrict__ W2t, const double* __restrict__ b1,
-                                                       const double* __restrict__ b2, int kind, double J, double hx,
-                                                       const int2* __restrict__ bonds, int n_bonds,
-                                                       double2* __restrict__ eloc) {
-  extern __shared__ double lds[];
-  double* W1s = lds;          // [N][H]
-  double* W2s = W1s + N * H;  // [H][N]
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int per = (3 + AR_CM) * N + (2 + AR_CM) * H + (n_bonds + 1) / 2;  // doubles per wave
-  double* x = W2s + H * N + wave * per;
-  double* l = x + N;
-  double* t = l + N;
-  double* a = t + N;
-  double* hh = a + H;
-  double* DH = hh + H;         // [AR_CM][H] hidden-unit changes of the chunk's moves
-  double* buf = DH + AR_CM * H;  // [AR_CM][N] per-pair log-likelihood changes
-  int* mv = (int*)(buf + AR_CM * N);  // anti-aligned bonds (Heisenberg), bond order
-  for (int e = threadIdx.x; e < N * H; e += NT) {
-    W1s[e] = W1mT[e];
-    W2s[e] = W2t[e];
-  }
-  __syncthreads();
-  const double mel = kind == HAM_TFIM ? -hx : 2.0 * J;
-  const bool offdiag = kind == HAM_TFIM ? hx != 0.0 : J != 0.0;
-  const int grp = lane >> 4, gl = lane & 15;  // 16-lane group of the per-move sums
-  for (int64_t b = (int64_t)blockIdx.x * (NT / 64) + wave; b < B; b += (int64_t)gridDim.x * (NT / 64)) {
-    const uint64_t* srow = s + b * W;
-    for (int i = lane; i < N; i += 64) x[i] = (double)((srow[i >> 6] >> (i & 63)) & 1ull);
-    wave_sync();
-    for (int k = lane; k < H; k += 64) {
-      double acc = b1[k];
-      for (int d = 0; d < N; ++d) acc = fma(W1s[d * H + k], x[d], acc);  // zero beyond the unit's degree
-      a[k] = acc;
-      hh[k] = fmax(acc, 0.0);
-    }
-    wave_sync();
-    for (int i = lane; i < N; i += 64) {
-      double acc = b2[i];
-      for (int k = 0; k < H; ++k) acc = fma(W2s[k * N + i], hh[k], acc);
-      l[i] = acc;
-      t[i] = x[i] * acc - ar_softplus(acc);
-    }
-    // moves: diagonal count and the anti-aligned bond list
-    int n_al = 0, M = 0;
-    for (int q0 = 0; q0 < n_bonds; q0 += 64) {
-      const int q = q0 + lane;
-      bool al = false, anti = false;
-      if (q < n_bonds) {
-        const int2 bd = bonds[q];
-        al = get_bit(srow, bd.x) == get_bit(srow, bd.y);
-        anti = !al;
-      }
-      n_al += __popcll(__ballot(al));
-      const unsigned long long am = __ballot(anti);
-      if (kind == HAM_HEIS && anti) mv[M + __popcll(am & ((1ull << lane) - 1ull))] = q;
-      M += __popcll(am);
-    }
-    if (kind == HAM_TFIM) M = N;
-    if (!offdiag) M = 0;
-    wave_sync();
-    auto move_sites = [&](int m, int& p0, int& p1) {
-      if (kind == HAM_TFIM) {
-        p0 = m;
-        p1 = -1;
-      } else {
-        const int2 bd = bonds[mv[m]];
-        p0 = min(bd.x, bd.y);
-        p1 = max(bd.x, bd.y);
-      }
-    };
-    double e = 0.0;
-    for (int m0 = 0; m0 < M; m0 += AR_CM) {
-      const int cm = min(AR_CM, M - m0);
-      int p0s[AR_CM], p1s[AR_CM], off[AR_CM + 1];
-      off[0] = 0;
-#pragma unroll
-      for (int mm = 0; mm < AR_CM; ++mm) {
-        int p0 = N, p1 = -1;
-        if (mm < cm) move_sites(m0 + mm, p0, p1);
-        p0s[mm] = p0;
-        p1s[mm] = p1;
-        off[mm + 1] = off[mm] + (mm < cm ? N - p0 : 0);
-      }
-      // hidden-unit changes, lanes over (move, unit)
-      for (int q = lane; q < cm * H; q += 64) {
-        const int mm = q / H, k = q - mm * H;
-        int p0 = p0s[0], p1 = p1s[0];
-#pragma unroll
-        for (int r = 1; r < AR_CM; ++r)
-          if (mm == r) {
-            p0 = p0s[r];
-            p1 = p1s[r];
-          }
-        double ap = fma(W1s[p0 * H + k], 1.0 - 2.0 * x[p0], a[k]);
-        if (p1 >= 0) ap = fma(W1s[p1 * H + k], 1.0 - 2.0 * x[p1], ap);
-        DH[q] = fmax(ap, 0.0) - hh[k];  // exactly 0 for units of degree <= p0
-      }
-      wave_sync();
-      // (move, output) pairs over the lanes
-      const int total = off[AR_CM];  // moves past cm add nothing
-      for (int q0 = 0; q0 < total; q0 += 64) {
-        const int q = q0 + lane;
-        if (q < total) {
-          int mm = 0;
-#pragma unroll
-          for (int r = 1; r < AR_CM; ++r) mm += q >= off[r] ? 1 : 0;
-          int p0 = p0s[0], p1 = p1s[0], o = off[0];
-#pragma unroll
-          for (int r = 1; r < AR_CM; ++r)
-            if (mm == r) {
-              p0 = p0s[r];
-              p1 = p1s[r];
-              o = off[r];
-            }
-          const int i = p0 + (q - o);
-          const double* dh = DH + mm * H;
-          double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-          int k = 0;
-          for (; k + 4 <= H; k += 4) {
-            s0 = fma(W2s[k * N + i], dh[k], s0);
-            s1 = fma(W2s[(k + 1) * N + i], dh[k + 1], s1);
-            s2 = fma(W2s[(k + 2) * N + i], dh[k + 2], s2);
-            s3 = fma(W2s[(k + 3) * N + i], dh[k + 3], s3);
-          }
-          for (; k < H; ++k) s0 = fma(W2s[k * N + i], dh[k], s0);
-          const double lp = l[i] + ((s0 + s1) + (s2 + s3));
-          const double xi = (i == p0 || i == p1) ? 1.0 - x[i] : x[i];
-          buf[mm * N + i] = (xi * lp - ar_softplus(lp)) - t[i];
-        }
-      }
-      wave_sync();
-      // per-move sums: 16 lanes per move, fixed order
-      double acc = 0.0;
-      int p0g = p0s[0];
-#pragma unroll
-      for (int r = 1; r < AR_CM; ++r)
-        if (grp == r) p0g = p0s[r];
-      if (grp < cm)
-        for (int i = p0g + gl; i < N; i += 16) acc += buf[grp * N + i];
-      acc = row16_sum(acc);
-      const double r = grp < cm ? mel * exp(0.5 * acc) : 0.0;
-#pragma unroll
-      for (int mm = 0; mm < AR_CM; ++mm) e += lane_bcast(r, 16 * mm);
-      wave_sync();  // DH and buf are rewritten by the next chunk
-    }
-    if (lane == 0) {
-      const int n_anti = n_bonds - n_al;
-      const double diag = (kind == HAM_TFIM ? -J : J) * (double)(n_al - n_anti);
-      eloc[b] = make_double2(diag + e, 0.0);
-    }
-    wave_sync();  // per-wave arrays are rewritten by the next configuration
-  }
-}
-
 // O_k = (1/2) d log q / d theta_k for SB configurations per group:
 //   g_l[i] = s_i - sigmoid(l_i),  g_h[k] = [a_k > 0] sum_i (W2 * M2)[i, k] g_l[i],
 //   W1 (k, d): g_h[k] s_d,  b1 k: g_h[k],  W2 (i, k): g_l[i] relu(a_k),  b2 i: g_l[i].
@@ -418,75 +253,382 @@ __global__ __launch_bounds__(AR_NT) void k_ar_grad(const uint64_t* __restrict__ 
   }
 }
 
-// The same O_k with one wave per configuration and both masked weight matrices
-// in LDS (staged once per group, configurations taken grid-stride): the forward
-// pass, g_l and g_h with lanes over units, then the K outputs with lanes over the
-// live parameters (coalesced row writes).
-template <typename OutT>
-__global__ __launch_bounds__(AR_NT) void k_ar_grad_w(const uint64_t* __restrict__ s, int64_t B, int N, int H, int W,
-                                                     const double* __restrict__ W1mT,
-                                                     const double* __restrict__ W2t, const double* __restrict__ b1,
-                                                     const double* __restrict__ b2, const int2* __restrict__ idx,
-                                                     int64_t r1, int64_t r2, int64_t r3, int64_t K,
-                                                     OutT* __restrict__ O) {
+// ---- 16 configurations per work-group on the float64 matrix cores -----------
+// The network of a batch of 16 configurations is three small products on 16 x 16 x 4
+// operands (lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and, in register r,
+// D[l / 16 + 4 r][l % 16]):
+//   a[n][k] = b1 + sum_d x[n][d] W1[d][k],   l[n][i] = b2 + sum_k relu(a) W2[k][i],
+//   g_h[n][k] = sum_i g_l[n][i] W2[k][i].
+// Hidden units are stored by ascending degree, so the units that a flip of site p
+// changes (degree > p) and the units that output i reads (degree <= i) are ranges of
+// positions, and the reduction of a block runs over their intersection only.
+// Weights in LDS, zero past the network; the row lengths keep 16 rows apart in the
+// banks.
+struct ar_net {
+  int N, H, W;
+  int NT1, NT2;      // tiles of 16 hidden units / outputs
+  int Hs, Ns;        // row lengths of W1 [4 ceil(N / 4)][Hs] and W2 [16 NT1][Ns]
+  int pm;            // sites p < pm change some hidden unit
+  const double* pad; // W1 | W2 | b1 [Hs] | b2 [Ns]
+  const int* mst;    // [N + 1]: first position of degree >= v
+  __host__ __device__ int n4() const { return (N + 3) / 4 * 4; }
+  __host__ __device__ int w_doubles() const { return n4() * Hs + 16 * NT1 * Ns + Hs + Ns; }
+};
+
+constexpr int AB = 16;  // configurations per batch
+constexpr int AB_NT = 512, AB_WAVES = AB_NT / 64;
+
+struct ar_lds {
+  double *W1, *W2, *b1, *b2;
+  int* mst;       // [N + 1]
+  double *a;      // [AB][Hs] pre-activations
+  double *l;      // [AB][Ns] logits (or g_l)
+  double *x2;     // [AB][Ns] 1 + e^{-|l|} (local energies) or [AB][Hs] g_h (gradients)
+  uint64_t* bits; // [AB][W]
+};
+
+__host__ __device__ inline size_t ar_lds_doubles(const ar_net& d, int x2) {
+  return d.w_doubles() + (size_t)AB * (d.Hs + d.Ns + x2 + d.W) + (d.N + 2) / 2;
+}
+
+__device__ __forceinline__ ar_lds ar_lds_at(const ar_net& d, double* p, int x2) {
+  ar_lds L;
+  L.W1 = p;
+  L.W2 = L.W1 + d.n4() * d.Hs;
+  L.b1 = L.W2 + 16 * d.NT1 * d.Ns;
+  L.b2 = L.b1 + d.Hs;
+  L.mst = (int*)(L.b2 + d.Ns);
+  L.a = L.b2 + d.Ns + (d.N + 2) / 2;
+  L.l = L.a + AB * d.Hs;
+  L.x2 = L.l + AB * d.Ns;
+  L.bits = (uint64_t*)(L.x2 + AB * x2);
+  return L;
+}
+
+__device__ __forceinline__ void ar_load(const ar_net& d, const ar_lds& L) {
+  const int n = d.w_doubles();
+  for (int e = threadIdx.x; e < n; e += AB_NT) L.W1[e] = d.pad[e];
+  for (int e = threadIdx.x; e <= d.N; e += AB_NT) L.mst[e] = d.mst[e];
+}
+
+__device__ __forceinline__ doublex4 mfma64(double a, double b, doublex4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ double ar_bit(const ar_net& d, const ar_lds& L, int n, int i) {
+  return (double)((L.bits[n * d.W + (i >> 6)] >> (i & 63)) & 1ull);
+}
+
+// Bits and pre-activations of configurations b0 .. b0 + 15 (repeating the last past B)
+// into LDS, by the group (ends with a barrier) or, WAVE, by one wave with a batch of its own.
+template <bool WAVE>
+__device__ __forceinline__ void ar_hidden16(const ar_net& d, const ar_lds& L, const uint64_t* __restrict__ s,
+                                            int64_t b0, int64_t B) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  for (int e = WAVE ? lane : threadIdx.x; e < AB * d.W; e += WAVE ? 64 : AB_NT) {
+    const int n = e / d.W;
+    L.bits[e] = s[min(b0 + n, B - 1) * d.W + e - n * d.W];
+  }
+  if (WAVE)
+    wave_sync();
+  else
+    __syncthreads();
+  const uint64_t* row = L.bits + li * d.W;
+  for (int nt = WAVE ? 0 : wave; nt < d.NT1; nt += WAVE ? 1 : AB_WAVES) {
+    const double b = L.b1[16 * nt + li];
+    doublex4 acc = doublex4{b, b, b, b};
+    for (int k0 = 0; k0 < d.N; k0 += 4) {
+      const int i = k0 + lk;  // rows of W1 past N are 0
+      const double x = i < d.N ? (double)((row[i >> 6] >> (i & 63)) & 1ull) : 0.0;
+      acc = mfma64(x, L.W1[i * d.Hs + 16 * nt + li], acc);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) L.a[(lk + 4 * r) * d.Hs + 16 * nt + li] = acc[r];
+  }
+  if (WAVE)
+    wave_sync();
+  else
+    __syncthreads();
+}
+
+// Logits of the batch at outputs 16 nt + li: register r is configuration lk + 4 r.
+__device__ __forceinline__ doublex4 ar_logits16(const ar_net& d, const ar_lds& L, int nt, int li, int lk) {
+  const double b = L.b2[16 * nt + li];
+  doublex4 acc = doublex4{b, b, b, b};
+  const int ke = L.mst[min(d.N, 16 * nt + 16)];  // units of degree <= 16 nt + 15
+  for (int k0 = 0; k0 < ke; k0 += 4) {
+    const int k = k0 + lk;
+    acc = mfma64(fmax(L.a[li * d.Hs + k], 0.0), L.W2[k * d.Ns + 16 * nt + li], acc);
+  }
+  return acc;
+}
+
+// log psi, a batch per wave: the softplus sum as one logarithm of prod (1 + e^{-|l|}) per
+// configuration (the product of N <= 512 factors in [1, 2] stays in range).  Bound: the
+// latency of the products and of one exponential per logit.  3e5 configurations, N = 50,
+// H = 29: 0.81 -> 0.10 ms (0.21 ms with a batch per group).
+__global__ __launch_bounds__(AB_NT, 4) void k_ar_log_psi16(ar_net d, const uint64_t* __restrict__ s, int64_t B,
+                                                           double2* __restrict__ out) {
   extern __shared__ double lds[];
-  double* W1s = lds;          // [N][H]
-  double* W2s = W1s + N * H;  // [H][N]
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  double* x = W2s + H * N + wave * (2 * N + 2 * H);
-  double* gl = x + N;   // logits, then s_i - sigmoid(l_i)
-  double* hh = gl + N;  // ReLU(a), with a kept as the sign of the gate below
-  double* gh = hh + H;
-  for (int e = threadIdx.x; e < N * H; e += AR_NT) {
-    W1s[e] = W1mT[e];
-    W2s[e] = W2t[e];
-  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  ar_lds L = ar_lds_at(d, lds, 0);
+  ar_load(d, L);
   __syncthreads();
-  for (int64_t b = (int64_t)blockIdx.x * AR_WAVES + wave; b < B; b += (int64_t)gridDim.x * AR_WAVES) {
-    const uint64_t* srow = s + b * W;
-    for (int i = lane; i < N; i += 64) x[i] = (double)((srow[i >> 6] >> (i & 63)) & 1ull);
-    wave_sync();
-    for (int k = lane; k < H; k += 64) {
-      double acc = b1[k];
-      for (int d = 0; d < N; ++d) acc = fma(W1s[d * H + k], x[d], acc);
-      hh[k] = fmax(acc, 0.0);
-      gh[k] = acc > 0.0 ? 1.0 : 0.0;  // ReLU gate
+  L.bits = (uint64_t*)(lds + d.w_doubles() + (d.N + 2) / 2) + wave * AB * (d.W + d.Hs);  // after weights and mst
+  L.a = (double*)(L.bits + AB * d.W);
+  const int64_t step = (int64_t)gridDim.x * AB_WAVES * AB;
+  for (int64_t b0 = ((int64_t)blockIdx.x * AB_WAVES + wave) * AB; b0 < B; b0 += step) {
+    ar_hidden16<true>(d, L, s, b0, B);
+    double lin[4] = {0.0, 0.0, 0.0, 0.0}, q[4] = {1.0, 1.0, 1.0, 1.0};
+    for (int nt = 0; nt < d.NT2; ++nt) {
+      const doublex4 l = ar_logits16(d, L, nt, li, lk);
+      const int i = 16 * nt + li;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double x = ar_bit(d, L, lk + 4 * r, min(i, d.N - 1));
+        lin[r] += i < d.N ? x * l[r] - fmax(l[r], 0.0) : 0.0;
+        q[r] *= i < d.N ? 1.0 + m64::fexp_neg(l[r]) : 1.0;
+      }
     }
-    wave_sync();
-    for (int i = lane; i < N; i += 64) {
-      double acc = b2[i];
-      for (int k = 0; k < H; ++k) acc = fma(W2s[k * N + i], hh[k], acc);
-      gl[i] = x[i] - 1.0 / (1.0 + exp(-acc));
+    double a = 0.0, p = 1.0;  // lane li < 4: configuration lk + 4 li
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double ar = row16_sum(lin[r]), pr = row16_prod(q[r]);
+      if (li == r) {
+        a = ar;
+        p = pr;
+      }
     }
-    wave_sync();
-    for (int k = lane; k < H; k += 64) {
-      double acc = 0.0;
-      for (int i = ar_deg(k, N); i < N; ++i) acc = fma(W2s[k * N + i], gl[i], acc);
-      gh[k] *= acc;
-    }
-    wave_sync();
-    OutT* row = O + b * K;
-    for (int64_t j = lane; j < K; j += 64) {
-      const int2 pr = idx[j];
-      double v;
-      if (j < r1)
-        v = gh[pr.x] * x[pr.y];
-      else if (j < r2)
-        v = gh[pr.x];
-      else if (j < r3)
-        v = gl[pr.x] * hh[pr.y];
-      else
-        v = gl[pr.x];
-      v *= 0.5;
-      if constexpr (std::is_same<OutT, double2>::value)
-        row[j] = make_double2(v, 0.0);
-      else if constexpr (std::is_same<OutT, float2>::value)
-        row[j] = make_float2((float)v, 0.0f);
-      else
-        row[j] = (OutT)v;
-    }
-    wave_sync();
+    if (li < 4 && b0 + lk + 4 * li < B) out[b0 + lk + 4 * li] = make_double2(0.5 * (a - m64::flog(p)), 0.0);
+    wave_sync();  // the batch's LDS is rewritten by the next one
   }
+}
+
+// Local energies.  The forward pass as above; then a wave takes a configuration's connected
+// moves 16 at a time: the changes of the hidden units (rows: moves) times W2 give the new
+// logits as one product with the old logits as its start, over the units of degree > the
+// smallest site of the block, for the outputs from that site on.  Per entry one exponential:
+//   2 (log psi' - log psi) = sum_i [x' l' - max(l', 0) - x l + max(l, 0)] - log(prod q' / prod q),
+//   q = 1 + e^{-|l|}, with one logarithm per move.  Flips that change no unit (TFIM, p >= pm)
+// need no product and no q.
+// Bound: float64 vector work (the exponentials).  3e5 configurations, N = 50, H = 29, TFIM:
+// 7.09 -> 1.81 ms (one wave per configuration with (move, output) pairs over its lanes, both
+// weight operands of every multiply-add from LDS, exp and log1p per pair).
+__global__ __launch_bounds__(AB_NT, 4) void k_ar_eloc16(ar_net d, const uint64_t* __restrict__ s, int64_t B, int kind,
+                                                     double J, double hx, const int2* __restrict__ bonds, int n_bonds,
+                                                     double2* __restrict__ eloc) {
+  extern __shared__ double lds[];
+  const ar_lds L = ar_lds_at(d, lds, d.Ns);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  int* mv = (int*)(L.bits + AB * d.W) + wave * n_bonds;  // anti-aligned bonds (Heisenberg), bond order
+  const double mel = kind == HAM_TFIM ? -hx : 2.0 * J;
+  const bool offdiag = kind == HAM_TFIM ? hx != 0.0 : J != 0.0;
+  ar_load(d, L);
+  for (int64_t b0 = (int64_t)blockIdx.x * AB; b0 < B; b0 += (int64_t)gridDim.x * AB) {
+    __syncthreads();
+    ar_hidden16<false>(d, L, s, b0, B);
+    for (int nt = wave; nt < d.NT2; nt += AB_WAVES) {
+      const doublex4 l = ar_logits16(d, L, nt, li, lk);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        L.l[(lk + 4 * r) * d.Ns + 16 * nt + li] = l[r];
+        L.x2[(lk + 4 * r) * d.Ns + 16 * nt + li] = 1.0 + m64::fexp_neg(l[r]);
+      }
+    }
+    __syncthreads();
+    for (int n = wave; n < AB && b0 + n < B; n += AB_WAVES) {
+      const uint64_t* brow = L.bits + n * d.W;
+      const double *an = L.a + n * d.Hs, *ln = L.l + n * d.Ns, *qn = L.x2 + n * d.Ns;
+      int n_al = 0, M = 0;
+      for (int q0 = 0; q0 < n_bonds; q0 += 64) {
+        const int q = q0 + lane;
+        bool al = false, anti = false;
+        if (q < n_bonds) {
+          const int2 bd = bonds[q];
+          al = get_bit(brow, bd.x) == get_bit(brow, bd.y);
+          anti = !al;
+        }
+        n_al += __popcll(__ballot(al));
+        const unsigned long long am = __ballot(anti);
+        if (kind == HAM_HEIS && anti) mv[M + __popcll(am & ((1ull << lane) - 1ull))] = q;
+        M += __popcll(am);
+      }
+      if (kind == HAM_TFIM) M = d.pm;
+      if (!offdiag) M = 0;
+      wave_sync();
+      double e = 0.0;
+      if (offdiag && kind == HAM_TFIM)
+        for (int p = d.pm + lane; p < d.N; p += 64) e += m64::fexp(0.5 * (1.0 - 2.0 * get_bit(brow, p)) * ln[p]);
+      for (int m0 = 0; m0 < M; m0 += 16) {
+        // this lane's row of the block: move m0 + li
+        int p0 = d.N, p1 = -1;
+        if (m0 + li < M) {
+          p0 = m0 + li;
+          if (kind == HAM_HEIS) {
+            const int2 bd = bonds[mv[m0 + li]];
+            p0 = min(bd.x, bd.y);
+            p1 = max(bd.x, bd.y);
+          }
+        }
+        const bool ok = p0 < d.N;
+        const int pc0 = min(p0, d.N - 1), pc1 = max(p1, 0);
+        const double d0 = ok ? 1.0 - 2.0 * get_bit(brow, pc0) : 0.0, d1 = p1 >= 0 ? 1.0 - 2.0 * get_bit(brow, pc1) : 0.0;
+        int pmin = m0;
+        if (kind == HAM_HEIS) {
+          pmin = p0;
+          for (int o = 8; o > 0; o >>= 1) pmin = min(pmin, __shfl_xor(pmin, o, 64));
+          pmin = __builtin_amdgcn_readfirstlane(pmin);
+        }
+        int r0[4], r1[4];  // sites of the lane's accumulator rows
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          r0[r] = __shfl(p0, lk + 4 * r, 64);
+          r1[r] = kind == HAM_HEIS ? __shfl(p1, lk + 4 * r, 64) : -1;
+        }
+        double lin[4] = {0.0, 0.0, 0.0, 0.0}, num[4] = {1.0, 1.0, 1.0, 1.0}, den[4] = {1.0, 1.0, 1.0, 1.0};
+        const int ks = __builtin_amdgcn_readfirstlane(L.mst[pmin + 1]) & ~3;
+        for (int n0 = pmin >> 4; n0 < d.NT2; n0 += 4) {
+          const int ne = min(4, d.NT2 - n0);
+          const int ke = __builtin_amdgcn_readfirstlane(L.mst[min(d.N, 16 * (n0 + ne))]);
+          doublex4 acc[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const double l = j < ne ? ln[16 * (n0 + j) + li] : 0.0;
+            acc[j] = doublex4{l, l, l, l};
+          }
+          for (int k0 = ks; k0 < ke; k0 += 4) {
+            const int k = k0 + lk;
+            const double av = an[k];
+            double ap = fma(L.W1[pc0 * d.Hs + k], d0, av);
+            if (kind == HAM_HEIS) ap = fma(L.W1[pc1 * d.Hs + k], d1, ap);
+            const double dh = fmax(ap, 0.0) - fmax(av, 0.0);  // 0 for units of degree <= p0
+            const double* w2 = L.W2 + k * d.Ns + 16 * n0 + li;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (j < ne) acc[j] = mfma64(dh, w2[16 * j], acc[j]);
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if (j >= ne) break;
+            const int i = 16 * (n0 + j) + li, ic = min(i, d.N - 1);
+            const double x = (double)get_bit(brow, ic), l = ln[i], q = qn[i];
+            const double t = x * l - fmax(l, 0.0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const bool in = i >= r0[r] && i < d.N;
+              const double lp = acc[j][r], xp = (i == r0[r] || i == r1[r]) ? 1.0 - x : x;
+              lin[r] += in ? (xp * lp - fmax(lp, 0.0)) - t : 0.0;
+              if (ke > ks) {
+                num[r] *= in ? 1.0 + m64::fexp_neg(lp) : 1.0;
+                den[r] *= in ? q : 1.0;
+              }
+            }
+          }
+        }
+        double la = 0.0, ra = 1.0;  // lane li < 4: the sums of row lk + 4 li
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const double a = row16_sum(lin[r]), p = row16_prod(m64::fdiv(num[r], den[r]));
+          if (li == r) {
+            la = a;
+            ra = p;
+          }
+        }
+        if (li < 4 && m0 + lk + 4 * li < M) e += m64::fexp(0.5 * (la - m64::flog(ra)));
+      }
+      e = wave_sum_uniform(e);
+      if (lane == 0) {
+        const int n_anti = n_bonds - n_al;
+        const double diag = (kind == HAM_TFIM ? -J : J) * (double)(n_al - n_anti);
+        eloc[b0 + n] = make_double2(fma(mel, e, diag), 0.0);
+      }
+      wave_sync();  // mv is rewritten by the next configuration
+    }
+  }
+}
+
+// O_k of 16 configurations per batch: g_l and g_h as products, then the K outputs with
+// threads over the live parameters, each index pair used for the whole batch.
+// Bound: writing B K values.  3e5 configurations, N = 50, H = 29, float32: 0.80 -> 0.54 ms
+// (1.83 GB).
+template <typename OutT>
+__global__ __launch_bounds__(AB_NT, 4) void k_ar_grad16(ar_net d, const uint64_t* __restrict__ s, int64_t B,
+                                                     const int2* __restrict__ idx, int64_t r1, int64_t r2, int64_t r3,
+                                                     int64_t K, OutT* __restrict__ O) {
+  extern __shared__ double lds[];
+  const ar_lds L = ar_lds_at(d, lds, d.Hs);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  ar_load(d, L);
+  for (int64_t b0 = (int64_t)blockIdx.x * AB; b0 < B; b0 += (int64_t)gridDim.x * AB) {
+    __syncthreads();
+    ar_hidden16<false>(d, L, s, b0, B);
+    for (int nt = wave; nt < d.NT2; nt += AB_WAVES) {
+      const doublex4 l = ar_logits16(d, L, nt, li, lk);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double x = ar_bit(d, L, lk + 4 * r, min(16 * nt + li, d.N - 1));
+        L.l[(lk + 4 * r) * d.Ns + 16 * nt + li] = x - 1.0 / (1.0 + m64::fexp(-l[r]));
+      }
+    }
+    __syncthreads();
+    for (int nt = wave; nt < d.NT1; nt += AB_WAVES) {
+      doublex4 acc = doublex4{0.0, 0.0, 0.0, 0.0};
+      for (int i0 = 0; i0 < d.N; i0 += 4)  // outputs past N: W2 is 0
+        acc = mfma64(L.l[li * d.Ns + i0 + lk], L.W2[(16 * nt + li) * d.Ns + i0 + lk], acc);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int e = (lk + 4 * r) * d.Hs + 16 * nt + li;
+        L.x2[e] = L.a[e] > 0.0 ? 0.5 * acc[r] : 0.0;
+      }
+    }
+    __syncthreads();
+    const int nb = (int)min((int64_t)AB, B - b0);
+    for (int64_t j = threadIdx.x; j < K; j += AB_NT) {
+      const int2 pr = idx[j];
+      const int region = j < r1 ? 0 : j < r2 ? 1 : j < r3 ? 2 : 3;
+      OutT* o = O + b0 * K + j;
+      for (int n = 0; n < nb; ++n, o += K) {
+        double v;
+        if (region == 0)
+          v = get_bit(L.bits + n * d.W, pr.y) ? L.x2[n * d.Hs + pr.x] : 0.0;
+        else if (region == 1)
+          v = L.x2[n * d.Hs + pr.x];
+        else if (region == 2)
+          v = 0.5 * L.l[n * d.Ns + pr.x] * fmax(L.a[n * d.Hs + pr.y], 0.0);
+        else
+          v = 0.5 * L.l[n * d.Ns + pr.x];
+        if constexpr (std::is_same<OutT, double2>::value)
+          *o = make_double2(v, 0.0);
+        else if constexpr (std::is_same<OutT, float2>::value)
+          *o = make_float2((float)v, 0.0f);
+        else
+          *o = (OutT)v;
+      }
+    }
+  }
+}
+
+// the padded weights of ar_net, hidden units by position
+__global__ void k_ar_pad(ar_net d, const double* __restrict__ W1mT, const double* __restrict__ W2m,
+                         const double* __restrict__ b1, const double* __restrict__ b2, const int* __restrict__ perm,
+                         double* __restrict__ pad) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  const int n1 = d.n4() * d.Hs, n2 = n1 + 16 * d.NT1 * d.Ns;
+  if (e >= d.w_doubles()) return;
+  double v = 0.0;
+  if (e < n1) {
+    const int i = e / d.Hs, k = e - i * d.Hs;
+    if (i < d.N && k < d.H) v = W1mT[(int64_t)i * d.H + perm[k]];
+  } else if (e < n2) {
+    const int k = (e - n1) / d.Ns, i = (e - n1) - k * d.Ns;
+    if (i < d.N && k < d.H) v = W2m[(int64_t)i * d.H + perm[k]];
+  } else if (e < n2 + d.Hs) {
+    if (e - n2 < d.H) v = b1[perm[e - n2]];
+  } else if (e - n2 - d.Hs < d.N) {
+    v = b2[e - n2 - d.Hs];
+  }
+  pad[e] = v;
 }
 
 // compact live parameters -> dense masked layout [W1 (H x N) | b1 | W2 (N x H) | b2]
@@ -532,6 +674,41 @@ ar_ptrs ptrs(const vmc_model* m) {
 
 constexpr size_t kArLdsMax = 64 * 1024;
 
+// Rows of 16 NT1 + 4 and 32 m + 20 doubles: 16 rows read at once start 8 words (Hs) or
+// 40 words (Ns) apart in the 64 banks.
+ar_net net_of(const vmc_model* m) {
+  ar_net d;
+  d.N = m->N;
+  d.H = m->Nh;
+  d.W = m->W;
+  d.NT1 = (m->Nh + 15) / 16;
+  d.NT2 = (m->N + 15) / 16;
+  d.Hs = 16 * d.NT1 + 4;
+  d.Ns = (16 * d.NT2 + 11) / 32 * 32 + 20;
+  d.pm = std::min(m->Nh, m->N - 1);
+  d.pad = m->ar_pad;
+  d.mst = m->ar_perm + m->Nh;
+  return d;
+}
+
+// LDS bytes of the 16-configuration kernels, or 0 where they do not apply: the product of N
+// factors in [1, 2] has to stay in range, and the padded weights have to fit beside a batch.
+constexpr size_t kArBatchLds = 158 * 1024;
+size_t batch_lds(const ar_net& d, int x2, size_t extra = 0) {
+  const size_t b = sizeof(double) * ar_lds_doubles(d, x2) + extra;
+  return d.N <= 512 && b <= kArBatchLds ? b : 0;
+}
+
+unsigned batch_groups(vmc_ctx* ctx, int64_t B, size_t lds) {
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)(160 * 1024) / (int64_t)lds));
+  return (unsigned)std::min<int64_t>((B + AB - 1) / AB, cu_count(ctx) * per_cu);
+}
+
+template <typename Kern>
+void batch_allow(Kern k, size_t lds) {
+  if (lds > 64 * 1024) VMC_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+}
+
 void* ar_alloc(size_t bytes) {
   void* p = nullptr;
   if (hipMalloc(&p, bytes) != hipSuccess) {
@@ -565,6 +742,18 @@ void ar_init(vmc_model* m) {
   m->made = md;
   m->ar_idx = (int2*)ar_alloc(sizeof(int2) * idx.size());
   m->ar_w2t = (double*)ar_alloc(sizeof(double) * (size_t)N * H);
+  // hidden units by degree: position -> unit, first position per degree, index pairs by position
+  std::vector<int> perm, mst, at(H);
+  mix_made_layout(N, H, perm, mst);
+  for (int q = 0; q < H; ++q) at[perm[q]] = q;
+  std::vector<int2> idxp = idx;
+  for (int64_t j = 0; j < m->ar_r3; ++j) (j < m->ar_r2 ? idxp[j].x : idxp[j].y) = at[j < m->ar_r2 ? idx[j].x : idx[j].y];
+  perm.insert(perm.end(), mst.begin(), mst.end());
+  m->ar_idxp = (int2*)ar_alloc(sizeof(int2) * idxp.size());
+  m->ar_perm = (int*)ar_alloc(sizeof(int) * perm.size());
+  m->ar_pad = (double*)ar_alloc(sizeof(double) * net_of(m).w_doubles());
+  VMC_HIP(hipMemcpyAsync(m->ar_idxp, idxp.data(), sizeof(int2) * idxp.size(), hipMemcpyHostToDevice, ctx->stream));
+  VMC_HIP(hipMemcpyAsync(m->ar_perm, perm.data(), sizeof(int) * perm.size(), hipMemcpyHostToDevice, ctx->stream));
   VMC_HIP(hipMemcpyAsync(m->ar_idx, idx.data(), sizeof(int2) * idx.size(), hipMemcpyHostToDevice, ctx->stream));
   VMC_HIP(hipStreamSynchronize(ctx->stream));
   ar_set_params(m);
@@ -573,6 +762,12 @@ void ar_init(vmc_model* m) {
 void ar_free(vmc_model* m) {
   if (m->ar_idx) (void)hipFree(m->ar_idx);
   if (m->ar_w2t) (void)hipFree(m->ar_w2t);
+  if (m->ar_idxp) (void)hipFree(m->ar_idxp);
+  if (m->ar_perm) (void)hipFree(m->ar_perm);
+  if (m->ar_pad) (void)hipFree(m->ar_pad);
+  m->ar_idxp = nullptr;
+  m->ar_perm = nullptr;
+  m->ar_pad = nullptr;
   if (m->made) (void)vmc_made_destroy(m->made);
   m->ar_idx = nullptr;
   m->ar_w2t = nullptr;
@@ -589,10 +784,21 @@ void ar_set_params(vmc_model* m) {
   made_refresh(md);
   const int64_t n = (int64_t)m->N * m->Nh;
   k_ar_transpose<<<grid_for(n, 256), 256, 0, st>>>(md->W2m, m->N, m->Nh, m->ar_w2t);
+  const ar_net d = net_of(m);
+  const ar_ptrs p = ptrs(m);
+  k_ar_pad<<<grid_for(d.w_doubles(), 256), 256, 0, st>>>(d, p.W1mT, p.W2m, p.b1, p.b2, m->ar_perm, m->ar_pad);
   VMC_HIP(hipGetLastError());
 }
 
 void ar_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* out) {
+  const ar_net d = net_of(m);
+  const size_t lw = sizeof(double) * (d.w_doubles() + (d.N + 2) / 2 + (size_t)AB_WAVES * AB * (d.W + d.Hs));
+  if (d.N <= 512 && lw <= kArBatchLds) {
+    batch_allow(k_ar_log_psi16, lw);
+    k_ar_log_psi16<<<batch_groups(m->ctx, (B + AB_WAVES - 1) / AB_WAVES, lw), AB_NT, lw, m->ctx->stream>>>(d, s, B, out);
+    VMC_HIP(hipGetLastError());
+    return;
+  }
   const ar_ptrs p = ptrs(m);
   const size_t lds = sizeof(double) * (2 * (size_t)m->N + 2 * (size_t)m->Nh);
   for (int64_t b0 = 0; b0 < B; b0 += INT32_MAX) {
@@ -605,22 +811,13 @@ void ar_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* out) {
 
 void ar_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, double2* eloc) {
   const ar_ptrs p = ptrs(m);
-  const size_t per_wave = (size_t)(3 + AR_CM) * m->N + (size_t)(2 + AR_CM) * m->Nh + ((size_t)H->n_bonds + 1) / 2;
-  auto lds_of = [&](int waves) { return sizeof(double) * (2 * (size_t)m->N * m->Nh + (size_t)waves * per_wave); };
-  // eight waves per group share one copy of the weights where it fits (more
-  // resident waves per compute unit for the same LDS), else four
-  const int nt = lds_of(8) <= kArLdsMax ? 512 : 256;
-  const size_t lds_w = lds_of(nt / 64);
-  if (lds_w <= kArLdsMax) {
-    // one resident wave of groups: as many as the LDS of 256 compute units holds (at most 8 each)
-    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)(160 * 1024) / (int64_t)lds_w));
-    const int64_t groups = std::min<int64_t>((B + nt / 64 - 1) / (nt / 64), 256 * per_cu);
-    if (nt == 512)
-      k_ar_eloc_tri<512><<<(unsigned)groups, 512, lds_w, m->ctx->stream>>>(
-          s, B, m->N, m->Nh, m->W, p.W1mT, m->ar_w2t, p.b1, p.b2, H->kind, H->J, H->h, H->bonds, H->n_bonds, eloc);
-    else
-      k_ar_eloc_tri<256><<<(unsigned)groups, 256, lds_w, m->ctx->stream>>>(
-          s, B, m->N, m->Nh, m->W, p.W1mT, m->ar_w2t, p.b1, p.b2, H->kind, H->J, H->h, H->bonds, H->n_bonds, eloc);
+  const ar_net d = net_of(m);
+  // the Heisenberg move lists of the waves follow the batch
+  const size_t extra = sizeof(int) * (H->kind == HAM_HEIS ? (size_t)AB_WAVES * H->n_bonds : 0);
+  if (const size_t lb = batch_lds(d, d.Ns, extra)) {
+    batch_allow(k_ar_eloc16, lb);
+    k_ar_eloc16<<<batch_groups(m->ctx, B, lb), AB_NT, lb, m->ctx->stream>>>(d, s, B, H->kind, H->J, H->h, H->bonds,
+                                                                           H->n_bonds, eloc);
     VMC_HIP(hipGetLastError());
     return;
   }
@@ -650,24 +847,23 @@ void ar_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, dou
 
 void ar_grad(vmc_model* m, const uint64_t* s, int64_t B, void* O, int dtype) {
   const ar_ptrs p = ptrs(m);
-  const size_t lds_w = sizeof(double) * (2 * (size_t)m->N * m->Nh + (size_t)AR_WAVES * (2 * (size_t)m->N + 2 * m->Nh));
-  if (lds_w <= kArLdsMax) {
-    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)(160 * 1024) / (int64_t)lds_w));
-    const unsigned g = (unsigned)std::min<int64_t>((B + AR_WAVES - 1) / AR_WAVES, 256 * per_cu);
-    hipStream_t st = m->ctx->stream;
-#define AR_GRAD_W(T)                                                                                           \
-  k_ar_grad_w<T><<<g, AR_NT, lds_w, st>>>(s, B, m->N, m->Nh, m->W, p.W1mT, m->ar_w2t, p.b1, p.b2, m->ar_idx, \
-                                          m->ar_r1, m->ar_r2, m->ar_r3, m->K, (T*)O)
+  const ar_net d = net_of(m);
+  if (const size_t lb = batch_lds(d, d.Hs)) {
+    auto run = [&](auto* o) {
+      using T = std::remove_pointer_t<decltype(o)>;
+      batch_allow(k_ar_grad16<T>, lb);
+      k_ar_grad16<T><<<batch_groups(m->ctx, B, lb), AB_NT, lb, m->ctx->stream>>>(d, s, B, m->ar_idxp, m->ar_r1, m->ar_r2,
+                                                                                 m->ar_r3, m->K, o);
+      VMC_HIP(hipGetLastError());
+    };
     if (dtype == VMC_DT_C128)
-      AR_GRAD_W(double2);
+      run((double2*)O);
     else if (dtype == VMC_DT_C64)
-      AR_GRAD_W(float2);
+      run((float2*)O);
     else if (dtype == VMC_DT_F64)
-      AR_GRAD_W(double);
+      run((double*)O);
     else
-      AR_GRAD_W(float);
-#undef AR_GRAD_W
-    VMC_HIP(hipGetLastError());
+      run((float*)O);
     return;
   }
   const size_t per = sizeof(double) * (2 * (size_t)m->N + 3 * (size_t)m->Nh);

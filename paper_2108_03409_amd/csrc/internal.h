@@ -180,6 +180,9 @@ struct vmc_model {
   vmc_made* made = nullptr;
   int2* ar_idx = nullptr;
   double* ar_w2t = nullptr;
+  int2* ar_idxp = nullptr;    // index pairs with hidden units by ascending degree
+  int* ar_perm = nullptr;     // [N_h] units by ascending degree, then [N + 1] first position per degree
+  double* ar_pad = nullptr;   // padded weights of the 16-configuration kernels (arnqs.hip)
   int64_t ar_r1 = 0, ar_r2 = 0, ar_r3 = 0;  // ends of the W1, b1 and W2 blocks of the compact vector
 };
 
@@ -270,7 +273,7 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
   }
 }
 __device__ __forceinline__ double2 cexp(double2 z) {
-  double e = exp(z.x), s, c;
+  double e = m64::fexp(z.x), s, c;
   m64::fsincos(z.y, &s, &c);
   return make_double2(e * c, e * s);
 }
@@ -283,7 +286,7 @@ __device__ __forceinline__ double2 clog(double2 z) {
 template <bool LIB = true>
 __device__ __forceinline__ double2 clogcosh(double2 z) {
   if (z.x < 0.0) z = make_double2(-z.x, -z.y);
-  double e = exp(-2.0 * z.x), s, c;
+  double e = m64::fexp_neg(2.0 * z.x), s, c;
   m64::fsincos<LIB>(-2.0 * z.y, &s, &c);
   double er = e * c, ei = e * s;  // e^{-2 z~}
   // log|1 + w| = 0.5 log1p(2 Re w + |w|^2)
@@ -307,7 +310,7 @@ template <bool LIB = true>
 __device__ __forceinline__ double2 ctanh(double2 z) {
   bool neg = z.x < 0.0;
   if (neg) z = make_double2(-z.x, -z.y);
-  double e = exp(-2.0 * z.x), s, c;
+  double e = m64::fexp(-2.0 * z.x), s, c;
   m64::fsincos<LIB>(-2.0 * z.y, &s, &c);
   double2 w = make_double2(e * c, e * s);
   double2 r = cdiv(make_double2(1.0 - w.x, -w.y), make_double2(1.0 + w.x, w.y));
@@ -425,6 +428,13 @@ __device__ __forceinline__ double row16_sum(double v) {
   v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]: lane ^ 2
   v += dpp_f64<0x141>(v);  // row_half_mirror: the two quads of each half row
   v += dpp_f64<0x140>(v);  // row_mirror: the two halves of the row
+  return v;
+}
+__device__ __forceinline__ double row16_prod(double v) {
+  v *= dpp_f64<0xB1>(v);
+  v *= dpp_f64<0x4E>(v);
+  v *= dpp_f64<0x141>(v);
+  v *= dpp_f64<0x140>(v);
   return v;
 }
 // Sum over the wavefront, returned wave-uniform to every lane.
