@@ -146,21 +146,24 @@ __global__ __launch_bounds__(64) void k_tables(const double2* __restrict__ param
 // move) the product prod_j (1 - sigma t_j T_jm) is kept with exact
 // power-of-two rescaling, and
 //   E_loc = diag + mel * sum_m exp(-2 sigma_m alpha_m + LC_m + log prod).
+// Bound: float64 vector work, ten instructions per (unit, move).  The padded table and
+// operands need no bounds, and its rows are addressed from scalar registers: N = 64,
+// N_h = 256, 16 384 samples with theta 237 -> 204 us.
 template <int S>
 __global__ __launch_bounds__(64) void k_eloc(const double2* __restrict__ theta, const uint64_t* __restrict__ s,
                                              int64_t B, int N, int W, int Nh, int ham_kind, double J, double h,
                                              const int2* __restrict__ bonds, int n_bonds,
                                              const double2* __restrict__ T, const double2* __restrict__ LC,
-                                             const double2* __restrict__ alpha, int n_moves,
+                                             const double2* __restrict__ alpha, int n_moves, int Nhp,
                                              double2* __restrict__ eloc) {
-  extern __shared__ double2 tl[];  // [S][Nh]
+  extern __shared__ double2 tl[];  // [S][Nhp], 0 past N_h
   const int64_t b0 = (int64_t)blockIdx.x * S;
   if (b0 >= B) return;
   const int lane = threadIdx.x;
-  for (int e = lane; e < S * Nh; e += 64) {
-    const int q = e / Nh, j = e - q * Nh;
-    tl[e] = b0 + q < B ? ctanh(theta[(b0 + q) * Nh + j]) : make_double2(0.0, 0.0);
-  }
+#pragma unroll
+  for (int q = 0; q < S; ++q)
+    for (int j = lane; j < Nhp; j += 64)
+      tl[q * Nhp + j] = b0 + q < B && j < Nh ? ctanh(theta[(b0 + q) * Nh + j]) : make_double2(0.0, 0.0);
   // diagonal element: coupling * (n_aligned - n_anti), exact integer count
   double diag[S];
 #pragma unroll
@@ -204,35 +207,30 @@ __global__ __launch_bounds__(64) void k_eloc(const double2* __restrict__ theta, 
         P[q] = make_double2(1.0, 0.0);
         e2[q] = 0;
       }
-      const double2* Tm = T + m;
-      for (int j0 = 0; j0 < Nh; j0 += 32) {
-        const int j1 = min(Nh, j0 + 32);
-        for (int jb = j0; jb < j1; jb += 8) {
+      for (int j0 = 0; j0 < Nhp; j0 += 16) {  // T and tl are 0 past N_h
+#pragma unroll
+        for (int jb = j0; jb < j0 + 16; jb += 8) {
           // eight table loads in flight before the products that use them
+          const double2* Tj = T + jb * n_moves;  // the same row for every lane
           double2 Tv[8];
 #pragma unroll
-          for (int u = 0; u < 8; ++u)
-            Tv[u] = jb + u < j1 ? Tm[(int64_t)(jb + u) * n_moves] : make_double2(0.0, 0.0);
+          for (int u = 0; u < 8; ++u) Tv[u] = Tj[u * n_moves + m];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            if (jb + u >= j1) break;
-            const int j = jb + u;
+          for (int u = 0; u < 8; ++u)
 #pragma unroll
             for (int q = 0; q < S; ++q) {
-              const double2 tt = cmul(tl[q * Nh + j], Tv[u]);
-              P[q] = cmul(P[q], make_double2(1.0 - sg[q] * tt.x, -sg[q] * tt.y));
+              const double2 tt = cmul(tl[q * Nhp + jb + u], Tv[u]);
+              P[q] = cmul(P[q], make_double2(fma(-sg[q], tt.x, 1.0), -sg[q] * tt.y));
             }
-          }
         }
         // keep |P| near 1: exact power-of-two rescaling
+        if (j0 & 16)
 #pragma unroll
-        for (int q = 0; q < S; ++q) {
-          int e;
-          frexp(fmax(fabs(P[q].x), fabs(P[q].y)), &e);
-          P[q].x = ldexp(P[q].x, -e);
-          P[q].y = ldexp(P[q].y, -e);
-          e2[q] += e;
-        }
+          for (int q = 0; q < S; ++q) {
+            const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(P[q].x), fabs(P[q].y)));
+            P[q] = make_double2(ldexp(P[q].x, -e), ldexp(P[q].y, -e));
+            e2[q] += e;
+          }
       }
       const double2 al = alpha[m], lcm = LC[m];
 #pragma unroll
@@ -517,11 +515,15 @@ void rbm_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, do
   const int64_t chunk = std::min<int64_t>(B, kChunk);
   ws_reserve(ctx, ws_round(sizeof(double2) * chunk * m->Nh));
   double2* theta = (double2*)ws_take(ctx, sizeof(double2) * chunk * m->Nh);
-  // flips: 4 samples per wavefront share the table reads; exchanges: one
-  // sample per wavefront over its compacted list of anti-aligned bonds
-  const int S = m->Nh <= 1024 ? 4 : 2;
-  const size_t lds = sizeof(double2) * (size_t)S * m->Nh;
+  // flips: 4 samples per wavefront share the table reads where that leaves two waves per
+  // SIMD (B >= 8 192) of which four fit the LDS (N_h <= 256) and fill their lanes (more
+  // than 32 moves): N = 64, N_h = 256: 204 against 220 us for 16 384 samples with one
+  // each; otherwise one sample: N = 400, N_h = 800, 4 096 samples 1.08 against 2.15 ms,
+  // N = 10, N_h = 10, 1 024 samples 12 against 20 us.  Exchanges: one sample per wavefront
+  // over its compacted list of anti-aligned bonds.
+  const int S = nh_pad16(m->Nh) <= 256 && tb.n_moves > 32 && B >= 8192 ? 4 : 1;
   const int Nhp = nh_pad16(m->Nh);
+  const size_t lds = sizeof(double2) * (size_t)S * Nhp;
   const size_t lds1 = sizeof(double2) * 2 * Nhp + sizeof(int) * std::max(1, tb.n_moves);
   VMC_REQUIRE((move_kind == 1 ? lds1 : lds) <= 64 * 1024, "model too large for the local-energy kernel's LDS budget");
   VMC_REQUIRE((int64_t)Nhp * std::max(1, tb.n_moves) < ((int64_t)1 << 31), "move table too large");
@@ -538,11 +540,11 @@ void rbm_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, do
     const unsigned grid = (unsigned)((nb + S - 1) / S);
 #define ELOC_LAUNCH(SS)                                                                                             \
   k_eloc<SS><<<grid, 64, lds, ctx->stream>>>(theta, s + b0 * m->W, nb, m->N, m->W, m->Nh, H->kind, H->J, H->h,     \
-                                             H->bonds, H->n_bonds, tb.T, tb.LC, tb.alpha, tb.n_moves, eloc + b0)
+                                             H->bonds, H->n_bonds, tb.T, tb.LC, tb.alpha, tb.n_moves, Nhp, eloc + b0)
     if (S == 4)
       ELOC_LAUNCH(4);
     else
-      ELOC_LAUNCH(2);
+      ELOC_LAUNCH(1);
 #undef ELOC_LAUNCH
     VMC_HIP(hipGetLastError());
   }
