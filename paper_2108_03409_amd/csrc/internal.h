@@ -535,6 +535,11 @@ void dgemm(vmc_ctx* ctx, const dgemm_args& g, int nsplit = 1);
 size_t herk_ws_bytes(int64_t N, int64_t K, int mode);
 void herk_mfma_f32(vmc_ctx* ctx, const float2* X, int64_t N, int64_t K, int mode, double nu, double eps, double2* S,
                    double2* diag, void* ws);
+// herk64.hip
+int herk64_splits(int64_t N, int64_t K, int mode, size_t room);
+size_t herk64_ws_bytes(int64_t K, int mode, int nsplit);
+void herk_f64(vmc_ctx* ctx, const double2* X, int64_t N, int64_t K, int mode, double nu, double eps, double2* S,
+              double2* diag, void* ws, int nsplit);
 // chol.hip
 size_t chol_linv_bytes(int64_t K);
 int chol_block();

@@ -198,55 +198,6 @@ __global__ __launch_bounds__(256) void k_center_force_pair(const InT* __restrict
 }
 
 
-// S[r][c] = sum_n conj(Xc[n][r]) Xc[n][c] for the 32x32 tile (r >= c block-wise),
-// written to both triangles; projection and shift applied here.
-template <typename XT>
-__global__ __launch_bounds__(256) void k_herk_simple(const XT* __restrict__ X, int64_t N, int64_t K, int mode,
-                                                     double nu, double eps, double2* __restrict__ S,
-                                                     double2* __restrict__ diag) {
-  const int tr = blockIdx.y, tc = blockIdx.x;
-  if (tc > tr) return;
-  __shared__ double2 xa[16][33], xb[16][33];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int64_t r0 = (int64_t)tr * 32, c0 = (int64_t)tc * 32;
-  double2 acc[2][2] = {};
-  for (int64_t n0 = 0; n0 < N; n0 += 16) {
-    for (int e = threadIdx.x; e < 16 * 32; e += 256) {
-      const int nn = e >> 5, cc = e & 31;
-      const int64_t n = n0 + nn;
-      xa[nn][cc] = (n < N && r0 + cc < K) ? load_c(X, n * K + r0 + cc) : make_double2(0.0, 0.0);
-      xb[nn][cc] = (n < N && c0 + cc < K) ? load_c(X, n * K + c0 + cc) : make_double2(0.0, 0.0);
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int nn = 0; nn < 16; ++nn) {
-      const double2 a0 = cconj(xa[nn][ty]), a1 = cconj(xa[nn][ty + 16]);
-      const double2 b0 = xb[nn][tx], b1 = xb[nn][tx + 16];
-      acc[0][0] = cadd(acc[0][0], cmul(a0, b0));
-      acc[0][1] = cadd(acc[0][1], cmul(a0, b1));
-      acc[1][0] = cadd(acc[1][0], cmul(a1, b0));
-      acc[1][1] = cadd(acc[1][1], cmul(a1, b1));
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int64_t r = r0 + ty + 16 * i, c = c0 + tx + 16 * j;
-      if (r >= K || c >= K || c > r) continue;
-      double2 v = acc[i][j];
-      if (mode == VMC_SR_REAL) v.y = 0.0;
-      if (mode == VMC_SR_IMAG) v.x = 0.0;  // i Im S
-      if (r == c) {
-        v = make_double2(v.x * (1.0 + nu) + eps, 0.0);
-        diag[r] = v;
-      }
-      S[r * K + c] = v;
-      if (r != c) S[c * K + r] = cconj(v);
-    }
-}
-
 // rhs = -[[gamma F]]; for the Im projection the system Im[S~] x = -Im[gamma F]
 // is held as (i Im S~) x = -i Im[gamma F], so rhs = (0, -Im[gamma F])
 __global__ void k_rhs(const double2* __restrict__ F, int64_t K, double gr, double gi, int mode, double2* __restrict__ rhs) {
@@ -733,7 +684,15 @@ void sr_solve_impl(vmc_ctx* ctx, const void* O, int dtype, const double2* eloc, 
                  ws_round(chol_linv_bytes(K)) +
                  ws_round(xsz) + ws_round(sizeof(double2) * (size_t)K * K) + ws_round(sizeof(double) * nblk) +
                  ws_round(sizeof(long long)) + ws_round(sizeof(double) * 4) + ws_round(chol_sync_bytes(K));
+  // float64 Gram: partial tiles of split sample ranges, from what the workspace limit leaves
+  const size_t room = ctx->ws_limit ? (ctx->ws_limit > total + 512 ? ctx->ws_limit - total - 512 : 0) : SIZE_MAX;
+  const int fmode = o->mode == VMC_SR_REAL ? VMC_SR_REAL : VMC_SR_COMPLEX;
+  const int sp64 = f32 ? 1 : herk64_splits(Nx, K, hmode, room);
+  const int sp64y = f32 || !use_snr ? 1 : herk64_splits(N, K, fmode, room);
+  const size_t h64 = std::max(herk64_ws_bytes(K, hmode, sp64), herk64_ws_bytes(K, fmode, sp64y));
+  total += ws_round(h64);
   ws_reserve(ctx, total);
+  void* h64_ws = h64 ? ws_take(ctx, h64) : nullptr;
   double* stats = (double*)ws_take(ctx, 64);
   double2* partial = (double2*)ws_take(ctx, sizeof(double2) * npart * K);
   double2* mean = (double2*)ws_take(ctx, sizeof(double2) * K);
@@ -792,14 +751,12 @@ void sr_solve_impl(vmc_ctx* ctx, const void* O, int dtype, const double2* eloc, 
   ph.reset();
 
   ph.reset(new phase_scope(ctx, "sr.herk"));
-  const unsigned nb32 = (unsigned)((K + 31) / 32);
-  dim3 hg(nb32, nb32);
   if (split16)
     herk_split16(ctx, (const float2*)Xc, Nx, K, hmode, o->nu_rel, o->eps_abs, S, diag, h16ws);
   else if (f32)
     herk_mfma_f32(ctx, (const float2*)Xc, Nx, K, hmode, o->nu_rel, o->eps_abs, S, diag, hws_p);
   else
-    k_herk_simple<double2><<<hg, 256, 0, st>>>((const double2*)Xc, Nx, K, hmode, o->nu_rel, o->eps_abs, S, diag);
+    herk_f64(ctx, (const double2*)Xc, Nx, K, hmode, o->nu_rel, o->eps_abs, S, diag, h64_ws, sp64);
   VMC_HIP(hipGetLastError());
   ph.reset();
 
@@ -823,7 +780,6 @@ void sr_solve_impl(vmc_ctx* ctx, const void* O, int dtype, const double2* eloc, 
     // second moment of the per-sample force terms (SNR): H = Y^H Y
     if (use_snr) {
       ph.reset(new phase_scope(ctx, "sr.snr"));
-      const int fmode = o->mode == VMC_SR_REAL ? VMC_SR_REAL : VMC_SR_COMPLEX;
       if (dtype == VMC_DT_C64)
         k_force_terms<float2, float2><<<cg, 256, 0, st>>>((const float2*)O, w, eloc, N, K, mean, stats, o->gamma_re,
                                                            o->gamma_im, o->mode, (float2*)Ysnr);
@@ -840,7 +796,7 @@ void sr_solve_impl(vmc_ctx* ctx, const void* O, int dtype, const double2* eloc, 
       if (f32)
         herk_mfma_f32(ctx, (const float2*)Ysnr, N, K, fmode, 0.0, 0.0, Hm, rho, hws_p);
       else
-        k_herk_simple<double2><<<hg, 256, 0, st>>>((const double2*)Ysnr, N, K, fmode, 0.0, 0.0, Hm, rho);
+        herk_f64(ctx, (const double2*)Ysnr, N, K, fmode, 0.0, 0.0, Hm, rho, h64_ws, sp64y);
       VMC_HIP(hipGetLastError());
       ph.reset();
     }
