@@ -14,8 +14,8 @@
 //
 // Inner cyclic Jacobi on M (2 BJ indices, each round pairs every index once):
 // for a pair (p, q) with M_pp = a, M_qq = b, M_pq = |z| e^{i phi}, the unitary
-//     J = [[c, s], [-s e, c e]],  e = e^{-i phi},  t = s / c the smaller root of
-//     t^2 + 2 tau t - 1 = 0,  tau = (b - a) / (2 |z|),
+//     J = [[c, conj(s)], [-s, c]],  s = |s| e^{-i phi} times a sign,  |s| / c the smaller
+//     root t of t^2 + 2 tau t - 1 = 0,  tau = |b - a| / (2 |z|),
 // zeroes M_pq (M <- J^H M J on rows and columns p, q; U <- U J).
 #include <hip/hip_runtime.h>
 
@@ -30,18 +30,11 @@ namespace {
 
 constexpr int BJ = 16;       // index block of the outer Jacobi
 constexpr int BM = 2 * BJ;   // a pair's submatrix
+constexpr int BLD = BM + 1;  // its row length in LDS
 constexpr int MAX_INNER = 1; // inner sweeps per submatrix and round (one measured fastest)
 // a pair's submatrix is reduced below INNER_TOL x the outer tolerance, so that what the
 // pairs leave on their own off-diagonals stays below the outer criterion
 constexpr double INNER_TOL = 0.125;
-
-struct jrot {
-  int p, q;
-  double c, s;
-  double2 e;
-  double a_new, b_new;  // diagonal after the rotation
-  int active;
-};
 
 // circle ordering of n indices (n even), round r: pair i
 __device__ __forceinline__ void circle_pair(int n, int r, int i, int& p, int& q) {
@@ -55,34 +48,65 @@ __device__ __forceinline__ void circle_pair(int n, int r, int i, int& p, int& q)
   }
 }
 
-// rotation of pair i of inner round r on the BM x BM matrix M (row-major in LDS)
-__device__ __forceinline__ jrot make_rot(const double2* M, int i, int r) {
-  int p, q;
-  circle_pair(BM, r, i, p, q);
-  const double a = M[p * BM + p].x, b = M[q * BM + q].x;
-  const double2 z = M[p * BM + q];
-  const double az = hypot(z.x, z.y);
-  jrot R;
-  R.p = p;
-  R.q = q;
+// Arithmetic on entries of a real (double) or complex (double2) matrix.
+__device__ __forceinline__ double zero_of(double) { return 0.0; }
+__device__ __forceinline__ double2 zero_of(double2) { return make_double2(0.0, 0.0); }
+__device__ __forceinline__ double real_of(double v) { return v; }
+__device__ __forceinline__ double real_of(double2 v) { return v.x; }
+__device__ __forceinline__ double norm2(double v) { return v * v; }
+__device__ __forceinline__ double norm2(double2 v) { return fma(v.x, v.x, v.y * v.y); }
+__device__ __forceinline__ double conj_of(double v) { return v; }
+__device__ __forceinline__ double2 conj_of(double2 v) { return cconj(v); }
+__device__ __forceinline__ double scaled(double v, double s) { return v * s; }
+__device__ __forceinline__ double2 scaled(double2 v, double s) { return cscale(v, s); }
+__device__ __forceinline__ double of_real(double, double x) { return x; }
+__device__ __forceinline__ double2 of_real(double2, double x) { return make_double2(x, 0.0); }
+// acc + a b
+__device__ __forceinline__ double fmac(double acc, double a, double b) { return fma(a, b, acc); }
+__device__ __forceinline__ double2 fmac(double2 acc, double2 a, double2 b) {
+  return make_double2(fma(-a.y, b.y, fma(a.x, b.x, acc.x)), fma(a.y, b.x, fma(a.x, b.y, acc.y)));
+}
+// c a + s b, c real
+__device__ __forceinline__ double mix(double c, double a, double s, double b) { return fma(c, a, s * b); }
+__device__ __forceinline__ double2 mix(double c, double2 a, double2 s, double2 b) {
+  const double2 t = cmul(s, b);
+  return make_double2(fma(c, a.x, t.x), fma(c, a.y, t.y));
+}
+
+// 1 / sqrt(x) of a normal x: the hardware estimate and two Newton steps
+__device__ __forceinline__ double rsqrt_nr(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  const double h = 0.5 * x;
+  y = y * fma(-h * y, y, 1.5);
+  return y * fma(-h * y, y, 1.5);
+}
+
+template <typename T>
+struct jrot {
+  double c;
+  T s;                   // J = [[c, conj(s)], [-s, c]] on the index pair (p, q)
+  double a_new, b_new;   // diagonal after the rotation
+  bool active;
+};
+
+// Rotation that zeroes z = M_pq between a = M_pp and b = M_qq: with d = (b - a) / 2,
+// r = sqrt(d^2 + |z|^2): c^2 = (1 + |d| / r) / 2, s = sgn(d) conj(z) / (2 r c) (the smaller
+// of the two angles), and a, b move by -+ sgn(d) |z|^2 / (|d| + r).  Two reciprocal square
+// roots are its whole dependent chain.
+template <typename T>
+__device__ __forceinline__ jrot<T> make_rot(double a, double b, T z) {
+  const double h2 = norm2(z), d = 0.5 * (b - a), r2 = fma(d, d, h2);
+  jrot<T> R;
   // negligible coupling: no rotation (also for the decoupled padding indices)
-  if (!(az > 0.0) || az <= 1e-300 || az < 1e-17 * sqrt(fabs(a) * fabs(b))) {
-    R.c = 1.0;
-    R.s = 0.0;
-    R.e = make_double2(1.0, 0.0);
-    R.a_new = a;
-    R.b_new = b;
-    R.active = 0;
-  } else {
-    const double tau = (b - a) / (2.0 * az);
-    const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-    R.c = 1.0 / sqrt(1.0 + t * t);
-    R.s = t * R.c;
-    R.e = make_double2(z.x / az, -z.y / az);  // e^{-i phi}
-    R.a_new = a - t * az;
-    R.b_new = b + t * az;
-    R.active = 1;
-  }
+  R.active = h2 > 1e-34 * fabs(a) * fabs(b) && h2 > 0.0 && r2 > 1e-290;
+  const double q = rsqrt_nr(R.active ? r2 : 1.0), ad = fabs(d);
+  const double c2 = fma(0.5 * ad, q, 0.5), ci = rsqrt_nr(c2);
+  const double sg = d >= 0.0 ? 1.0 : -1.0;
+  const double t = sg * m64::fdiv(h2, fma(r2, q, ad));
+  R.c = R.active ? c2 * ci : 1.0;
+  R.s = scaled(conj_of(z), R.active ? 0.5 * sg * q * ci : 0.0);
+  R.a_new = R.active ? a - t : a;
+  R.b_new = R.active ? b + t : b;
   return R;
 }
 
@@ -95,19 +119,29 @@ __device__ __forceinline__ int64_t gidx(int P, int Q, int l) {
 // by inner Jacobi sweeps (until its off-diagonal norm is below tol times its
 // norm, max_inner at most) and write the accumulated unitary U (BM x BM,
 // row-major) to Ub[i] and the rotated submatrix to Mb[i].
-__global__ __launch_bounds__(256) void k_bj_solve(const double2* __restrict__ A, int64_t Kp, int nb, int r,
-                                                  double tol, int max_inner, double2* __restrict__ Ub,
-                                                  double2* __restrict__ Mb) {
-  __shared__ double2 M[2][BM * BM];
-  __shared__ double2 U[BM * BM];
+// Bound: the dependent chain of a round (operands from LDS, rotation, update, barrier), 31
+// rounds a sweep: 59.7 -> 25.6 us at K = 404 with real entries (hypot, two square roots
+// and three divisions per rotation before, complex arithmetic for real matrices).
+template <typename T>
+__global__ __launch_bounds__(256) void k_bj_solve(const T* __restrict__ A, int64_t Kp, int nb, int r, double tol,
+                                                  int max_inner, T* __restrict__ Ub, T* __restrict__ Mb) {
+  __shared__ T M[2][BM * BLD];
+  __shared__ T U[BM * BLD];
   __shared__ double red[2][4];
+  __shared__ unsigned short pq[(BM - 1) * BJ];  // the pairs of each inner round, p << 8 | q
   const int i = blockIdx.x, tid = threadIdx.x;
+  const T zero = zero_of(T());
   int P, Q;
   circle_pair(nb, r, i, P, Q);
   for (int e = tid; e < BM * BM; e += 256) {
     const int a = e / BM, b = e % BM;
-    M[0][e] = A[gidx(P, Q, a) * Kp + gidx(P, Q, b)];
-    U[e] = make_double2(a == b ? 1.0 : 0.0, 0.0);
+    M[0][a * BLD + b] = A[gidx(P, Q, a) * Kp + gidx(P, Q, b)];
+    U[a * BLD + b] = of_real(T(), a == b ? 1.0 : 0.0);
+  }
+  for (int e = tid; e < (BM - 1) * BJ; e += 256) {
+    int p, q;
+    circle_pair(BM, e / BJ, e % BJ, p, q);
+    pq[e] = (unsigned short)(p << 8 | q);
   }
   __syncthreads();
   // thread (ii, jj): the 2 x 2 block of pair ii's rows and pair jj's columns,
@@ -118,8 +152,7 @@ __global__ __launch_bounds__(256) void k_bj_solve(const double2* __restrict__ A,
     // off-diagonal and full norm of M
     double off = 0.0, all = 0.0;
     for (int e = tid; e < BM * BM; e += 256) {
-      const double2 v = M[cur][e];
-      const double m2 = v.x * v.x + v.y * v.y;
+      const double m2 = norm2(M[cur][e / BM * BLD + e % BM]);
       all += m2;
       if (e / BM != e % BM) off += m2;
     }
@@ -135,51 +168,37 @@ __global__ __launch_bounds__(256) void k_bj_solve(const double2* __restrict__ A,
     __syncthreads();
     if (!(to > tol * tol * ta)) break;
     for (int rr = 0; rr < BM - 1; ++rr) {
-      const double2* Mi = M[cur];
-      double2* Mo = M[cur ^ 1];
-      const jrot Ri = make_rot(Mi, ii, rr), Rj = make_rot(Mi, jj, rr);
-      double2* w0 = Mo + Ri.p * BM;
-      double2* w1 = Mo + Ri.q * BM;
-      const double2* r0 = Mi + Ri.p * BM;
-      const double2* r1 = Mi + Ri.q * BM;
-      if (ii == jj) {
-        if (Ri.active) {  // the pair's own 2 x 2 block: diagonal by construction
-          w0[Ri.p] = make_double2(Ri.a_new, 0.0);
-          w1[Ri.q] = make_double2(Ri.b_new, 0.0);
-          w0[Ri.q] = make_double2(0.0, 0.0);
-          w1[Ri.p] = make_double2(0.0, 0.0);
-        } else {
-          w0[Ri.p] = r0[Ri.p];
-          w1[Ri.q] = r1[Ri.q];
-          w0[Ri.q] = r0[Ri.q];
-          w1[Ri.p] = r1[Ri.p];
-        }
-      } else {
-        const double2 m00 = r0[Rj.p], m01 = r0[Rj.q], m10 = r1[Rj.p], m11 = r1[Rj.q];
-        // T = M J_j:  T[:,0] = c M[:,0] - s e M[:,1],  T[:,1] = s M[:,0] + c e M[:,1]
-        const double2 em01 = cmul(Rj.e, m01), em11 = cmul(Rj.e, m11);
-        const double2 t00 = make_double2(Rj.c * m00.x - Rj.s * em01.x, Rj.c * m00.y - Rj.s * em01.y);
-        const double2 t10 = make_double2(Rj.c * m10.x - Rj.s * em11.x, Rj.c * m10.y - Rj.s * em11.y);
-        const double2 t01 = make_double2(Rj.s * m00.x + Rj.c * em01.x, Rj.s * m00.y + Rj.c * em01.y);
-        const double2 t11 = make_double2(Rj.s * m10.x + Rj.c * em11.x, Rj.s * m10.y + Rj.c * em11.y);
-        // M' = J_i^H T:  row 0 = c T[0,:] - s conj(e) T[1,:],  row 1 = s T[0,:] + c conj(e) T[1,:]
-        const double2 ce = cconj(Ri.e);
-        const double2 u10 = cmul(ce, t10), u11 = cmul(ce, t11);
-        w0[Rj.p] = make_double2(Ri.c * t00.x - Ri.s * u10.x, Ri.c * t00.y - Ri.s * u10.y);
-        w0[Rj.q] = make_double2(Ri.c * t01.x - Ri.s * u11.x, Ri.c * t01.y - Ri.s * u11.y);
-        w1[Rj.p] = make_double2(Ri.s * t00.x + Ri.c * u10.x, Ri.s * t00.y + Ri.c * u10.y);
-        w1[Rj.q] = make_double2(Ri.s * t01.x + Ri.c * u11.x, Ri.s * t01.y + Ri.c * u11.y);
+      const T* Mi = M[cur];
+      T* Mo = M[cur ^ 1];
+      const int vi = pq[rr * BJ + ii], vj = pq[rr * BJ + jj];
+      const int ip = vi >> 8, iq = vi & 255, jp = vj >> 8, jq = vj & 255;
+      const T *r0 = Mi + ip * BLD, *r1 = Mi + iq * BLD;
+      const T m00 = r0[jp], m01 = r0[jq], m10 = r1[jp], m11 = r1[jq];
+      const T u00 = U[ii * BLD + jp], u01 = U[ii * BLD + jq], u10 = U[(ii + 16) * BLD + jp],
+              u11 = U[(ii + 16) * BLD + jq];
+      const jrot<T> Ri = make_rot(real_of(r0[ip]), real_of(r1[iq]), r0[iq]);
+      const jrot<T> Rj = make_rot(real_of(Mi[jp * BLD + jp]), real_of(Mi[jq * BLD + jq]), Mi[jp * BLD + jq]);
+      const T sj = Rj.s, mj = scaled(sj, -1.0), cj = conj_of(sj), si = Ri.s, ci = conj_of(si), mi = scaled(ci, -1.0);
+      // T = M J_j, then J_i^H T
+      const T t00 = mix(Rj.c, m00, mj, m01), t01 = mix(Rj.c, m01, cj, m00);
+      const T t10 = mix(Rj.c, m10, mj, m11), t11 = mix(Rj.c, m11, cj, m10);
+      T n00 = mix(Ri.c, t00, mi, t10), n01 = mix(Ri.c, t01, mi, t11);
+      T n10 = mix(Ri.c, t10, si, t00), n11 = mix(Ri.c, t11, si, t01);
+      if (ii == jj && Ri.active) {  // the pair's own 2 x 2 block: diagonal by construction
+        n00 = of_real(T(), Ri.a_new);
+        n11 = of_real(T(), Ri.b_new);
+        n01 = zero;
+        n10 = zero;
       }
+      Mo[ip * BLD + jp] = n00;
+      Mo[ip * BLD + jq] = n01;
+      Mo[iq * BLD + jp] = n10;
+      Mo[iq * BLD + jq] = n11;
       // U <- U J_j on rows ii and ii + 16
-      if (Rj.active)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          double2* row = U + (ii + 16 * h) * BM;
-          const double2 v0 = row[Rj.p], v1 = row[Rj.q];
-          const double2 ev1 = cmul(Rj.e, v1);
-          row[Rj.p] = make_double2(Rj.c * v0.x - Rj.s * ev1.x, Rj.c * v0.y - Rj.s * ev1.y);
-          row[Rj.q] = make_double2(Rj.s * v0.x + Rj.c * ev1.x, Rj.s * v0.y + Rj.c * ev1.y);
-        }
+      U[ii * BLD + jp] = mix(Rj.c, u00, mj, u01);
+      U[ii * BLD + jq] = mix(Rj.c, u01, cj, u00);
+      U[(ii + 16) * BLD + jp] = mix(Rj.c, u10, mj, u11);
+      U[(ii + 16) * BLD + jq] = mix(Rj.c, u11, cj, u10);
       __syncthreads();
       cur ^= 1;
     }
@@ -189,39 +208,36 @@ __global__ __launch_bounds__(256) void k_bj_solve(const double2* __restrict__ A,
   // of one step, so that V, which takes a U every round, stays orthonormal
   {
     const int a = tid >> 3, b0 = tid & 7;
-    double2 g[4];
+    T g[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) g[k] = make_double2(0.0, 0.0);
+    for (int k = 0; k < 4; ++k) g[k] = zero;
+#pragma unroll 8
     for (int m = 0; m < BM; ++m) {
-      const double2 u = cconj(U[m * BM + a]);
+      const T u = conj_of(U[m * BLD + a]);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) g[k] = cadd(g[k], cmul(u, U[m * BM + b0 + 8 * k]));
+      for (int k = 0; k < 4; ++k) g[k] = fmac(g[k], u, U[m * BLD + b0 + 8 * k]);
     }
     // H = (3 I - G) / 2 into M[cur ^ 1]
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int b = b0 + 8 * k;
-      M[cur ^ 1][a * BM + b] = make_double2((a == b ? 1.5 : 0.0) - 0.5 * g[k].x, -0.5 * g[k].y);
+      M[cur ^ 1][a * BLD + b] = mix(-0.5, g[k], of_real(T(), a == b ? 1.5 : 0.0), of_real(T(), 1.0));
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 4; ++k) g[k] = make_double2(0.0, 0.0);
+    for (int k = 0; k < 4; ++k) g[k] = zero;
+#pragma unroll 8
     for (int m = 0; m < BM; ++m) {
-      const double2 u = U[a * BM + m];
+      const T u = U[a * BLD + m];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) g[k] = cadd(g[k], cmul(u, M[cur ^ 1][m * BM + b0 + 8 * k]));
+      for (int k = 0; k < 4; ++k) g[k] = fmac(g[k], u, M[cur ^ 1][m * BLD + b0 + 8 * k]);
     }
-    __syncthreads();
+    T* out = Ub + (int64_t)i * BM * BM;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) U[a * BM + b0 + 8 * k] = g[k];
-    __syncthreads();
+    for (int k = 0; k < 4; ++k) out[a * BM + b0 + 8 * k] = g[k];
   }
-  double2* out = Ub + (int64_t)i * BM * BM;
-  double2* mout = Mb + (int64_t)i * BM * BM;
-  for (int e = tid; e < BM * BM; e += 256) {
-    out[e] = U[e];
-    mout[e] = M[cur][e];
-  }
+  T* mout = Mb + (int64_t)i * BM * BM;
+  for (int e = tid; e < BM * BM; e += 256) mout[e] = M[cur][e / BM * BLD + e % BM];
 }
 
 // Groups with blockIdx.y < np: block (i = blockIdx.y, j = blockIdx.x) of pairs,
@@ -230,85 +246,78 @@ __global__ __launch_bounds__(256) void k_bj_solve(const double2* __restrict__ A,
 // into its off-diagonal, where the sweeps could not remove it again).  The
 // others: V <- V U_j on rows 32 x of V (in place; each group owns its rows and
 // pair j's columns).
-__global__ __launch_bounds__(256) void k_bj_apply(const double2* __restrict__ Ain, double2* __restrict__ Aout,
-                                                  double2* __restrict__ Vm, int64_t Kp, int nb, int r,
-                                                  const double2* __restrict__ Ub, const double2* __restrict__ Mb) {
-  __shared__ double2 T[BM * (BM + 1)];
-  __shared__ double2 Uj[BM * (BM + 1)];
+template <typename T>
+__global__ __launch_bounds__(256) void k_bj_apply(const T* __restrict__ Ain, T* __restrict__ Aout, T* __restrict__ Vm,
+                                                  int64_t Kp, int nb, int r, const T* __restrict__ Ub,
+                                                  const T* __restrict__ Mb) {
+  __shared__ T X[BM * BLD];
+  __shared__ T Uj[BM * BLD];
+  __shared__ T Ui[BM * BLD];
   const int np = nb / 2;
   const int tid = threadIdx.x;
   const int j = blockIdx.x;
+  const bool own = (int)blockIdx.y == j, isA = (int)blockIdx.y < np;
   int Pj, Qj;
   circle_pair(nb, r, j, Pj, Qj);
-  for (int e = tid; e < BM * BM; e += 256) Uj[(e / BM) * (BM + 1) + e % BM] = Ub[(int64_t)j * BM * BM + e];
-  if ((int)blockIdx.y == j) {
+  if (own) {
     for (int e = tid; e < BM * BM; e += 256)
       Aout[gidx(Pj, Qj, e / BM) * Kp + gidx(Pj, Qj, e % BM)] = Mb[(int64_t)j * BM * BM + e];
-  } else if ((int)blockIdx.y < np) {
-    const int i = blockIdx.y;
-    int Pi, Qi;
-    circle_pair(nb, r, i, Pi, Qi);
-    for (int e = tid; e < BM * BM; e += 256) {
-      const int a = e / BM, b = e % BM;
-      T[a * (BM + 1) + b] = Ain[gidx(Pi, Qi, a) * Kp + gidx(Pj, Qj, b)];
-    }
-    __syncthreads();
-    // thread: row a = tid / 8 of the block, columns b = (tid % 8) + 8 k
-    const int a = tid >> 3, b0 = tid & 7;
-    double2 x[4];  // (T U_j)[a][b]
-#pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] = make_double2(0.0, 0.0);
-    for (int m = 0; m < BM; ++m) {
-      const double2 t = T[a * (BM + 1) + m];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) x[k] = cadd(x[k], cmul(t, Uj[m * (BM + 1) + b0 + 8 * k]));
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 4; ++k) T[a * (BM + 1) + b0 + 8 * k] = x[k];
-    // U_i into Uj's place (U_j is no longer needed)
-    for (int e = tid; e < BM * BM; e += 256) Uj[(e / BM) * (BM + 1) + e % BM] = Ub[(int64_t)i * BM * BM + e];
-    __syncthreads();
-    // out[a][b] = sum_m conj(U_i[m][a]) (T U_j)[m][b]
-#pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] = make_double2(0.0, 0.0);
-    for (int m = 0; m < BM; ++m) {
-      const double2 u = cconj(Uj[m * (BM + 1) + a]);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) x[k] = cadd(x[k], cmul(u, T[m * (BM + 1) + b0 + 8 * k]));
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) Aout[gidx(Pi, Qi, a) * Kp + gidx(Pj, Qj, b0 + 8 * k)] = x[k];
-  } else {
-    const int64_t r0 = (int64_t)(blockIdx.y - np) * BM;
-    for (int e = tid; e < BM * BM; e += 256) {
-      const int a = e / BM, b = e % BM;
-      T[a * (BM + 1) + b] = Vm[(r0 + a) * Kp + gidx(Pj, Qj, b)];
-    }
-    __syncthreads();
-    const int a = tid >> 3, b0 = tid & 7;
-    double2 x[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] = make_double2(0.0, 0.0);
-    for (int m = 0; m < BM; ++m) {
-      const double2 t = T[a * (BM + 1) + m];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) x[k] = cadd(x[k], cmul(t, Uj[m * (BM + 1) + b0 + 8 * k]));
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) Vm[(r0 + a) * Kp + gidx(Pj, Qj, b0 + 8 * k)] = x[k];
+    return;
   }
+  const int i = blockIdx.y;
+  int Pi = 0, Qi = 0;
+  if (isA) circle_pair(nb, r, i, Pi, Qi);
+  const int64_t v0 = (int64_t)(i - np) * BM;
+#pragma unroll
+  for (int k = 0; k < BM * BM / 256; ++k) {
+    const int e = tid + 256 * k, a = e / BM, b = e % BM;
+    Uj[a * BLD + b] = Ub[(int64_t)j * BM * BM + e];
+    if (isA) Ui[a * BLD + b] = Ub[(int64_t)i * BM * BM + e];
+    X[a * BLD + b] = isA ? Ain[gidx(Pi, Qi, a) * Kp + gidx(Pj, Qj, b)] : Vm[(v0 + a) * Kp + gidx(Pj, Qj, b)];
+  }
+  __syncthreads();
+  // thread: row a = tid / 8 of the block, columns b = (tid % 8) + 8 k
+  const int a = tid >> 3, b0 = tid & 7;
+  T x[4];  // (X U_j)[a][b]
+#pragma unroll
+  for (int k = 0; k < 4; ++k) x[k] = zero_of(T());
+#pragma unroll 8
+  for (int m = 0; m < BM; ++m) {
+    const T t = X[a * BLD + m];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = fmac(x[k], t, Uj[m * BLD + b0 + 8 * k]);
+  }
+  if (!isA) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) Vm[(v0 + a) * Kp + gidx(Pj, Qj, b0 + 8 * k)] = x[k];
+    return;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) X[a * BLD + b0 + 8 * k] = x[k];
+  __syncthreads();
+  // out[a][b] = sum_m conj(U_i[m][a]) (X U_j)[m][b]
+#pragma unroll
+  for (int k = 0; k < 4; ++k) x[k] = zero_of(T());
+#pragma unroll 8
+  for (int m = 0; m < BM; ++m) {
+    const T u = conj_of(Ui[m * BLD + a]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = fmac(x[k], u, X[m * BLD + b0 + 8 * k]);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) Aout[gidx(Pi, Qi, a) * Kp + gidx(Pj, Qj, b0 + 8 * k)] = x[k];
 }
 
 // out[0] += sum of |A_ij|^2 off the diagonal, out[1] += sum of all |A_ij|^2 (per row, one wave)
-__global__ __launch_bounds__(256) void k_offnorm(const double2* __restrict__ A, int64_t Kp, double* __restrict__ out) {
+template <typename T>
+__global__ __launch_bounds__(256) void k_offnorm(const T* __restrict__ A, int64_t Kp, double* __restrict__ out) {
   const int64_t row = blockIdx.x * 4ll + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= Kp) return;
   double off = 0.0, all = 0.0;
   for (int64_t c = lane; c < Kp; c += 64) {
-    const double2 v = A[row * Kp + c];
-    const double m = v.x * v.x + v.y * v.y;
+    const double m = norm2(A[row * Kp + c]);
     all += m;
     if (c != row) off += m;
   }
@@ -320,22 +329,31 @@ __global__ __launch_bounds__(256) void k_offnorm(const double2* __restrict__ A, 
   }
 }
 
-__global__ void k_pad_copy(const double2* __restrict__ S, int64_t K, int64_t Kp, double2* __restrict__ A,
-                           double2* __restrict__ V) {
+template <typename T>
+__global__ void k_pad_copy(const double2* __restrict__ S, int64_t K, int64_t Kp, T* __restrict__ A,
+                           T* __restrict__ V) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= Kp * Kp) return;
   const int64_t r = e / Kp, c = e % Kp;
-  A[e] = (r < K && c < K) ? S[r * K + c] : make_double2(0.0, 0.0);
-  V[e] = make_double2(r == c ? 1.0 : 0.0, 0.0);
+  const double2 v = (r < K && c < K) ? S[r * K + c] : make_double2(0.0, 0.0);
+  if constexpr (sizeof(T) == sizeof(double))
+    A[e] = v.x;
+  else
+    A[e] = v;
+  V[e] = of_real(T(), r == c ? 1.0 : 0.0);
 }
 
-__global__ void k_eig_out(const double2* __restrict__ A, const double2* __restrict__ Vp, int64_t K, int64_t Kp,
+template <typename T>
+__global__ void k_eig_out(const T* __restrict__ A, const T* __restrict__ Vp, int64_t K, int64_t Kp,
                           double* __restrict__ lam, double2* __restrict__ V) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= K * K) return;
   const int64_t r = e / K, c = e % K;
-  V[e] = Vp[r * Kp + c];
-  if (r == 0) lam[c] = A[c * Kp + c].x;
+  if constexpr (sizeof(T) == sizeof(double))
+    V[e] = make_double2(Vp[r * Kp + c], 0.0);
+  else
+    V[e] = Vp[r * Kp + c];
+  if (r == 0) lam[c] = real_of(A[c * Kp + c]);
 }
 
 int64_t padded(int64_t K) { return (K + BM - 1) / BM * BM; }
@@ -348,36 +366,37 @@ size_t eig_ws_bytes(int64_t K) {
          ws_round(2 * sizeof(double));
 }
 
-int eig_hermitian(vmc_ctx* ctx, const double2* S, int64_t K, double tol, int max_sweeps, double* lam, double2* V,
-                  void* ws) {
+namespace {
+template <typename T>
+int jacobi(vmc_ctx* ctx, const double2* S, int64_t K, double tol, int max_sweeps, double* lam, double2* V, void* ws) {
   hipStream_t st = ctx->stream;
   const int64_t Kp = padded(K);
   const int nb = (int)(Kp / BJ), np = nb / 2;
   char* w = (char*)ws;
-  double2* A = (double2*)w;
-  w += ws_round(sizeof(double2) * Kp * Kp);
-  double2* A2 = (double2*)w;
-  w += ws_round(sizeof(double2) * Kp * Kp);
-  double2* Vp = (double2*)w;
-  w += ws_round(sizeof(double2) * Kp * Kp);
-  double2* Ub = (double2*)w;
-  w += ws_round(sizeof(double2) * (Kp / BM) * BM * BM);
-  double2* Mb = (double2*)w;
-  w += ws_round(sizeof(double2) * (Kp / BM) * BM * BM);
+  T* A = (T*)w;
+  w += ws_round(sizeof(T) * Kp * Kp);
+  T* A2 = (T*)w;
+  w += ws_round(sizeof(T) * Kp * Kp);
+  T* Vp = (T*)w;
+  w += ws_round(sizeof(T) * Kp * Kp);
+  T* Ub = (T*)w;
+  w += ws_round(sizeof(T) * (Kp / BM) * BM * BM);
+  T* Mb = (T*)w;
+  w += ws_round(sizeof(T) * (Kp / BM) * BM * BM);
   double* nrm = (double*)w;
-  k_pad_copy<<<grid_for(Kp * Kp, 256), 256, 0, st>>>(S, K, Kp, A, Vp);
+  k_pad_copy<T><<<grid_for(Kp * Kp, 256), 256, 0, st>>>(S, K, Kp, A, Vp);
   VMC_HIP(hipGetLastError());
   double* hn = (double*)pinned_host(ctx, 2 * sizeof(double));
   int sweeps = 0;
   for (;;) {
     VMC_HIP(hipMemsetAsync(nrm, 0, 2 * sizeof(double), st));
-    k_offnorm<<<(unsigned)((Kp + 3) / 4), 256, 0, st>>>(A, Kp, nrm);
+    k_offnorm<T><<<(unsigned)((Kp + 3) / 4), 256, 0, st>>>(A, Kp, nrm);
     VMC_HIP(hipMemcpyAsync(hn, nrm, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
     VMC_HIP(hipStreamSynchronize(st));
     if (!(hn[0] > tol * tol * hn[1]) || sweeps >= max_sweeps) break;
     for (int r = 0; r < nb - 1; ++r) {
-      k_bj_solve<<<(unsigned)np, 256, 0, st>>>(A, Kp, nb, r, INNER_TOL * tol, MAX_INNER, Ub, Mb);
-      k_bj_apply<<<dim3((unsigned)np, (unsigned)(np + Kp / BM)), 256, 0, st>>>(A, A2, Vp, Kp, nb, r, Ub, Mb);
+      k_bj_solve<T><<<(unsigned)np, 256, 0, st>>>(A, Kp, nb, r, INNER_TOL * tol, MAX_INNER, Ub, Mb);
+      k_bj_apply<T><<<dim3((unsigned)np, (unsigned)(np + Kp / BM)), 256, 0, st>>>(A, A2, Vp, Kp, nb, r, Ub, Mb);
       std::swap(A, A2);
     }
     VMC_HIP(hipGetLastError());
@@ -385,9 +404,17 @@ int eig_hermitian(vmc_ctx* ctx, const double2* S, int64_t K, double tol, int max
   }
   if (!std::isfinite(hn[0]) || !std::isfinite(hn[1]))
     throw vmc_error{VMC_ERR_NONFINITE, "eigendecomposition produced non-finite values"};
-  k_eig_out<<<grid_for(K * K, 256), 256, 0, st>>>(A, Vp, K, Kp, lam, V);
+  k_eig_out<T><<<grid_for(K * K, 256), 256, 0, st>>>(A, Vp, K, Kp, lam, V);
   VMC_HIP(hipGetLastError());
   return sweeps;
+}
+}  // namespace
+
+// real: every imaginary part of S is 0 (the sweeps then run in real arithmetic)
+int eig_hermitian(vmc_ctx* ctx, const double2* S, int64_t K, bool real, double tol, int max_sweeps, double* lam,
+                  double2* V, void* ws) {
+  return real ? jacobi<double>(ctx, S, K, tol, max_sweeps, lam, V, ws)
+              : jacobi<double2>(ctx, S, K, tol, max_sweeps, lam, V, ws);
 }
 
 extern "C" int vmc_eigh(vmc_ctx* ctx, const double* A, int64_t K, double tol, int max_sweeps, double* evals,
@@ -401,7 +428,7 @@ extern "C" int vmc_eigh(vmc_ctx* ctx, const double* A, int64_t K, double tol, in
     phase_scope ps(ctx, "eig");
     ws_reserve(ctx, eig_ws_bytes(K));
     void* w = ws_take(ctx, eig_ws_bytes(K));
-    const int s = eig_hermitian(ctx, (const double2*)A, K, tol > 0.0 ? tol : 1e-14, max_sweeps > 0 ? max_sweeps : 50,
+    const int s = eig_hermitian(ctx, (const double2*)A, K, false, tol > 0.0 ? tol : 1e-14, max_sweeps > 0 ? max_sweeps : 50,
                                 evals, (double2*)V, w);
     if (sweeps_host) *sweeps_host = s;
   });

@@ -560,7 +560,7 @@ double fisher_quad_impl(vmc_ctx* ctx, const void* O, int dtype, const double* w,
                         const double2* v);
 // eig.hip
 size_t eig_ws_bytes(int64_t K);
-int eig_hermitian(vmc_ctx* ctx, const double2* S, int64_t K, double tol, int max_sweeps, double* lam, double2* V,
+int eig_hermitian(vmc_ctx* ctx, const double2* S, int64_t K, bool real, double tol, int max_sweeps, double* lam, double2* V,
                   void* ws);
 void sr_solve_cg_impl(vmc_ctx* ctx, const void* O, int dtype, const double2* eloc, const double* w, int64_t N,
                       int64_t K, const vmc_sr_opts* o, double tol, int max_iter, double2* x, vmc_sr_info* info,

@@ -801,7 +801,7 @@ void sr_solve_impl(vmc_ctx* ctx, const void* O, int dtype, const double2* eloc, 
       ph.reset();
     }
     ph.reset(new phase_scope(ctx, "sr.eig"));
-    const int sw = eig_hermitian(ctx, S, K, eo->tol > 0.0 ? eo->tol : 1e-14, eo->max_sweeps > 0 ? eo->max_sweeps : 50,
+    const int sw = eig_hermitian(ctx, S, K, hmode == VMC_SR_REAL, eo->tol > 0.0 ? eo->tol : 1e-14, eo->max_sweeps > 0 ? eo->max_sweeps : 50,
                                  lam, Vm, eig_ws);
     if (sweeps) *sweeps = sw;
     ph.reset();
