@@ -464,6 +464,7 @@ __device__ __forceinline__ int wave_isum_uniform(int v) {
 // -------------------------------------------------- cross-file launchers --
 // rbm.hip
 void rbm_theta(vmc_model* m, const uint64_t* s, int64_t B, double2* theta, hipStream_t st = nullptr);
+void rbm_log_psi_theta(vmc_model* m, const uint64_t* s, int64_t B, const double2* theta, double2* logpsi);
 void rbm_ensure_tables(vmc_model* m, const vmc_ham* H, int move_kind);
 void rbm_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi);
 void rbm_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, double2* eloc);

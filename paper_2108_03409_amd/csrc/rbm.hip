@@ -493,6 +493,12 @@ void rbm_ensure_tables(vmc_model* m, const vmc_ham* H, int move_kind) {
   tb.param_version = m->version;
 }
 
+// log psi from theta of the same configurations
+void rbm_log_psi_theta(vmc_model* m, const uint64_t* s, int64_t B, const double2* theta, double2* logpsi) {
+  k_logpsi<<<(unsigned)B, 64, 0, m->ctx->stream>>>(m->params, theta, s, B, m->N, m->W, m->Nh, logpsi);
+  VMC_HIP(hipGetLastError());
+}
+
 void rbm_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
   vmc_ctx* ctx = m->ctx;
   const int64_t chunk = std::min<int64_t>(B, kChunk);
@@ -501,9 +507,7 @@ void rbm_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
   for (int64_t b0 = 0; b0 < B; b0 += chunk) {
     const int64_t nb = std::min(chunk, B - b0);
     rbm_theta(m, s + b0 * m->W, nb, theta);
-    k_logpsi<<<(unsigned)nb, 64, 0, ctx->stream>>>(m->params, theta, s + b0 * m->W, nb, m->N, m->W, m->Nh,
-                                                  logpsi + b0);
-    VMC_HIP(hipGetLastError());
+    rbm_log_psi_theta(m, s + b0 * m->W, nb, theta, logpsi + b0);
   }
 }
 

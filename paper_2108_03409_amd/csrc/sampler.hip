@@ -1,20 +1,20 @@
 // Metropolis sampler (Sec. 2.1 and Sec. 4.2 "Sampler"): all chains advance in
-// sync, one wavefront per chain (two when the chains leave SIMDs idle), the
-// chain's hidden units spread over the lanes (t_j = tanh theta_j in registers,
-// theta_j in lane-private LDS slots).  A proposal costs N_h/64 complex
+// sync, one or two wavefronts per chain, the chain's hidden units spread over
+// the lanes (t_j = tanh theta_j in registers).  A proposal costs N_h/64 complex
 // multiply-adds per lane plus one wave reduction, using the move identity of
 // rbm.hip:
 //   2 Re(log psi(s') - log psi(s)) = 2 Re(-2 sigma_m alpha_m + LC_m)
 //                                    + sum_j log|1 - sigma_m t_j T_jm|^2.
-// On acceptance theta_j -= 2 sigma_m D_jm and t_j follows the tanh addition
-// rule t' = (t - sigma T) / (1 - sigma t T); theta is rebuilt from the spins
-// at the start of every call and t from theta at every recorded sample.
+// On acceptance t_j follows the tanh addition rule
+// t' = (t - sigma T) / (1 - sigma t T); theta itself is not carried along: it is
+// rebuilt from the spins at the start of every call and, with t, at every
+// recorded sample.
 //
 // VMC_PROP_MADE_MIX: each sweep starts with global Metropolis-Hastings steps
 // made by all chains together (mixsampler.hip; the proposals of the next step
 // are formed on a second stream during the sweep); the sweep's single-spin
-// flips then run here, one launch per sweep, with each chain's theta kept in
-// device memory between the launches.
+// flips then run here, one launch per sweep, and the matrix cores form each
+// chain's theta for the next global step and the record from its spins.
 #include "internal.h"
 
 using namespace dev;
@@ -24,8 +24,8 @@ namespace {
 struct sampler_args {
   const double2* params;
   const double2* Wt;
-  const double2* T;  // [n_moves][N_h]
   const double2* D;  // [n_moves][N_h]
+  const double2* T;  // [n_moves][N_h]
   const double2* LC;
   const double2* alpha;
   const int2* bonds;
@@ -43,25 +43,36 @@ struct sampler_args {
   uint64_t* s_out;
   double2* logpsi_out;
   unsigned long long* acc;  // [n_chains] accepted proposals (added to)
-  double2* theta_store;     // [n_chains][N_h] theta kept between launches (NULL: none)
-  int theta_in;             // 1: start from theta_store instead of rebuilding theta from the spins
+  const double2* theta;     // [n_chains][N_h] theta of the chains' spins (NULL: rebuilt here)
 };
 
-// One chain per work-group of NW waves.  With NW = 2 (chains fewer than the
-// device's SIMDs, so that one wave per chain would leave SIMDs idle) wave w
-// takes the hidden units j = 64 Q w + 64 q + lane; both waves keep their own
-// copy of the configuration and of the step tables and reach the same
-// decisions, exchanging only their partial ratio (mantissa and exponent)
-// through LDS behind one barrier per proposal.  Up to four slots of hidden
-// units the kernel is held to 256 registers, so that two waves share a SIMD
-// (1 024 chains of two waves fill 2 048 wave slots on 1 024 SIMDs).
-template <int Q, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(Q <= 4 ? 2 : 1))) void k_metropolis(sampler_args a) {
+// One chain per work-group of NW waves.  With NW = 2 wave w takes the hidden
+// units j = 64 Q w + 64 q + lane; both waves keep their own copy of the
+// configuration and of the step tables and reach the same decisions, exchanging
+// only their partial ratio (mantissa and exponent) through LDS behind one
+// barrier per proposal.  The configuration and the draws of 64 steps lie over the
+// lanes, and everything a proposal takes from them (its move, site, spin and the
+// ratio it needs) is read by lane number into scalar registers, so that the chain's
+// dependent path holds no LDS read and the rows are addressed without vector
+// arithmetic.  TRACK: theta follows the accepted moves, and every record forms log
+// psi and t anew from it; without it (global proposals) the caller does so between
+// launches, and the row of D is not read at all.
+// Bound: the dependent path of ratio, reduction, decision and update at one or two
+// waves per SIMD; with many chains the vector instructions and the row of T (12.8 KB
+// a proposal at N_h = 800) from L2.  Waves per SIMD: without TRACK three where the
+// registers allow (20 x 20: 11.1 ms for 4 sweeps instead of 12.1 with two); the
+// two-wave groups of few chains are held to two, without which the dispatcher
+// leaves three on some SIMDs and one on others (Heisenberg 10 x 10: 0.92 instead of 0.79 ms).
+// 20 x 20, N_h = 800, 4 096 chains: 8.25 -> 1.8 ms a sweep; Heisenberg 10 x 10,
+// N_h = 400, 1 024 chains x 8 sweeps 1.13 -> 0.79 ms, 4 096 chains x 4 sweeps
+// 2.36 -> 1.0 ms (theta in LDS, rows of T and D per proposal, step tables in LDS,
+// one wave of 16 slots per chain above 512 units before).
+template <int Q, int NW, bool TRACK>
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(TRACK || Q > 7 || (NW == 2 && Q <= 4) ? 2 : 3,
+                                   NW == 2 && (TRACK || Q <= 4) ? 2 : 8))) void k_metropolis(sampler_args a) {
   __shared__ uint64_t cbs[NW][64];  // chain configuration, W <= 64 words (one copy per wave)
-  // theta_j of the chain in lane-private LDS slots [q][lane]: registers hold
-  // only t_j = tanh theta_j (theta in registers measured slower)
-  __shared__ double2 thss[NW][Q * 64];
-  __shared__ double pm_s[2][NW];  // partial ratios of the waves (double-buffered by step parity)
+  __shared__ double pm_s[2][NW];  // partial ratios of the waves, alternating over the exchanges
   __shared__ int pe_s[2][NW];
   __shared__ double2 lp_s[NW];
   const int c = blockIdx.x;
@@ -69,7 +80,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(Q <= 4 
   const int lane = threadIdx.x & 63;
   const int wv = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   uint64_t* cb = cbs[wv];
-  double2* ths = thss[wv];
   const int jb = 64 * Q * wv;  // first hidden unit of this wave
   const int N = a.N, W = a.W, Nh = a.Nh;
 
@@ -102,157 +112,179 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(Q <= 4 
   }
   __syncthreads();
 
-  // theta_j = b_j + sum_i W_ji sigma_i for the lane's hidden units (or the
-  // value kept from the previous launch of this call)
-  double2 tt[Q];
-  auto theta = [&](int q) -> double2& { return ths[q * 64 + lane]; };
+  // theta_j = b_j + sum_i W_ji sigma_i for the lane's hidden units, four sites'
+  // rows in flight; 0 past N_h
+  double2 tt[Q], th[Q];
+  auto build_theta = [&] {
+    int64_t at[Q];
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int j = jb + lane + 64 * q;
-    double2 acc = j < Nh ? a.params[N + j] : make_double2(0.0, 0.0);
-    if (j < Nh) {
-      if (a.theta_in) {
-        acc = a.theta_store[(int64_t)c * Nh + j];
-      } else {
-        for (int i = 0; i < N; ++i) {
-          const bool up = (cb[i >> 6] >> (i & 63)) & 1ull;
-          const double2 w = a.Wt[(int64_t)i * Nh + j];
-          acc.x += up ? w.x : -w.x;
-          acc.y += up ? w.y : -w.y;
-        }
+    for (int q = 0; q < Q; ++q) {
+      const int j = jb + lane + 64 * q;
+      at[q] = j < Nh ? j : Nh - 1;
+      th[q] = a.params[N + at[q]];
+    }
+#pragma unroll 4
+    for (int i = 0; i < N; ++i) {
+      const double sg = ((cb[i >> 6] >> (i & 63)) & 1ull) ? 1.0 : -1.0;
+      const double2* w = a.Wt + (int64_t)i * Nh;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const double2 v = w[at[q]];
+        th[q] = make_double2(fma(sg, v.x, th[q].x), fma(sg, v.y, th[q].y));
       }
     }
-    theta(q) = acc;
-  }
 #pragma unroll
-  for (int q = 0; q < Q; ++q) tt[q] = ctanh(theta(q));
+    for (int q = 0; q < Q; ++q)
+      if (jb + lane + 64 * q >= Nh) th[q] = make_double2(0.0, 0.0);
+  };
+  if (a.theta) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int j = jb + lane + 64 * q;
+      th[q] = j < Nh ? a.theta[(int64_t)c * Nh + j] : make_double2(0.0, 0.0);
+    }
+  } else {
+    build_theta();
+  }
+  // t = tanh theta, and the sum of log cosh theta over the lane's units if it is asked for:
+  // one unit at a time through lane-private LDS slots, so that the elementary functions
+  // stand in the code once and the loop over the proposals stays in the instruction cache
+  __shared__ double2 ths[NW][Q][64];
+  auto tanh_theta = [&](bool logs) {
+    double2 lp = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) ths[wv][q][lane] = th[q];
+#pragma unroll 1
+    for (int q = 0; q < Q; ++q) {
+      const double2 v = ths[wv][q][lane];
+      if (logs && jb + lane + 64 * q < Nh) lp = cadd(lp, clogcosh(v));
+      ths[wv][q][lane] = ctanh(v);
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) tt[q] = ths[wv][q][lane];
+    return lp;
+  };
+  tanh_theta(false);
 
   unsigned long long accepted = 0;
   const int64_t total = a.therm_steps + a.n_record * a.sweep;
   // The move of step t + 1 is known from its counter before step t resolves:
-  // its rows of T (the ratio) and D (the update on acceptance) are loaded one
-  // step ahead (local-move kernels with up to 512 hidden units, where the
-  // extra registers fit).
-  constexpr bool PF = Q <= 8;
+  // its row of T is loaded one step ahead.
   // The counters of 64 consecutive steps are drawn together, one per lane, into
-  // a table of moves and log u (the same Philox values as one per step; the
-  // test u < exp(r) is decided from log u, below, alike away from |r - log u|
-  // at the rounding level).
-  __shared__ int mv_ss[NW][64];
-  __shared__ double uv_ss[NW][64];
-  int* mv_s = mv_ss[wv];
-  double* uv_s = uv_ss[wv];
-  // entry (m, lane + 64 q) of a [n_moves][N_h] table, zero past N_h: the
-  // address is clamped and the value selected, so the proposal and the update
-  // run without branches over the lane's units (a unit past N_h has t = 0 and
-  // T = D = 0, hence f = 1 and no change)
-  auto row_entry = [&](const double2* tab, int m, int q) {
-    const int j = jb + lane + 64 * q;
-    const double2 v = tab[(int64_t)m * Nh + (j < Nh ? j : Nh - 1)];
-    return j < Nh ? v : make_double2(0.0, 0.0);
+  // a table of moves and of the ratio each needs to be accepted (the same Philox
+  // values as one per step).  accept iff L = sum_j log |f_j|^2 > log u - c,
+  // c = 2 Re(-2 sigma alpha + LC), without a logarithm on the chain's path: each
+  // lane's product of |f|^2 as mantissa in [1/2, 1) and exponent, the wave's
+  // product M 2^E (M >= 2^-64, no underflow), and M 2^E > e^(log u - c) tested as
+  // ldexp(M, E - n) > 2^r with (log u - c) / ln 2 = n + r, n integer, r in [0, 1):
+  // n and 2^r of both values of sigma stand in the table.  Decides as
+  // log u < c + L except within rounding of a tie.  Step s of a group of 64 stands
+  // in lane s of its registers.
+  struct draw_t {
+    int m, x;        // move; its sites (first | second << 16)
+    double p2[2];    // [sigma > 0]
+    int n2[2];
   };
+  // entries of the lane's units in row m of a [n_moves][N_h] table, zero past N_h
+  // (out of the buffer's range: a unit past N_h has t = 0 and T = 0, hence f = 1
+  // and no change)
+  auto load_row = [&](const double2* tab, int m, double2(&r)[Q]) {
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(tab + (int64_t)m * Nh), 0, Nh * 16, 0x00027000);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      r[q] = __builtin_bit_cast(double2,
+                                __builtin_amdgcn_raw_buffer_load_b128(rsrc, (jb + lane) * 16, 1024 * q, 0));
+  };
+  const int exch = a.proposal == VMC_PROP_EXCHANGE;
   auto draw64 = [&](int64_t s0) {
     const uint64_t tl = a.t0 + (uint64_t)(s0 + lane);
     const uint4 y = philox(make_uint4((uint32_t)c, (uint32_t)tl, (uint32_t)(tl >> 32), 0u), a.key);
-    __syncthreads();
-    mv_s[lane] = (int)to_index(y.x, (uint32_t)a.n_moves);
-    uv_s[lane] = log(to_uniform(y.y, y.z));
-    __syncthreads();
-  };
-  draw64(0);
-  // Two sets of prefetch registers, A and B, alternate between the current
-  // step's rows and the next step's (the loop runs two steps per trip), so
-  // that no step copies its prefetched rows from one set to the other.
-  constexpr int QP = PF ? Q : 1;
-  double2 TA[QP], DA[QP], TB[QP], DB[QP];
-  double2 alA = make_double2(0.0, 0.0), lcA = alA;  // alpha and LC of the move
-  int2 bdA = make_int2(0, 0);                       // its bond (exchange moves)
-  double2 alB = alA, lcB = alA;
-  int2 bdB = bdA;
-  if (PF) {
-    const int mn = mv_s[0];
-    alA = a.alpha[mn];
-    lcA = a.LC[mn];
-    if (a.proposal == VMC_PROP_EXCHANGE) bdA = a.bonds[mn];
-#pragma unroll
-    for (int q = 0; q < QP; ++q) {
-      TA[q] = row_entry(a.T, mn, q);
-      DA[q] = row_entry(a.D, mn, q);
+    draw_t d;
+    d.m = d.x = (int)to_index(y.x, (uint32_t)a.n_moves);
+    const double lu = log(to_uniform(y.y, y.z));
+    const double2 al = a.alpha[d.m], lc = a.LC[d.m];
+    if (exch) {
+      const int2 bd = a.bonds[d.m];
+      d.x = bd.x | (bd.y << 16);
     }
-  }
-  constexpr int NSTEP = PF ? 2 : 1;  // proposals per trip of the loop (one without prefetch)
-  for (int64_t s0 = 0; s0 < total; s0 += NSTEP) {
 #pragma unroll
-  for (int h = 0; h < NSTEP; ++h) {
+    for (int up = 0; up < 2; ++up) {
+      const double sg = up ? 1.0 : -1.0;
+      const double t2 =
+          fmin(fmax((lu - 2.0 * (-2.0 * sg * al.x + lc.x)) * 1.4426950408889634074, -4096.0), 4096.0);
+      const double n2 = floor(t2);
+      d.p2[up] = exp2(t2 - n2);
+      d.n2[up] = (int)n2;
+    }
+    return d;
+  };
+  auto rl = [](int v, int i) { return __builtin_amdgcn_readlane(v, i); };
+  // the configuration, word w in lane w
+  uint32_t cl = lane < W ? (uint32_t)cb[lane] : 0u, ch = lane < W ? (uint32_t)(cb[lane] >> 32) : 0u;
+  auto spin_up = [&](int i) {
+    const uint32_t w = i & 32 ? (uint32_t)__builtin_amdgcn_readlane((int)ch, i >> 6)
+                              : (uint32_t)__builtin_amdgcn_readlane((int)cl, i >> 6);
+    return (w >> (i & 31)) & 1u;
+  };
+  auto flip = [&](int i) {
+    const uint32_t b = lane == (i >> 6) ? 1u << (i & 31) : 0u;
+    cl ^= i & 32 ? 0u : b;
+    ch ^= i & 32 ? b : 0u;
+  };
+  // Two sets of row registers alternate between the current step and the next
+  // (the loop runs two steps per trip), so that no row is copied from one set to
+  // the other; rows two and three steps ahead measured no faster.
+  double2 TR[2][Q];
+  int mr[2], xr[2];
+  // TRACK: theta, and the row of D the last accepted move adds to it (factor dsg,
+  // zero after a rejection, when the row asked for is the first one, a hit in L1)
+  constexpr int QT = TRACK ? Q : 1;
+  double2 DP[QT];
+  double dsg = 0.0;
+#pragma unroll
+  for (int q = 0; q < QT; ++q) DP[q] = make_double2(0.0, 0.0);
+  int par = 0;  // buffer of the waves' exchange, alternating over the exchanges
+  draw_t cur = draw64(0);
+  mr[0] = rl(cur.m, 0);
+  xr[0] = rl(cur.x, 0);
+  load_row(a.T, mr[0], TR[0]);
+  int64_t to_record = a.therm_steps + a.sweep, row = c;  // steps to the next record, its row
+  for (int64_t s0 = 0; s0 < total; s0 += 2) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
     const int64_t step = s0 + h;
     if (h > 0 && step >= total) break;
-    // the current move's prefetched rows in (Tc, Dc, alc, lcc, bdc), the
-    // next move's loaded into (Tn, Dn, aln, lcn, bdn)
-    const double2(&Tc)[QP] = h ? TB : TA;
-    const double2(&Dc)[QP] = h ? DB : DA;
-    const double2 alc = h ? alB : alA, lcc = h ? lcB : lcA;
-    const int2 bdc = h ? bdB : bdA;
-    double2(&Tn)[QP] = h ? TA : TB;
-    double2(&Dn)[QP] = h ? DA : DB;
-    double2& aln = h ? alA : alB;
-    double2& lcn = h ? lcA : lcB;
-    int2& bdn = h ? bdA : bdB;
-    const int m = mv_s[step & 63];
-    const double lu = uv_s[step & 63];
-    if (step + 1 < total) {
-      if (((step + 1) & 63) == 0) draw64(step + 1);
-      if (PF) {
-        const int mn = mv_s[(step + 1) & 63];
-        aln = a.alpha[mn];
-        lcn = a.LC[mn];
-        if (a.proposal == VMC_PROP_EXCHANGE) bdn = a.bonds[mn];
-#pragma unroll
-        for (int q = 0; q < QP; ++q) {
-          Tn[q] = row_entry(a.T, mn, q);
-          Dn[q] = row_entry(a.D, mn, q);
-        }
-      }
-    }
-    {
-    int site = m, site2 = -1;
-    bool identity = false;
-    if (a.proposal == VMC_PROP_EXCHANGE) {
-      const int2 bd = PF ? bdc : a.bonds[m];
-      site = bd.x;
-      site2 = bd.y;
-      identity = ((cb[site >> 6] >> (site & 63)) & 1ull) == ((cb[site2 >> 6] >> (site2 & 63)) & 1ull);
-    }
-    if (identity) {
-      ++accepted;
+    const int i = (int)(step & 63);
+    const double2(&Tc)[Q] = TR[h];
+    const int m = mr[h], x = xr[h];
+    const int site = exch ? x & 0xffff : x, site2 = x >> 16;
+    const uint32_t up = spin_up(site);
+    const double p2 = up ? readlane_f64(cur.p2[1], i) : readlane_f64(cur.p2[0], i);
+    const int n2 = up ? rl(cur.n2[1], i) : rl(cur.n2[0], i);
+    if (h == 1 && i == 63 && step + 1 < total) cur = draw64(step + 1);
+    mr[h ^ 1] = rl(cur.m, (i + 1) & 63);
+    xr[h ^ 1] = rl(cur.x, (i + 1) & 63);
+    load_row(a.T, mr[h ^ 1], TR[h ^ 1]);
+    if (exch && up == spin_up(site2)) {
+      ++accepted;  // the exchange changes nothing
     } else {
-      const double sg = ((cb[site >> 6] >> (site & 63)) & 1ull) ? 1.0 : -1.0;
+      const double sg = up ? 1.0 : -1.0;
       double prod = 1.0;
-      // per hidden unit the factor f = 1 - sigma t_j T_jm and |f|^2, kept for the update
-      double2 fq[Q];
-      double nq[Q];
+      // per hidden unit the factor f = 1 - sigma t_j T_jm and |f|^2
+      double2 f[Q];
+      double n[Q];
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const double2 p = cmul(tt[q], PF ? Tc[PF ? q : 0] : row_entry(a.T, m, q));
-        fq[q] = make_double2(1.0 - sg * p.x, -sg * p.y);
-        nq[q] = fq[q].x * fq[q].x + fq[q].y * fq[q].y;
-        prod *= nq[q];
+        const double2 p = cmul(tt[q], Tc[q]);
+        f[q] = make_double2(1.0 - sg * p.x, -sg * p.y);
+        n[q] = f[q].x * f[q].x + f[q].y * f[q].y;
+        prod *= n[q];
       }
-      // accept iff L = sum_j log |f_j|^2 > lu - c, c = 2 Re(-2 sigma alpha + LC), without a
-      // logarithm on the chain's path: each lane's product as mantissa in [1/2, 1) and
-      // exponent, the wave's product M 2^E (M >= 2^-64, no underflow), and M 2^E > e^(lu - c)
-      // tested as ldexp(M, E - n) > 2^r with (lu - c) / ln 2 = n + r, n integer, r in [0, 1);
-      // n and 2^r do not depend on the ratio and are formed beside it.  Decides as
-      // lu < c + L except within rounding of a tie.
-      const double2 al = PF ? alc : a.alpha[m], lc = PF ? lcc : a.LC[m];
-      const double t2 = fmin(fmax((lu - 2.0 * (-2.0 * sg * al.x + lc.x)) * 1.4426950408889634074, -4096.0), 4096.0);
-      const double n2 = floor(t2);
-      const double p2 = exp2(t2 - n2);
       int ex;
       const double mt = frexp(prod, &ex);
       double M = wave_prod_uniform(mt);
       int E = wave_isum_uniform(ex);
       if constexpr (NW > 1) {  // the other waves' units: every wave forms the same product
-        const int par = (int)(step & 1);
         if (lane == 0) {
           pm_s[par][wv] = M;
           pe_s[par][wv] = E;
@@ -267,81 +299,69 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(Q <= 4 
           M *= pm_s[par][w];
           E += pe_s[par][w];
         }
+        par ^= 1;
       }
-      const bool acc = ldexp(M, E - (int)n2) > p2;  // one value for the work-group: a uniform decision
+      // one value for the work-group: a uniform decision
+      const bool acc = __builtin_amdgcn_readfirstlane(ldexp(M, E - n2) > p2);
+      if constexpr (TRACK) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+          th[q] = make_double2(fma(-dsg, DP[q].x, th[q].x), fma(-dsg, DP[q].y, th[q].y));
+        dsg = acc ? 2.0 * sg : 0.0;
+        load_row(a.D, acc ? m : 0, DP);
+      }
       if (acc) {
         ++accepted;
-        double2 th[Q];  // all LDS reads first: one wait instead of one per unit
-#pragma unroll
-        for (int q = 0; q < Q; ++q) th[q] = theta(q);
+        // t' = (t - sigma T) / f = (t - sigma T) conj(f) / |f|^2, with 1 / |f|^2 from the
+        // hardware reciprocal and two Newton steps (a zero factor gives a zero ratio, which
+        // is never accepted)
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-          const double2 d = PF ? Dc[PF ? q : 0] : row_entry(a.D, m, q);
-          const double2 Tm = PF ? Tc[PF ? q : 0] : row_entry(a.T, m, q);
-          theta(q) = make_double2(th[q].x - 2.0 * sg * d.x, th[q].y - 2.0 * sg * d.y);
-          // t' = (t - sigma T) / f = (t - sigma T) conj(f) / |f|^2, with 1 / |f|^2
-          // from the hardware reciprocal and two Newton steps (|f|^2 > 0 here:
-          // a zero factor gives a zero ratio, which is never accepted)
-          const double2 nu = make_double2(tt[q].x - sg * Tm.x, tt[q].y - sg * Tm.y);
-          double inv = __builtin_amdgcn_rcp(nq[q]);
-          inv = fma(inv, fma(-nq[q], inv, 1.0), inv);
-          inv = fma(inv, fma(-nq[q], inv, 1.0), inv);
-          tt[q] = make_double2((nu.x * fq[q].x + nu.y * fq[q].y) * inv, (nu.y * fq[q].x - nu.x * fq[q].y) * inv);
+          const double2 nu = make_double2(tt[q].x - sg * Tc[q].x, tt[q].y - sg * Tc[q].y);
+          double inv = __builtin_amdgcn_rcp(n[q]);
+          inv = fma(inv, fma(-n[q], inv, 1.0), inv);
+          inv = fma(inv, fma(-n[q], inv, 1.0), inv);
+          tt[q] = make_double2((nu.x * f[q].x + nu.y * f[q].y) * inv, (nu.y * f[q].x - nu.x * f[q].y) * inv);
         }
-        // one wavefront per work-group: LDS operations of the wave stay in
-        // program order, so the flips need no barrier and no returned value
-        if (lane == 0) {
-          __hip_atomic_fetch_xor(&cb[site >> 6], 1ull << (site & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (site2 >= 0)
-            __hip_atomic_fetch_xor(&cb[site2 >> 6], 1ull << (site2 & 63), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+        flip(site);
+        if (exch) flip(site2);
       }
-    }
     }
     // record after every completed sweep of the recording phase
-    if (step >= a.therm_steps && ((step - a.therm_steps + 1) % a.sweep) == 0) {
-      const int64_t k = (step - a.therm_steps + 1) / a.sweep - 1;
-      const int64_t row = k * a.n_chains + c;
+    if (--to_record == 0) {
+      to_record = a.sweep;
       if (wv == 0)
-        for (int w = lane; w < W; w += 64) a.s_out[row * W + w] = cb[w];
-      double2 lp = make_double2(0.0, 0.0);
-      if (wv == 0)
-        for (int i = lane; i < N; i += 64) {
-          const double2 av = a.params[i];
-          const double sgi = ((cb[i >> 6] >> (i & 63)) & 1ull) ? 1.0 : -1.0;
-          lp = cadd(lp, cscale(av, sgi));
-        }
+        if (lane < W) a.s_out[row * W + lane] = (uint64_t)cl | ((uint64_t)ch << 32);
+      if constexpr (TRACK) {
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const int j = jb + lane + 64 * q;
-        if (j < Nh) {
-          const double2 thv = theta(q);
-          lp = cadd(lp, clogcosh(thv));
-          tt[q] = ctanh(thv);
-        }
-      }
-      lp = wave_sum(lp);
-      if constexpr (NW > 1) {  // records are rare: plain barriers around the exchange
-        if (lane == 0) lp_s[wv] = lp;
-        __syncthreads();
-        lp = lp_s[0];
+        for (int q = 0; q < Q; ++q)
+          th[q] = make_double2(fma(-dsg, DP[q].x, th[q].x), fma(-dsg, DP[q].y, th[q].y));
+        dsg = 0.0;
+        double2 lp = tanh_theta(true);
+        if (wv == 0)
+          for (int i = lane; i - lane < N; i += 64) {  // word i / 64 is the same in all lanes
+            const uint32_t lo = (uint32_t)rl((int)cl, (i - lane) >> 6);
+            const uint32_t hi = (uint32_t)rl((int)ch, (i - lane) >> 6);
+            const uint32_t b = ((lane & 32 ? hi : lo) >> (lane & 31)) & 1u;
+            if (i < N) lp = cadd(lp, cscale(a.params[i], b ? 1.0 : -1.0));
+          }
+        lp = wave_sum(lp);
+        if constexpr (NW > 1) {  // records are rare: plain barriers around the exchange
+          if (lane == 0) lp_s[wv] = lp;
+          __syncthreads();
+          lp = lp_s[0];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) lp = cadd(lp, lp_s[w]);
-        __syncthreads();
+          for (int w = 1; w < NW; ++w) lp = cadd(lp, lp_s[w]);
+          __syncthreads();
+        }
+        if (wv == 0 && lane == 0 && a.logpsi_out) a.logpsi_out[row] = lp;
       }
-      if (wv == 0 && lane == 0 && a.logpsi_out) a.logpsi_out[row] = lp;
+      row += a.n_chains;
     }
   }
   }
   if (wv == 0)
-    for (int w = lane; w < W; w += 64) a.bits[(int64_t)c * W + w] = cb[w];
-  if (a.theta_store)
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int j = jb + lane + 64 * q;
-      if (j < Nh) a.theta_store[(int64_t)c * Nh + j] = theta(q);
-    }
+    if (lane < W) a.bits[(int64_t)c * W + lane] = (uint64_t)cl | ((uint64_t)ch << 32);
   if (wv == 0 && lane == 0) a.acc[c] += accepted;
 }
 
@@ -350,35 +370,39 @@ __global__ void k_zero_u64(unsigned long long* p, int64_t n) {
   if (e < n) p[e] = 0ull;
 }
 
-template <int NW>
-void launch_nw(const sampler_args& a, int Q, hipStream_t st) {
-  const dim3 blk(64 * NW);
-  if (Q <= 1)
-    k_metropolis<1, NW><<<a.n_chains, blk, 0, st>>>(a);
-  else if (Q <= 2)
-    k_metropolis<2, NW><<<a.n_chains, blk, 0, st>>>(a);
-  else if (Q <= 4)
-    k_metropolis<4, NW><<<a.n_chains, blk, 0, st>>>(a);
-  else if (Q <= 8)
-    k_metropolis<8, NW><<<a.n_chains, blk, 0, st>>>(a);
-  else if (Q <= 16)
-    k_metropolis<16, NW><<<a.n_chains, blk, 0, st>>>(a);
-  else
-    throw vmc_error{VMC_ERR_UNSUPPORTED, "sampler supports up to 1024 hidden units"};
-  VMC_HIP(hipGetLastError());
-}
-
-// Two waves per chain when the chains leave SIMDs idle (at most one chain per
-// SIMD) and each wave keeps more than two slots of 64 hidden units: measured
-// at 1 024 chains, N_h = 400 (exchanges) 1.38 -> 1.24 ms per 8 sweeps, while
-// at N_h = 256 (flips) the barrier per proposal costs more than the halved
-// per-unit work saves (1.27 -> 1.50 ms per 16 sweeps).
+// Two waves per chain above 512 hidden units (eight slots of 64 fill one wave's
+// registers), and above 128 when the chains leave SIMDs idle (at most one chain
+// per SIMD).  1 024 chains: Heisenberg 10 x 10, N_h = 400, 8 sweeps 0.79 ms with
+// two waves, 0.90 with one, 0.91 with four; flips 8 x 8, N_h = 256, 16 sweeps 0.93,
+// 1.10, 1.17; one slot per lane (N_h = 20, 512 chains) 0.30 with two, 0.22 with one.
+// 4 096 chains: N_h = 400 2.07 with two, 1.0 with one; N_h = 256 0.76, 0.55.
+template <bool TRACK>
 void launch(vmc_ctx* ctx, const sampler_args& a, hipStream_t st) {
-  const bool two = a.n_chains <= 4 * cu_count(ctx) && a.Nh > 256;
-  if (two)
-    launch_nw<2>(a, (a.Nh + 127) / 128, st);
-  else
-    launch_nw<1>(a, (a.Nh + 63) / 64, st);
+  const int nw = a.Nh > 512 || (a.Nh > 128 && a.n_chains <= 4 * cu_count(ctx)) ? 2 : 1;
+  const int q = (a.Nh + 64 * nw - 1) / (64 * nw);
+  const dim3 grid(a.n_chains), blk(64 * nw);
+  switch (nw * 16 + q) {
+#define CASE(Q, NW) \
+  case NW * 16 + Q: k_metropolis<Q, NW, TRACK><<<grid, blk, 0, st>>>(a); break
+    CASE(1, 1);
+    CASE(2, 1);
+    CASE(3, 1);
+    CASE(4, 1);
+    CASE(5, 1);
+    CASE(6, 1);
+    CASE(7, 1);
+    CASE(8, 1);
+    CASE(2, 2);
+    CASE(3, 2);
+    CASE(4, 2);
+    CASE(5, 2);
+    CASE(6, 2);
+    CASE(7, 2);
+    CASE(8, 2);
+#undef CASE
+    default: throw vmc_error{VMC_ERR_UNSUPPORTED, "sampler supports up to 1024 hidden units"};
+  }
+  VMC_HIP(hipGetLastError());
 }
 
 }  // namespace
@@ -418,26 +442,25 @@ void sampler_run(vmc_sampler* S, int64_t n_per_chain, uint64_t* s_out, double2* 
     a.n_record = n_per_chain;
     a.s_out = s_out;
     a.logpsi_out = logpsi_out;
-    launch(S->ctx, a, st);
+    launch<true>(S->ctx, a, st);
     S->t += (uint64_t)(a.therm_steps + a.n_record * a.sweep);
     S->thermalized = 1;
     S->bits_valid = 1;
     return;
   }
   // MADE_MIX: per sweep, global_steps global steps of all chains, then one
-  // launch of the sweep's flips; theta is rebuilt once per call and kept in
-  // S->mix_theta between the launches
+  // launch of the sweep's flips; the chains' theta (S->mix_theta) is formed on the
+  // matrix cores from their spins after every launch
   mix_ensure(S);
-  a.theta_store = S->mix_theta;
   a.t0 = S->t;
   a.init = !S->bits_valid;
-  a.theta_in = 0;
   a.therm_steps = 0;
   a.n_record = 0;
-  launch(S->ctx, a, st);  // initial states (first call) and theta, no proposals
+  if (a.init) launch<false>(S->ctx, a, st);  // initial states (first call), no proposals
+  rbm_theta(m, S->bits, nc, S->mix_theta);
   S->bits_valid = 1;
   a.init = 0;
-  a.theta_in = 1;
+  a.theta = S->mix_theta;
   const int64_t n_therm = S->thermalized ? 0 : S->opts.therm_sweeps;
   for (int64_t sw = 0; sw < n_therm + n_per_chain; ++sw) {
     for (int gs = 0; gs < S->opts.global_steps; ++gs) mix_global_step(S, S->g++);
@@ -446,9 +469,10 @@ void sampler_run(vmc_sampler* S, int64_t n_per_chain, uint64_t* s_out, double2* 
     a.therm_steps = rec ? 0 : a.sweep;
     a.n_record = rec ? 1 : 0;
     a.s_out = rec ? s_out + (sw - n_therm) * (int64_t)nc * m->W : nullptr;
-    a.logpsi_out = (rec && logpsi_out) ? logpsi_out + (sw - n_therm) * (int64_t)nc : nullptr;
-    launch(S->ctx, a, st);
+    launch<false>(S->ctx, a, st);
     S->t += (uint64_t)a.sweep;
+    rbm_theta(m, S->bits, nc, S->mix_theta);
+    if (rec && logpsi_out) rbm_log_psi_theta(m, S->bits, nc, S->mix_theta, logpsi_out + (sw - n_therm) * (int64_t)nc);
   }
   mix_wait_side(S);
   S->thermalized = 1;
