@@ -85,8 +85,34 @@ __global__ __launch_bounds__(256) void k_theta_mfma(const double* __restrict__ b
   }
 }
 
+// theta of a sample's hidden units as the kernels below take it: from memory
+// (k_theta_mfma), or for small calls formed where it is used, which saves the
+// launch and the round trip.
+struct theta_src {
+  const double2* theta;   // [B][N_h], or NULL
+  const double2* params;  // for theta == NULL: parameters and transposed weights [N][N_h]
+  const double2* Wt;
+};
+
+__device__ __forceinline__ double2 theta_at(const theta_src& t, const uint64_t* sn, int64_t n, int N, int Nh, int j) {
+  if (t.theta) return t.theta[n * Nh + j];
+  double2 th = t.params[N + j];
+  for (int i0 = 0; i0 < N; i0 += 64) {
+    const uint64_t w = sn[i0 >> 6];
+    const double2* col = t.Wt + (int64_t)i0 * Nh + j;
+    const int ni = N - i0 < 64 ? N - i0 : 64;
+#pragma unroll 8
+    for (int i = 0; i < ni; ++i) {
+      const double sg = (w >> i) & 1ull ? 1.0 : -1.0;
+      const double2 v = col[(int64_t)i * Nh];
+      th = make_double2(fma(sg, v.x, th.x), fma(sg, v.y, th.y));
+    }
+  }
+  return th;
+}
+
 // log psi(n) = sum_i a_i sigma_i + sum_j logcosh(theta_j); one wave per sample.
-__global__ __launch_bounds__(64) void k_logpsi(const double2* __restrict__ params, const double2* __restrict__ theta,
+__global__ __launch_bounds__(64) void k_logpsi(const double2* __restrict__ params, theta_src theta,
                                                const uint64_t* __restrict__ s, int64_t B, int N, int W, int Nh,
                                                double2* __restrict__ logpsi) {
   const int64_t n = blockIdx.x;
@@ -99,7 +125,7 @@ __global__ __launch_bounds__(64) void k_logpsi(const double2* __restrict__ param
     const double sg = get_bit(sn, i) ? 1.0 : -1.0;
     acc = cadd(acc, cscale(a, sg));
   }
-  for (int j = lane; j < Nh; j += 64) acc = cadd(acc, clogcosh(theta[n * Nh + j]));
+  for (int j = lane; j < Nh; j += 64) acc = cadd(acc, clogcosh(theta_at(theta, sn, n, N, Nh, j)));
   acc = wave_sum(acc);
   if (lane == 0) logpsi[n] = acc;
 }
@@ -150,7 +176,7 @@ __global__ __launch_bounds__(64) void k_tables(const double2* __restrict__ param
 // operands need no bounds, and its rows are addressed from scalar registers: N = 64,
 // N_h = 256, 16 384 samples with theta 237 -> 204 us.
 template <int S>
-__global__ __launch_bounds__(64) void k_eloc(const double2* __restrict__ theta, const uint64_t* __restrict__ s,
+__global__ __launch_bounds__(64) void k_eloc(theta_src theta, const uint64_t* __restrict__ s,
                                              int64_t B, int N, int W, int Nh, int ham_kind, double J, double h,
                                              const int2* __restrict__ bonds, int n_bonds,
                                              const double2* __restrict__ T, const double2* __restrict__ LC,
@@ -163,7 +189,7 @@ __global__ __launch_bounds__(64) void k_eloc(const double2* __restrict__ theta, 
 #pragma unroll
   for (int q = 0; q < S; ++q)
     for (int j = lane; j < Nhp; j += 64)
-      tl[q * Nhp + j] = b0 + q < B && j < Nh ? ctanh(theta[(b0 + q) * Nh + j]) : make_double2(0.0, 0.0);
+      tl[q * Nhp + j] = b0 + q < B && j < Nh ? ctanh(theta_at(theta, s + (b0 + q) * W, b0 + q, N, Nh, j)) : make_double2(0.0, 0.0);
   // diagonal element: coupling * (n_aligned - n_anti), exact integer count
   double diag[S];
 #pragma unroll
@@ -253,7 +279,7 @@ __global__ __launch_bounds__(64) void k_eloc(const double2* __restrict__ theta, 
 // Fused enumeration + evaluation + reduction of E_loc, one wave per sample, for
 // move sets that depend on the sample (exchanges of anti-aligned bonds).
 // LDS: t_j (Nh complex) and the compacted move list (<= n_moves ints).
-__global__ __launch_bounds__(64) void k_eloc_compact(const double2* __restrict__ theta, const uint64_t* __restrict__ s,
+__global__ __launch_bounds__(64) void k_eloc_compact(theta_src theta, const uint64_t* __restrict__ s,
                                              int64_t B, int N, int W, int Nh, int ham_kind, double J, double h,
                                              const int2* __restrict__ bonds, int n_bonds,
                                              const double2* __restrict__ T, const double2* __restrict__ LC,
@@ -270,7 +296,7 @@ __global__ __launch_bounds__(64) void k_eloc_compact(const double2* __restrict__
   const uint64_t* sn = s + n * W;
 
   for (int j = lane; j < Nhp; j += 64) {
-    const double2 tj = j < Nh ? ctanh(theta[n * Nh + j]) : make_double2(0.0, 0.0);
+    const double2 tj = j < Nh ? ctanh(theta_at(theta, sn, n, N, Nh, j)) : make_double2(0.0, 0.0);
     tpm[j] = make_double2(-tj.x, -tj.y);
     tpm[Nhp + j] = tj;
   }
@@ -359,14 +385,14 @@ __global__ __launch_bounds__(64) void k_eloc_compact(const double2* __restrict__
 
 // O_k rows: [sigma (N), t (Nh), t_j sigma_i (Nh x N)]; one block per sample.
 template <typename OutT>
-__global__ __launch_bounds__(256) void k_grad(const double2* __restrict__ theta, const uint64_t* __restrict__ s,
+__global__ __launch_bounds__(256) void k_grad(theta_src theta, const uint64_t* __restrict__ s,
                                               int64_t B, int N, int W, int Nh, int64_t K, OutT* __restrict__ O) {
   extern __shared__ double2 tl[];  // [Nh]
   const int64_t n = blockIdx.x;
   if (n >= B) return;
   const int tid = threadIdx.x;
   const uint64_t* sn = s + n * W;
-  for (int j = tid; j < Nh; j += 256) tl[j] = ctanh(theta[n * Nh + j]);
+  for (int j = tid; j < Nh; j += 256) tl[j] = ctanh(theta_at(theta, sn, n, N, Nh, j));
   __syncthreads();
   OutT* row = O + n * K;
   auto put = [&](int64_t k, double2 v) {
@@ -448,6 +474,21 @@ void rbm_theta(vmc_model* m, const uint64_t* s, int64_t B, double2* theta, hipSt
 }
 
 namespace {
+// where the kernels take theta of B samples at s from: `buf`, filled here, or for
+// small calls their own loop.  That loop reads N rows of W per 64 units in batches of
+// eight and B N N_h entries in all, against a launch and theta's round trip (3 to 5 us):
+// the line is where either would cost about as much (64 rows; 2^22 entries, 64 MB from
+// the caches; 8 192 samples).  Log psi, local energies and O_k, 1 024 samples: N = N_h =
+// 10 31.9 -> 20.9 us, N = N_h = 64 60.5 -> 39.6 us, N = 30, N_h = 120 53.3 -> 42.7 us;
+// 16 384 samples of N = N_h = 6 would gain 2 us in each of the first two and lose 3 in
+// the last.
+theta_src take_theta(vmc_model* m, const uint64_t* s, int64_t B, double2* buf) {
+  if ((int64_t)m->N * ((m->Nh + 63) / 64) <= 64 && B <= 8192 && B * m->N * m->Nh <= (int64_t)1 << 22)
+    return {nullptr, m->params, m->Wt};
+  rbm_theta(m, s, B, buf);
+  return {buf, nullptr, nullptr};
+}
+
 // [rows][cols] -> [cols][rows] for two tables at once (sampler layout)
 __global__ void k_transpose2(const double2* __restrict__ A, const double2* __restrict__ B, int rows, int cols,
                              double2* __restrict__ At, double2* __restrict__ Bt) {
@@ -495,7 +536,8 @@ void rbm_ensure_tables(vmc_model* m, const vmc_ham* H, int move_kind) {
 
 // log psi from theta of the same configurations
 void rbm_log_psi_theta(vmc_model* m, const uint64_t* s, int64_t B, const double2* theta, double2* logpsi) {
-  k_logpsi<<<(unsigned)B, 64, 0, m->ctx->stream>>>(m->params, theta, s, B, m->N, m->W, m->Nh, logpsi);
+  k_logpsi<<<(unsigned)B, 64, 0, m->ctx->stream>>>(m->params, theta_src{theta, nullptr, nullptr}, s, B, m->N, m->W,
+                                                  m->Nh, logpsi);
   VMC_HIP(hipGetLastError());
 }
 
@@ -506,8 +548,9 @@ void rbm_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
   double2* theta = (double2*)ws_take(ctx, sizeof(double2) * chunk * m->Nh);
   for (int64_t b0 = 0; b0 < B; b0 += chunk) {
     const int64_t nb = std::min(chunk, B - b0);
-    rbm_theta(m, s + b0 * m->W, nb, theta);
-    rbm_log_psi_theta(m, s + b0 * m->W, nb, theta, logpsi + b0);
+    const theta_src th = take_theta(m, s + b0 * m->W, nb, theta);
+    k_logpsi<<<(unsigned)nb, 64, 0, ctx->stream>>>(m->params, th, s + b0 * m->W, nb, m->N, m->W, m->Nh, logpsi + b0);
+    VMC_HIP(hipGetLastError());
   }
 }
 
@@ -533,9 +576,9 @@ void rbm_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, do
   VMC_REQUIRE((int64_t)Nhp * std::max(1, tb.n_moves) < ((int64_t)1 << 31), "move table too large");
   for (int64_t b0 = 0; b0 < B; b0 += chunk) {
     const int64_t nb = std::min(chunk, B - b0);
-    rbm_theta(m, s + b0 * m->W, nb, theta);
+    const theta_src th = take_theta(m, s + b0 * m->W, nb, theta);
     if (move_kind == 1) {
-      k_eloc_compact<<<(unsigned)nb, 64, lds1, ctx->stream>>>(theta, s + b0 * m->W, nb, m->N, m->W, m->Nh, H->kind,
+      k_eloc_compact<<<(unsigned)nb, 64, lds1, ctx->stream>>>(th, s + b0 * m->W, nb, m->N, m->W, m->Nh, H->kind,
                                                               H->J, H->h, H->bonds, H->n_bonds, tb.T, tb.LC, tb.alpha,
                                                               tb.n_moves, Nhp, eloc + b0);
       VMC_HIP(hipGetLastError());
@@ -543,7 +586,7 @@ void rbm_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, do
     }
     const unsigned grid = (unsigned)((nb + S - 1) / S);
 #define ELOC_LAUNCH(SS)                                                                                             \
-  k_eloc<SS><<<grid, 64, lds, ctx->stream>>>(theta, s + b0 * m->W, nb, m->N, m->W, m->Nh, H->kind, H->J, H->h,     \
+  k_eloc<SS><<<grid, 64, lds, ctx->stream>>>(th, s + b0 * m->W, nb, m->N, m->W, m->Nh, H->kind, H->J, H->h,     \
                                              H->bonds, H->n_bonds, tb.T, tb.LC, tb.alpha, tb.n_moves, Nhp, eloc + b0)
     if (S == 4)
       ELOC_LAUNCH(4);
@@ -562,14 +605,14 @@ void rbm_grad(vmc_model* m, const uint64_t* s, int64_t B, void* O, int dtype) {
   const size_t esz = dtype == VMC_DT_C128 ? sizeof(double2) : sizeof(float2);
   for (int64_t b0 = 0; b0 < B; b0 += chunk) {
     const int64_t nb = std::min(chunk, B - b0);
-    rbm_theta(m, s + b0 * m->W, nb, theta);
+    const theta_src th = take_theta(m, s + b0 * m->W, nb, theta);
     void* out = (char*)O + (size_t)b0 * m->K * esz;
     if (dtype == VMC_DT_C128)
       k_grad<double2><<<(unsigned)nb, 256, sizeof(double2) * m->Nh, ctx->stream>>>(
-          theta, s + b0 * m->W, nb, m->N, m->W, m->Nh, m->K, (double2*)out);
+          th, s + b0 * m->W, nb, m->N, m->W, m->Nh, m->K, (double2*)out);
     else
       k_grad<float2><<<(unsigned)nb, 256, sizeof(double2) * m->Nh, ctx->stream>>>(
-          theta, s + b0 * m->W, nb, m->N, m->W, m->Nh, m->K, (float2*)out);
+          th, s + b0 * m->W, nb, m->N, m->W, m->Nh, m->K, (float2*)out);
     VMC_HIP(hipGetLastError());
   }
 }
