@@ -16,8 +16,8 @@
 // With K even and Obar 16-byte aligned (k_herk_c_dma) the samples are loaded
 // 12 at a time straight from global memory into double-buffered LDS
 // (global_load_lds_dwordx4, no staging registers), three groups per compute
-// unit; otherwise (k_herk_mfma_f32) 16 at a time through registers into
-// double-buffered LDS, two groups per compute unit.  Only tiles
+// unit; otherwise (k_herk_mfma_f32) 16 (real mode 8) at a time through registers
+// into double-buffered LDS, two (four) groups per compute unit.  Only tiles
 // that touch the lower triangle are launched; the linear tile index is
 // remapped so that consecutive tiles of one row stripe run on the same XCD
 // (shared L2).  The epilogue writes S~ (float64, projection and diagonal shift
@@ -30,7 +30,11 @@
 // registers that frees it takes square
 // 128 x 128 tiles (each wave 64 x 64), so the matrix-core work per staged sample
 // and per barrier stays that of the complex tile and the operand traffic per
-// flop halves.  When the tiles alone cannot fill the chip (small K, many
+// flop halves.  Bound: the matrix cores, 78 % of the cycles, four groups of 128
+// registers per compute unit (3e5 real samples, K = 1 529: 9.0 -> 6.4 ms; before, the
+// lane addresses of every load were formed anew, leaving two groups, each product
+// waited for the one before it on the same accumulator, and the splits were spread
+// over all XCDs).  When the tiles alone cannot fill the chip (small K, many
 // samples) the sample range is split over blockIdx.y; each split stores its
 // float32 accumulators in register order and a second kernel adds the splits in
 // float64 (fixed order, so the result is reproducible) before the epilogue.
@@ -43,7 +47,7 @@ namespace {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 128;  // complex rows per tile
-constexpr int BK = 16;   // samples per LDS stage
+constexpr int BK = 16;   // samples per LDS stage (complex mode), unit of the sample splits
 constexpr int PAD = 2;   // float2 padding per LDS row
 
 // complex mode: 128 x 64 tiles, three accumulators; real mode: 128 x 128, one
@@ -52,6 +56,7 @@ struct herk_shape {
   static constexpr int BN = REAL ? 128 : 64;  // columns per tile
   static constexpr int JN = REAL ? 4 : 2;     // 16-column blocks per wave
   static constexpr int QN = REAL ? 1 : 3;     // accumulators per block
+  static constexpr int SK = REAL ? 8 : BK;    // samples per LDS stage
   static constexpr int ACC = 4 * JN * QN * 4; // accumulator values per thread
 };
 
@@ -72,6 +77,18 @@ __device__ __forceinline__ int64_t remap_tile(int64_t bid, int64_t nb) {
   // XCD-aware remap: hardware places block i on XCD i % 8
   const int64_t per = (nb + 7) / 8;
   return (bid % 8) * per + bid / 8;
+}
+
+// this group's tile and sample split: all tiles of a split follow one another, so that
+// those that run on one XCD read the same samples at about the same time (3e5 real
+// samples, K = 1 529, 13 splits: with every XCD at all splits four of five reads missed
+// its L2)
+__device__ __forceinline__ bool tile_and_split(const herk_args& a, int64_t& lin, int& split) {
+  const int64_t id = remap_tile(blockIdx.x, a.n_tiles * a.ksplit);
+  if (id >= a.n_tiles * a.ksplit) return false;
+  split = (int)(id / a.n_tiles);
+  lin = id - split * a.n_tiles;
+  return true;
 }
 
 // lower-triangle tile (tr, tc) of linear index b: complex mode has 2 t + 2 column
@@ -97,14 +114,14 @@ __device__ __forceinline__ int acc_index(int i, int j, int q, int r, int JN, int
   return ((i * JN + j) * QN + q) * 4 + r;
 }
 
-// writes one lane's values of the 16 x 16 blocks; get(i, j, q, r) returns accumulator q
-template <bool REAL, typename Get>
+// writes one lane's values of IN 16 x 16 row blocks; get(i, j, q, r) returns accumulator q
+template <bool REAL, int IN = 4, typename Get>
 __device__ __forceinline__ void herk_epilogue(const herk_args& a, int64_t row0, int64_t col0, int wr, int wc, int li,
                                               int lk, Get get) {
   using sh = herk_shape<REAL>;
   const int64_t K = a.K;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < IN; ++i)
 #pragma unroll
     for (int j = 0; j < sh::JN; ++j)
 #pragma unroll
@@ -136,17 +153,16 @@ template <bool REAL>
 __global__ __launch_bounds__(256, 2) void k_herk_mfma_f32(herk_args a) {
   using sh = herk_shape<REAL>;
   constexpr int BN = sh::BN, JN = sh::JN, QN = sh::QN;
-  constexpr int NA = BK * BM / 256, NB = BK * BN / 256;  // float2 per thread per stage
-  // complex mode: two LDS stages (one barrier per stage); real mode: one stage
-  // (two barriers per stage) so that its square tiles leave room for four
-  // resident groups per compute unit
-  constexpr int NBUF = REAL ? 1 : 2;
-  __shared__ float2 As[NBUF][BK][BM + PAD];
-  __shared__ float2 Bs[NBUF][BK][BN + PAD];
+  constexpr int SK = sh::SK;
+  constexpr int NA = SK * BM / 256, NB = SK * BN / 256;  // float2 per thread per stage
+  // two LDS stages, one barrier per stage; the real mode's are half as deep, so that
+  // its square tiles leave room for four resident groups per compute unit
+  __shared__ float2 As[2][SK][BM + PAD];
+  __shared__ float2 Bs[2][SK][BN + PAD];
 
-  const int64_t nb = a.n_tiles;
-  const int64_t lin = remap_tile(blockIdx.x, nb);
-  if (lin >= nb) return;
+  int64_t lin;
+  int split;
+  if (!tile_and_split(a, lin, split)) return;
   int tr, tc;
   tile_of<REAL>(lin, tr, tc);
   const int64_t row0 = (int64_t)tr * BM, col0 = (int64_t)tc * BN;
@@ -164,29 +180,26 @@ __global__ __launch_bounds__(256, 2) void k_herk_mfma_f32(herk_args a) {
 #pragma unroll
       for (int q = 0; q < QN; ++q) acc[i][j][q] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // global -> register staging of one stage: A BK x BM, B BK x BN float2.
-  // Out-of-range elements load X[0] (always valid) and are replaced by zero,
-  // so the loads need no branches.
+  // global -> register staging of one stage: A SK x BM, B SK x BN float2, by buffer
+  // loads from the stage's first row: samples past the last read zero (out of the
+  // buffer's range), columns past K read the next row and feed only outputs that are
+  // never written.  Lane addresses are the same in every stage.
   float2 ra[NA], rb[NB];
+  const int va = (tid / BM * (int)K + tid % BM) * 8, vb = (tid / BN * (int)K + tid % BN) * 8;
   auto gload = [&](int64_t n0) {
+    const int64_t left = max((int64_t)0, (N - n0) * K);  // entries from sample n0 on
+    auto range = [&](int64_t c0) {
+      return __builtin_amdgcn_make_buffer_rsrc((void*)(a.X + n0 * K + c0), 0,
+                                               (int)(uint32_t)min(max((int64_t)0, left - c0) * 8, (int64_t)0xfffffff8),
+                                               0x00027000);
+    };
+    const auto sa = range(row0), sb = range(col0);
 #pragma unroll
-    for (int r = 0; r < NA; ++r) {
-      const int q = tid + 256 * r;
-      const int nn = q / BM, cc = q % BM;
-      const int64_t n = n0 + nn, c = row0 + cc;
-      const bool ok = n < N && c < K;
-      const float2 v = a.X[ok ? n * K + c : 0];
-      ra[r] = ok ? v : make_float2(0.f, 0.f);
-    }
+    for (int r = 0; r < NA; ++r)
+      ra[r] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(sa, va, r * (256 / BM) * (int)K * 8, 0));
 #pragma unroll
-    for (int r = 0; r < NB; ++r) {
-      const int q = tid + 256 * r;
-      const int nn = q / BN, cc = q % BN;
-      const int64_t n = n0 + nn, c = col0 + cc;
-      const bool ok = n < N && c < K;
-      const float2 v = a.X[ok ? n * K + c : 0];
-      rb[r] = ok ? v : make_float2(0.f, 0.f);
-    }
+    for (int r = 0; r < NB; ++r)
+      rb[r] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(sb, vb, r * (256 / BN) * (int)K * 8, 0));
   };
   auto sstore = [&](int buf) {
 #pragma unroll
@@ -203,15 +216,18 @@ __global__ __launch_bounds__(256, 2) void k_herk_mfma_f32(herk_args a) {
 
   const int64_t n_stages = (N + BK - 1) / BK;
   const int64_t sp = (n_stages + a.ksplit - 1) / a.ksplit;
-  const int64_t st0 = blockIdx.y * sp, st1 = min(n_stages, st0 + sp);
+  const int64_t s0 = min(N, split * sp * BK), s1 = min(N, (split + 1) * sp * BK);
+  const int st1 = (int)((s1 - s0 + SK - 1) / SK);
   const int li = lane & 15, lk = lane >> 4;
-  if (st0 < st1) {  // uniform over the group
-    gload(st0 * BK);
+  // a wave whose blocks all lie above the diagonal has no products to form
+  const bool idle = REAL && tr == tc && wr < wc;
+  if (st1 > 0) {  // uniform over the group
+    gload(s0);
     sstore(0);
     __syncthreads();
-    for (int64_t st = st0; st < st1; ++st) {
-      const int buf = NBUF == 2 ? (int)((st - st0) & 1) : 0;
-      if (st + 1 < st1) gload((st + 1) * BK);
+    for (int st = 0; st < st1; ++st) {
+      const int buf = st & 1;
+      if (st + 1 < st1) gload(s0 + (int64_t)(st + 1) * SK);
       // MFMA fragments double-buffered in registers: the LDS reads of step
       // ks + 1 are issued before the matrix-core work of step ks
       float2 fr[2][4], fc[2][JN];
@@ -222,53 +238,51 @@ __global__ __launch_bounds__(256, 2) void k_herk_mfma_f32(herk_args a) {
 #pragma unroll
         for (int j = 0; j < JN; ++j) fc[p][j] = Bs[buf][n][wc * (16 * JN) + j * 16 + li];
       };
-      fload(0, 0);
+      if (!idle) {
+        fload(0, 0);
 #pragma unroll
-      for (int ks = 0; ks < BK / 4; ++ks) {
-        const int p = ks & 1;
-        if (ks + 1 < BK / 4) fload(p ^ 1, ks + 1);
-        __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the products
-        const float2* fa = fr[p];
-        const float2* fb = fc[p];
-        if constexpr (REAL) {
+        for (int ks = 0; ks < SK / 4; ++ks) {
+          const int p = ks & 1;
+          if (ks + 1 < SK / 4) fload(p ^ 1, ks + 1);
+          __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the products
+          const float2* fa = fr[p];
+          const float2* fb = fc[p];
+          if constexpr (REAL) {
+            // all first products, then all second ones: no product waits for its own block's
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < JN; ++j) {
-              acc[i][j][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].x, fb[j].x, acc[i][j][0], 0, 0, 0);
-              acc[i][j][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].y, fb[j].y, acc[i][j][0], 0, 0, 0);
-            }
-        } else {
-          float da[4], sb[JN];
+              for (int j = 0; j < JN; ++j)
+                acc[i][j][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].x, fb[j].x, acc[i][j][0], 0, 0, 0);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) da[i] = fa[i].x - fa[i].y;
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int j = 0; j < JN; ++j) sb[j] = fb[j].x + fb[j].y;
+              for (int j = 0; j < JN; ++j)
+                acc[i][j][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].y, fb[j].y, acc[i][j][0], 0, 0, 0);
+          } else {
+            float da[4], sb[JN];
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4; ++i) da[i] = fa[i].x - fa[i].y;
 #pragma unroll
-            for (int j = 0; j < JN; ++j) {
-              acc[i][j][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].x, fb[j].x, acc[i][j][0], 0, 0, 0);
-              acc[i][j][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].y, fb[j].y, acc[i][j][1], 0, 0, 0);
-              acc[i][j][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(da[i], sb[j], acc[i][j][2], 0, 0, 0);
-            }
+            for (int j = 0; j < JN; ++j) sb[j] = fb[j].x + fb[j].y;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+              for (int j = 0; j < JN; ++j) {
+                acc[i][j][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].x, fb[j].x, acc[i][j][0], 0, 0, 0);
+                acc[i][j][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].y, fb[j].y, acc[i][j][1], 0, 0, 0);
+                acc[i][j][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(da[i], sb[j], acc[i][j][2], 0, 0, 0);
+              }
+          }
         }
       }
-      if constexpr (NBUF == 2) {
-        if (st + 1 < st1) sstore(buf ^ 1);
-        __syncthreads();
-      } else {
-        __syncthreads();  // every wave is done with the stage
-        if (st + 1 < st1) {
-          sstore(0);
-          __syncthreads();
-        }
-      }
+      if (st + 1 < st1) sstore(buf ^ 1);
+      __syncthreads();
     }
   }
 
   if (a.ksplit > 1) {  // partial accumulators in register order, coalesced over threads
-    float* dst = a.part + ((int64_t)blockIdx.y * nb + lin) * (sh::ACC * 256) + tid;
+    float* dst = a.part + ((int64_t)split * a.n_tiles + lin) * (sh::ACC * 256) + tid;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -370,9 +384,9 @@ __global__ __launch_bounds__(256, OCC) void k_herk_c_dma(herk_args a) {
   __shared__ float2 As[2][SD * BM];
   __shared__ float2 Bs[2][SD * BN];
 
-  const int64_t nb = a.n_tiles;
-  const int64_t lin = remap_tile(blockIdx.x, nb);
-  if (lin >= nb) return;
+  int64_t lin;
+  int split;
+  if (!tile_and_split(a, lin, split)) return;
   int tr, tc;
   tile_of<false>(lin, tr, tc);
   const int64_t row0 = (int64_t)tr * BM, col0 = (int64_t)tc * BN;
@@ -395,7 +409,7 @@ __global__ __launch_bounds__(256, OCC) void k_herk_c_dma(herk_args a) {
   // of BK samples), walked in stages of SD samples
   const int64_t n_stages = (N + BK - 1) / BK;
   const int64_t sp = (n_stages + a.ksplit - 1) / a.ksplit;
-  const int64_t s0 = min(N, blockIdx.y * sp * BK), s1 = min(N, (blockIdx.y + 1) * sp * BK);
+  const int64_t s0 = min(N, split * sp * BK), s1 = min(N, (split + 1) * sp * BK);
   const int64_t st0 = 0, st1 = (s1 - s0 + SD - 1) / SD;
   if (st0 < st1) {  // uniform over the group
     // first stage into buffer 0 (loads only)
@@ -414,7 +428,7 @@ __global__ __launch_bounds__(256, OCC) void k_herk_c_dma(herk_args a) {
   }
 
   if (a.ksplit > 1) {
-    float* dst = a.part + ((int64_t)blockIdx.y * nb + lin) * (sh::ACC * 256) + tid;
+    float* dst = a.part + ((int64_t)split * a.n_tiles + lin) * (sh::ACC * 256) + tid;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -429,7 +443,9 @@ __global__ __launch_bounds__(256, OCC) void k_herk_c_dma(herk_args a) {
                        [&](int i, int j, int q, int r) { return (double)acc[i][j][q][r]; });
 }
 
-// adds the split partial accumulators (float64, split order) and writes S~
+// adds the split partial accumulators (float64, split order) and writes S~; one group
+// per 16-row stripe of each wave's blocks (13 splits of 78 tiles, K = 1 529: 333 us with
+// one group per tile, 42 with four)
 template <bool REAL>
 __global__ __launch_bounds__(256) void k_herk_reduce(herk_args a) {
   using sh = herk_shape<REAL>;
@@ -443,22 +459,25 @@ __global__ __launch_bounds__(256) void k_herk_reduce(herk_args a) {
   if (col0 >= a.K) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1;
-  double acc[4][JN][QN][4];
+  const int i0 = blockIdx.y;
+  double acc[JN][QN][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int j = 0; j < JN; ++j)
+#pragma unroll
+    for (int q = 0; q < QN; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[j][q][r] = 0.0;
+  for (int sp = 0; sp < a.ksplit; ++sp) {
+    const float* src = a.part + ((int64_t)sp * nb + lin) * (sh::ACC * 256) + tid;
 #pragma unroll
     for (int j = 0; j < JN; ++j)
 #pragma unroll
       for (int q = 0; q < QN; ++q)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          double s = 0.0;
-          for (int sp = 0; sp < a.ksplit; ++sp)
-            s += (double)a.part[((int64_t)sp * nb + lin) * (sh::ACC * 256) + acc_index(i, j, q, r, JN, QN) * 256 + tid];
-          acc[i][j][q][r] = s;
-        }
-  herk_epilogue<REAL>(a, row0, col0, wr, wc, lane & 15, lane >> 4,
-                      [&](int i, int j, int q, int r) { return acc[i][j][q][r]; });
+        for (int r = 0; r < 4; ++r) acc[j][q][r] += (double)src[acc_index(i0, j, q, r, JN, QN) * 256];
+  }
+  herk_epilogue<REAL, 1>(a, row0 + 16 * i0, col0, wr, wc, lane & 15, lane >> 4,
+                         [&](int, int j, int q, int r) { return acc[j][q][r]; });
 }
 
 int64_t herk_tiles(int64_t K, bool real) {
@@ -504,7 +523,7 @@ void herk_mfma_f32(vmc_ctx* ctx, const float2* X, int64_t N, int64_t K, int mode
   a.part = (float*)ws;
   if (a.ksplit > 1 && !ws) throw vmc_error{VMC_ERR_WORKSPACE, "internal: split Gram without workspace"};
   const int64_t grid = ((a.n_tiles + 7) / 8) * 8;
-  const dim3 g((unsigned)grid, (unsigned)a.ksplit);
+  const unsigned g = (unsigned)(((a.n_tiles * a.ksplit + 7) / 8) * 8);
   if (real)
     k_herk_mfma_f32<true><<<g, 256, 0, ctx->stream>>>(a);
   else if (K % 2 == 0 && (uintptr_t)X % 16 == 0)
@@ -514,9 +533,9 @@ void herk_mfma_f32(vmc_ctx* ctx, const float2* X, int64_t N, int64_t K, int mode
   VMC_HIP(hipGetLastError());
   if (a.ksplit > 1) {
     if (real)
-      k_herk_reduce<true><<<(unsigned)grid, 256, 0, ctx->stream>>>(a);
+      k_herk_reduce<true><<<dim3((unsigned)grid, 4), 256, 0, ctx->stream>>>(a);
     else
-      k_herk_reduce<false><<<(unsigned)grid, 256, 0, ctx->stream>>>(a);
+      k_herk_reduce<false><<<dim3((unsigned)grid, 4), 256, 0, ctx->stream>>>(a);
     VMC_HIP(hipGetLastError());
   }
 }
