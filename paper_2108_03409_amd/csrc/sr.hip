@@ -40,12 +40,27 @@ __global__ __launch_bounds__(1024) void k_energy_stats(const double2* __restrict
   __shared__ double red[3][16];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   double sw = 0, sr = 0, si = 0;
-  for (int64_t n = tid; n < N; n += 1024) {
-    const double wn = w ? w[n] : 1.0;
+  // eight loads in flight, added in the order of n
+  auto each = [&](auto f) {
+    int64_t n = tid;
+    for (; n + 7 * 1024 < N; n += 8 * 1024) {
+      double2 v[8];
+      double wn[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        v[u] = e[n + 1024 * u];
+        wn[u] = w ? w[n + 1024 * u] : 1.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) f(wn[u], v[u]);
+    }
+    for (; n < N; n += 1024) f(w ? w[n] : 1.0, e[n]);
+  };
+  each([&](double wn, double2 v) {
     sw += wn;
-    sr += wn * e[n].x;
-    si += wn * e[n].y;
-  }
+    sr += wn * v.x;
+    si += wn * v.y;
+  });
   sw = wave_sum(sw);
   sr = wave_sum(sr);
   si = wave_sum(si);
@@ -70,11 +85,10 @@ __global__ __launch_bounds__(1024) void k_energy_stats(const double2* __restrict
   __syncthreads();
   const double wsum = tot[0], mr = tot[1], mi = tot[2];
   double sv = 0;
-  for (int64_t n = tid; n < N; n += 1024) {
-    const double wn = w ? w[n] : 1.0;
-    const double dr = e[n].x - mr, di = e[n].y - mi;
+  each([&](double wn, double2 v) {
+    const double dr = v.x - mr, di = v.y - mi;
     sv += wn * (dr * dr + di * di);
-  }
+  });
   sv = wave_sum(sv);
   __syncthreads();
   if (lane == 0) red[0][wv] = sv;
@@ -97,12 +111,20 @@ __global__ __launch_bounds__(256) void k_col_partial(const InT* __restrict__ O, 
   if (k >= K) return;
   const int64_t n0 = (int64_t)blockIdx.y * kColChunk, n1 = min(N, n0 + kColChunk);
   double2 acc = make_double2(0.0, 0.0);
-  for (int64_t n = n0; n < n1; ++n) {
-    const double wn = w ? w[n] : 1.0;
-    const double2 v = load_c(O, n * K + k);
+  auto add = [&](double wn, double2 v) {
     acc.x += wn * v.x;
     acc.y += wn * v.y;
+  };
+  // bound by the read of O: sixteen rows in flight (3e5 x 1 529 float32 548 -> 359 us)
+  int64_t n = n0;
+  for (; n + 16 <= n1; n += 16) {
+    double2 v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = load_c(O, (n + u) * K + k);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) add(w ? w[n + u] : 1.0, v[u]);
   }
+  for (; n < n1; ++n) add(w ? w[n] : 1.0, load_c(O, n * K + k));
   partial[(int64_t)blockIdx.y * K + k] = acc;
 }
 
@@ -130,6 +152,28 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduce_cols(const double2* _
   }
 }
 
+// What the chunk's samples bring to the two kernels below: w_n / wsum, its square root
+// and E_n - Ebar, formed once per group (one sample per thread) instead of a division
+// and a square root per entry of O.
+struct sample_terms {
+  double wn[kColChunk], sq[kColChunk];
+  double2 de[kColChunk];
+  __device__ void fill(const double* __restrict__ w, const double2* __restrict__ e, const double* __restrict__ stats,
+                       int64_t n0, int64_t n1) {
+    const int t = threadIdx.x;
+    if (n0 + t < n1) {
+      const double v = (w ? w[n0 + t] : 1.0) / stats[0];
+      wn[t] = v;
+      sq[t] = sqrt(v);
+      de[t] = csub(e[n0 + t], make_double2(stats[1], stats[2]));
+    }
+    __syncthreads();
+  }
+};
+static_assert(kColChunk == 256, "one sample per thread of the centring kernels");
+
+// Bound of both: one read of O and one write of Xc, eight samples in flight (3e5 x
+// 1 529 float32 978 -> 854 us, 4.81 TB/s being a large copy's rate).
 // Xc[n][k] = sqrt(w_n / wsum) (O_nk - mean_k); Fpartial[chunk][k] = sum w_n conj(O_nk - mean_k) (E_n - Ebar)
 template <typename InT, typename XT>
 __global__ __launch_bounds__(256) void k_center_force(const InT* __restrict__ O, const double* __restrict__ w,
@@ -137,26 +181,34 @@ __global__ __launch_bounds__(256) void k_center_force(const InT* __restrict__ O,
                                                       const double2* __restrict__ mean,
                                                       const double* __restrict__ stats, XT* __restrict__ Xc,
                                                       double2* __restrict__ Fpartial) {
+  __shared__ sample_terms t;
   const int64_t k = blockIdx.x * 256ll + threadIdx.x;
-  if (k >= K) return;
   const int64_t n0 = (int64_t)blockIdx.y * kColChunk, n1 = min(N, n0 + kColChunk);
-  const double wsum = stats[0];
-  const double2 eb = make_double2(stats[1], stats[2]);
+  t.fill(w, e, stats, n0, n1);
+  if (k >= K) return;
   const double2 mk = mean[k];
   double2 acc = make_double2(0.0, 0.0);
-  for (int64_t n = n0; n < n1; ++n) {
-    const double wn = (w ? w[n] : 1.0) / wsum;
-    const double2 d = csub(load_c(O, n * K + k), mk);
-    const double sq = sqrt(wn);
+  auto put = [&](int64_t n, double2 v) {
+    const int u = (int)(n - n0);
+    const double2 d = csub(v, mk);
+    const double sq = t.sq[u];
     if constexpr (sizeof(XT) == sizeof(double2))
       Xc[n * K + k] = make_double2(sq * d.x, sq * d.y);
     else
       Xc[n * K + k] = make_float2((float)(sq * d.x), (float)(sq * d.y));
-    const double2 de = csub(e[n], eb);
-    const double2 p = cmul(cconj(d), de);
-    acc.x += wn * p.x;
-    acc.y += wn * p.y;
+    const double2 p = cmul(cconj(d), t.de[u]);
+    acc.x += t.wn[u] * p.x;
+    acc.y += t.wn[u] * p.y;
+  };
+  int64_t n = n0;
+  for (; n + 8 <= n1; n += 8) {
+    double2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = load_c(O, (n + u) * K + k);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) put(n + u, v[u]);
   }
+  for (; n < n1; ++n) put(n, load_c(O, n * K + k));
   Fpartial[(int64_t)blockIdx.y * K + k] = acc;
 }
 
@@ -170,29 +222,38 @@ __global__ __launch_bounds__(256) void k_center_force_pair(const InT* __restrict
                                                            const double2* __restrict__ mean,
                                                            const double* __restrict__ stats, XT* __restrict__ Xc,
                                                            double2* __restrict__ Fpartial) {
+  __shared__ sample_terms t;
   const int64_t k = blockIdx.x * 256ll + threadIdx.x;
-  if (k >= K) return;
   const int64_t n0 = (int64_t)blockIdx.y * kColChunk, n1 = min(N, n0 + kColChunk);  // n0 even
-  const double wsum = stats[0];
-  const double2 eb = make_double2(stats[1], stats[2]);
+  t.fill(w, e, stats, n0, n1);
+  if (k >= K) return;
   const double mk = mean[k].x;
   double2 acc = make_double2(0.0, 0.0);
-  for (int64_t n = n0; n < n1; n += 2) {
-    double v[2] = {0.0, 0.0};
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if (n + h >= N) break;
-      const double wn = (w ? w[n + h] : 1.0) / wsum;
-      const double d = (double)O[(n + h) * K + k] - mk;
-      v[h] = sqrt(wn) * d;
-      const double2 de = csub(e[n + h], eb);
-      acc.x += wn * d * de.x;
-      acc.y += wn * d * de.y;
-    }
+  auto put = [&](int64_t n, double o) {  // the sample's centred entry
+    const int u = (int)(n - n0);
+    const double d = o - mk;
+    acc.x += t.wn[u] * d * t.de[u].x;
+    acc.y += t.wn[u] * d * t.de[u].y;
+    return t.sq[u] * d;
+  };
+  auto put2 = [&](int64_t n, double o0, double o1, bool two) {
+    const double v0 = put(n, o0), v1 = two ? put(n + 1, o1) : 0.0;
     if constexpr (std::is_same<XT, double2>::value)
-      Xc[(n >> 1) * K + k] = make_double2(v[0], v[1]);
+      Xc[(n >> 1) * K + k] = make_double2(v0, v1);
     else
-      Xc[(n >> 1) * K + k] = make_float2((float)v[0], (float)v[1]);
+      Xc[(n >> 1) * K + k] = make_float2((float)v0, (float)v1);
+  };
+  int64_t n = n0;
+  for (; n + 8 <= n1; n += 8) {
+    InT v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = O[(n + u) * K + k];
+#pragma unroll
+    for (int u = 0; u < 8; u += 2) put2(n + u, (double)v[u], (double)v[u + 1], true);
+  }
+  for (; n < n1; n += 2) {
+    const bool two = n + 1 < n1;
+    put2(n, (double)O[n * K + k], two ? (double)O[(n + 1) * K + k] : 0.0, two);
   }
   Fpartial[(int64_t)blockIdx.y * K + k] = acc;
 }
@@ -723,7 +784,18 @@ void sr_solve_impl(vmc_ctx* ctx, const void* O, int dtype, const double2* eloc, 
   double2* Hm = use_snr ? (double2*)ws_take(ctx, kk) : nullptr;
 
   std::unique_ptr<phase_scope> ph(new phase_scope(ctx, "sr.center"));
-  k_energy_stats<<<1, 1024, 0, st>>>(eloc, w, N, stats);
+  // one group sums the energies (fixed order); with many samples beside the column sums,
+  // on the second stream (N = 3e5: 0.24 ms on its own with one load in flight)
+  const bool beside = N >= 1 << 15;
+  if (beside) {
+    hipStream_t aux = aux_stream(ctx);
+    VMC_HIP(hipEventRecord(ctx->ev_main, st));
+    VMC_HIP(hipStreamWaitEvent(aux, ctx->ev_main, 0));
+    k_energy_stats<<<1, 1024, 0, aux>>>(eloc, w, N, stats);
+    VMC_HIP(hipEventRecord(ctx->ev_aux, aux));
+  } else {
+    k_energy_stats<<<1, 1024, 0, st>>>(eloc, w, N, stats);
+  }
   dim3 cg(grid_for(K, 256), nchunk);
   if (dtype == VMC_DT_C64)
     k_col_partial<float2><<<cg, 256, 0, st>>>((const float2*)O, w, N, K, partial);
@@ -733,6 +805,7 @@ void sr_solve_impl(vmc_ctx* ctx, const void* O, int dtype, const double2* eloc, 
     k_col_partial<float><<<cg, 256, 0, st>>>((const float*)O, w, N, K, partial);
   else
     k_col_partial<double><<<cg, 256, 0, st>>>((const double*)O, w, N, K, partial);
+  if (beside) VMC_HIP(hipStreamWaitEvent(st, ctx->ev_aux, 0));
   k_reduce_cols<<<(unsigned)((K + 63) / 64), 64 * kRedWaves, 0, st>>>(partial, nchunk, K, stats, mean);
   if (dtype == VMC_DT_C64)
     k_center_force<float2, float2><<<cg, 256, 0, st>>>((const float2*)O, w, eloc, N, K, mean, stats, (float2*)Xc,
