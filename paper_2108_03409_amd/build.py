@@ -36,7 +36,7 @@ FLAGS = [
 # literals, which loop-invariant code motion would keep in registers across the
 # main loops (k_cnn_net 195 instead of 121 registers, k_cnn_eloc64 224 instead of 139,
 # k_metropolis<7, 2, false> spilling at 256 instead of 171)
-FILE_FLAGS = {f: ["-mllvm", "-disable-machine-licm"] for f in ("cnn.hip", "arnqs.hip", "sampler.hip")}
+FILE_FLAGS = {f: ["-mllvm", "-disable-machine-licm"] for f in ("cnn.hip", "arnqs.hip", "sampler.hip", "vjp.hip")}
 
 
 def hipcc() -> str:

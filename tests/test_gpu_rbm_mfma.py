@@ -1,0 +1,57 @@
+"""RBM log psi of many samples and the vector-Jacobian product at the edges of
+their matrix-core tiles (16 sites, 16 units, 32 or 64 samples, words of 64
+spins, the 128-site line of the one-kernel product) against the oracle.  Log
+psi: 1e-11 of its scale.  VJP: a sum over the samples of g conj(O), so
+|x - ref| <= (B + 64) 2^-50 sum_n |g_n| |O_nk| covers both sides' rounding."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import rbm as orbm
+from gpu_common import DEV, dev_bits, dev_c128, flush
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2108_03409_amd import nqsvmc as V  # noqa: E402
+
+
+def _model(N, Nh, seed):
+    ctx = V.Context(0)
+    p = si.rbm_params(N, Nh, std=0.4 / np.sqrt(N), is_complex=True, seed=seed)
+    m = V.Model.rbm(ctx, N, Nh, True)
+    m.set_params(dev_c128(p))
+    return m, p
+
+
+@pytest.mark.parametrize("N,Nh,B", [(3, 1, 8192), (16, 15, 8193), (17, 16, 8223), (63, 17, 8192), (64, 63, 8224),
+                                    (65, 64, 8200), (100, 65, 8192), (128, 33, 8192), (129, 5, 8192), (66, 130, 8191)])
+def test_log_psi_many(N, Nh, B):
+    flush(f"log psi N={N} Nh={Nh} B={B}")
+    m, p = _model(N, Nh, N + Nh)
+    bits = si.random_bits(B, N, seed=3)
+    got = m.log_psi(dev_bits(si.pack_bits(bits))).cpu().numpy()
+    idx = np.unique(np.r_[0:40, B // 2, B - 40:B])
+    ref = orbm.log_psi(p, bits[idx], Nh)
+    assert np.max(np.abs(got[idx] - ref)) <= 1e-11 * max(1.0, np.abs(ref).max())
+    # and every sample against the small-call route
+    few = torch.cat([m.log_psi(dev_bits(si.pack_bits(bits[a:a + 4000]))) for a in range(0, B, 4000)]).cpu().numpy()
+    assert np.max(np.abs(got - few)) <= 1e-11 * max(1.0, np.abs(few).max())
+
+
+@pytest.mark.parametrize("N", [1, 15, 16, 17, 48, 49, 64, 65, 80, 81, 96, 97, 112, 113, 128, 129])
+@pytest.mark.parametrize("Nh,B", [(1, 1), (15, 64), (16, 65), (17, 127), (40, 1000)])
+def test_vjp_edges(N, Nh, B):
+    flush(f"vjp N={N} Nh={Nh} B={B}")
+    m, p = _model(N, Nh, N + Nh)
+    bits = si.random_bits(B, N, seed=N)
+    rng = np.random.default_rng(B)
+    g = rng.normal(size=B) + 1j * rng.normal(size=B)
+    s, dg = dev_bits(si.pack_bits(bits)), torch.from_numpy(g).to(DEV)
+    O = orbm.grad_log_psi(p, bits, Nh)
+    ref, scale = O.conj().T @ g, np.abs(O).T @ np.abs(g)
+    x = m.log_psi_vjp(s, dg).cpu().numpy()
+    assert np.all(np.abs(x - ref) <= (B + 64) * 2.0 ** -50 * scale)
