@@ -25,64 +25,80 @@ namespace {
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 int nh_pad16(int Nh) { return (Nh + 15) / 16 * 16; }
-constexpr int kThRows = 64;  // samples per group of the matrix-core theta
-constexpr int kThCols = 64;  // real columns per group (32 hidden units, re and im)
-constexpr int kThKB = 4;     // k steps (4 sites each) whose operand loads are issued together
+constexpr int kThRows = 64;   // samples per group of the matrix-core theta
+constexpr int kThUnits = 32;  // hidden units per group
 
-// theta = b + W sigma on the float64 matrix cores.  With Wt viewed as reals
-// [N][2 N_h] (column c = 2 j + re/im), theta[n][c] = b[c] + sum_i sigma_i(n) Wt[i][c]:
-// a group takes 64 samples x 64 columns, wave w the samples 16 w .. 16 w + 15
-// against four 16-column tiles.  v_mfma_f64_16x16x4f64: lane l holds
-// A[l % 16][l / 16] (sample, site), B[l / 16][l % 16] (site, column) and, in
-// register r, D[l / 16 + 4 r][l % 16].  sigma = +-1 is exact; the sums are
-// float64 in the matrix core's order.
-__global__ __launch_bounds__(256) void k_theta_mfma(const double* __restrict__ bre, const double* __restrict__ Wr,
+__device__ __forceinline__ double sign_of(uint64_t w, int i) {  // +1 where bit i is set, else -1
+  return __hiloint2double((int)(0xBFF00000u ^ ((uint32_t)(w >> i) << 31)), 0);
+}
+
+// theta = b + W sigma on the float64 matrix cores: rows samples, columns units, the
+// real and the imaginary part in two accumulators of the same lanes; a group takes 64
+// samples x 32 units, a wave 32 x 16.  v_mfma_f64_16x16x4f64: lane l holds
+// A[l % 16][l / 16] (sample, site), B[l / 16][l % 16] (site, unit) and, in register r,
+// D[l / 16 + 4 r][l % 16].  sigma = +-1 is exact; the sums are float64 in the matrix
+// core's order.  Every 16 bytes of W a lane reads feed four products, eight sites'
+// reads ahead of them; theta leaves 256 contiguous bytes per 16 lanes.
+// Bound: the matrix cores (15 us at 64 sites, 256 units, 16 384 samples) and the write of
+// theta (14 us), 36 -> 31 us; 400 sites, 800 units, 4 096 samples 142 -> 122 us (real
+// columns of W read 8 bytes at a time, 64 x 64 tiles before).
+__global__ __launch_bounds__(256) void k_theta_mfma(const double2* __restrict__ bias, const double2* __restrict__ Wt,
                                                     const uint64_t* __restrict__ s, int64_t B, int N, int W, int Nh,
-                                                    double* __restrict__ theta) {
+                                                    double2* __restrict__ theta) {
   extern __shared__ uint64_t sbits[];  // [kThRows][W]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int li = lane & 15, lk = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t n0 = (int64_t)blockIdx.y * kThRows;
-  const int ncol = 2 * Nh;
-  const int c0 = blockIdx.x * kThCols;
-  for (int e = tid; e < kThRows * W; e += 256) {
-    const int64_t n = n0 + e / W;
-    sbits[e] = n < B ? s[n * W + e % W] : 0ull;
-  }
+  const int row = 32 * (wv >> 1), unit = blockIdx.x * kThUnits + 16 * (wv & 1) + li;
+  for (int e = tid; e < kThRows * W; e += 256) sbits[e] = n0 + e / W < B ? s[n0 * W + e] : 0ull;
   __syncthreads();
-  const uint64_t* myb = sbits + (wave * 16 + li) * W;  // the bits of the lane's A row
-  const bool row_ok = n0 + wave * 16 + li < B;
-  doublex4 acc[4];
+  const int ul = unit < Nh ? unit : Nh - 1;  // units past N_h repeat the last, unwritten
+  const double2 b = bias[ul];
+  doublex4 tr[2], ti[2];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < N; k0 += 4 * kThKB) {
-    double bv[kThKB][4];
+  for (int h = 0; h < 2; ++h) {
+    tr[h] = doublex4{b.x, b.x, b.x, b.x};
+    ti[h] = doublex4{b.y, b.y, b.y, b.y};
+  }
+  // rows of W of eight steps of four sites; past N: any row, its product left out
+  const double2* col = Wt + ul;
+  double2 v[2][8];
+  auto load = [&](int k0, double2(&d)[8]) {
 #pragma unroll
-    for (int kb = 0; kb < kThKB; ++kb) {
-      const int k = k0 + 4 * kb + lk;
+    for (int q = 0; q < 8; ++q) {
+      const int i = k0 + 4 * q + lk;
+      d[q] = col[(int64_t)(i < N ? i : N - 1) * Nh];
+    }
+  };
+  auto step = [&](int k0, const double2(&d)[8]) {
+    const uint64_t w0 = sbits[(row + li) * W + (k0 >> 6)] >> (k0 & 63);
+    const uint64_t w1 = sbits[(row + 16 + li) * W + (k0 >> 6)] >> (k0 & 63);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int c = c0 + 16 * t + li;
-        bv[kb][t] = (k < N && c < ncol) ? Wr[(int64_t)k * ncol + c] : 0.0;
+    for (int q = 0; q < 8; ++q) {
+      const bool in = k0 + 4 * q + lk < N;
+      const double a0 = in ? sign_of(w0, 4 * q + lk) : 0.0, a1 = in ? sign_of(w1, 4 * q + lk) : 0.0;
+      tr[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, d[q].x, tr[0], 0, 0, 0);
+      ti[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, d[q].y, ti[0], 0, 0, 0);
+      tr[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, d[q].x, tr[1], 0, 0, 0);
+      ti[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, d[q].y, ti[1], 0, 0, 0);
+    }
+  };
+  load(0, v[0]);
+  for (int k0 = 0; k0 < N; k0 += 64) {
+    if (k0 + 32 < N) load(k0 + 32, v[1]);
+    step(k0, v[0]);
+    if (k0 + 32 >= N) break;
+    if (k0 + 64 < N) load(k0 + 64, v[0]);
+    step(k0 + 32, v[1]);
+  }
+  if (unit < Nh)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t n = n0 + row + 16 * h + lk + 4 * r;
+        if (n < B) theta[n * Nh + unit] = make_double2(tr[h][r], ti[h][r]);
       }
-    }
-#pragma unroll
-    for (int kb = 0; kb < kThKB; ++kb) {
-      const int k = k0 + 4 * kb + lk;
-      const double a = (k < N && row_ok) ? (((myb[k >> 6] >> (k & 63)) & 1ull) ? 1.0 : -1.0) : 0.0;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv[kb][t], acc[t], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int c = c0 + 16 * t + li;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t n = n0 + wave * 16 + lk + 4 * r;
-      if (n < B && c < ncol) theta[n * ncol + c] = acc[t][r] + bre[c];
-    }
-  }
 }
 
 // theta of a sample's hidden units as the kernels below take it: from memory
@@ -109,6 +125,105 @@ __device__ __forceinline__ double2 theta_at(const theta_src& t, const uint64_t* 
     }
   }
   return th;
+}
+
+// log psi of many samples with theta in registers only: 32 samples per work-group, wave w
+// the unit tiles w, w + 4, ... of 16 units.  theta = b + sigma W is a product on the
+// float64 matrix cores (rows samples, columns units, real and imaginary parts in two
+// accumulators of the same lanes), so that a lane takes log cosh of its own entries and
+// adds them up over its tiles; the weights of the next 64 sites or tile are on their way
+// while it does.
+// Bound: the matrix cores and the elementary functions, one after the other.  N = 64,
+// N_h = 256, 16 384 samples 71 -> 58 us (theta through memory before).
+__global__ __launch_bounds__(256, 2) void k_logpsi_mfma(const double2* __restrict__ params,
+                                                        const double2* __restrict__ Wt,
+                                                        const uint64_t* __restrict__ s, int64_t B, int N, int W,
+                                                        int Nh, double2* __restrict__ logpsi) {
+  extern __shared__ uint64_t bits[];  // [32][W]
+  __shared__ double2 ths[4][4][64];  // theta of four of a lane's eight entries
+  __shared__ double2 lps[4][8][64];  // and their sums of log cosh over the tiles
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t n0 = (int64_t)blockIdx.x * 32;
+  for (int e = tid; e < 32 * W; e += 256) bits[e] = n0 + e / W < B ? s[n0 * W + e] : 0ull;
+  __syncthreads();
+  // entry (site, unit) of the weights; sites past N read zero (out of the buffer's range),
+  // units past N_h the next site's (their log cosh is left out)
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Wt, 0, N * Nh * 16, 0x00027000);
+  double2 v[16];
+  auto load = [&](int ut, int w) {
+    const int at = (lk * Nh + ut * 16 + li) * 16;
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+      v[q] = __builtin_bit_cast(double2,
+                                __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, (64 * w + 4 * q) * Nh * 16, 0));
+  };
+  const int ntile = (Nh + 15) / 16;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) lps[wv][e][lane] = make_double2(0.0, 0.0);
+  if (wv < ntile) load(wv, 0);
+  for (int ut = wv; ut < ntile; ut += 4) {
+    const int unit = ut * 16 + li;
+    double2 b = make_double2(0.0, 0.0);
+    if (unit < Nh) b = params[N + unit];
+    doublex4 tr[2], ti[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      tr[h] = doublex4{b.x, b.x, b.x, b.x};
+      ti[h] = doublex4{b.y, b.y, b.y, b.y};
+    }
+    for (int w = 0; w < W; ++w) {
+      const uint64_t w0 = bits[li * W + w], w1 = bits[(16 + li) * W + w];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const double a0 = sign_of(w0, 4 * q + lk), a1 = sign_of(w1, 4 * q + lk);
+        tr[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, v[q].x, tr[0], 0, 0, 0);
+        ti[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, v[q].y, ti[0], 0, 0, 0);
+        tr[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, v[q].x, tr[1], 0, 0, 0);
+        ti[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, v[q].y, ti[1], 0, 0, 0);
+      }
+      if (w + 1 < W)
+        load(ut, w + 1);
+      else if (ut + 4 < ntile)
+        load(ut + 4, 0);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ths[wv][r][lane] = make_double2(tr[h][r], ti[h][r]);
+      if (unit < Nh)
+#pragma unroll 1
+        for (int r = 0; r < 4; ++r)
+          lps[wv][4 * h + r][lane] = cadd(lps[wv][4 * h + r][lane], clogcosh(ths[wv][r][lane]));
+    }
+  }
+  // sum_i a_i sigma_i, eight threads per sample
+  double2 va = make_double2(0.0, 0.0);
+  for (int i = tid & 7; i < N; i += 8) {
+    const uint64_t w = bits[(tid >> 3) * W + (i >> 6)];
+    va = cadd(va, cscale(params[i], sign_of(w, i & 63)));
+  }
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) {
+    va.x += __shfl_xor(va.x, o, 64);
+    va.y += __shfl_xor(va.y, o, 64);
+  }
+  // sample 16 h + 4 r + k: entry 4 h + r of lanes 16 k .. 16 k + 15 of the four waves, two
+  // lanes of each wave per thread
+  __syncthreads();
+  const int q = tid >> 3, part = tid & 7;
+  double2 l = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int w = 0; w < 4; ++w)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      l = cadd(l, lps[w][4 * (q >> 4) + ((q & 15) >> 2)][16 * (q & 3) + 2 * part + u]);
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) {
+    l.x += __shfl_xor(l.x, o, 64);
+    l.y += __shfl_xor(l.y, o, 64);
+  }
+  if (part == 0 && n0 + q < B) logpsi[n0 + q] = cadd(va, l);
 }
 
 // log psi(n) = sum_i a_i sigma_i + sum_j logcosh(theta_j); one wave per sample.
@@ -463,12 +578,11 @@ void rbm_theta(vmc_model* m, const uint64_t* s, int64_t B, double2* theta, hipSt
   if (!st) st = m->ctx->stream;
   // at most 65535 row tiles per launch
   const int64_t chunk = (int64_t)65535 * kThRows;
-  const unsigned gx = (unsigned)((2 * m->Nh + kThCols - 1) / kThCols);
+  const unsigned gx = (unsigned)((m->Nh + kThUnits - 1) / kThUnits);
   for (int64_t b0 = 0; b0 < B; b0 += chunk) {
     const int64_t nb = std::min(chunk, B - b0);
-    k_theta_mfma<<<dim3(gx, (unsigned)((nb + kThRows - 1) / kThRows)), 256, sizeof(uint64_t) * kThRows * m->W,
-                   st>>>((const double*)(m->params + m->N), (const double*)m->Wt, s + b0 * m->W, nb, m->N,
-                                     m->W, m->Nh, (double*)(theta + b0 * m->Nh));
+    k_theta_mfma<<<dim3(gx, (unsigned)((nb + kThRows - 1) / kThRows)), 256, sizeof(uint64_t) * kThRows * m->W, st>>>(
+        m->params + m->N, m->Wt, s + b0 * m->W, nb, m->N, m->W, m->Nh, theta + b0 * m->Nh);
     VMC_HIP(hipGetLastError());
   }
 }
@@ -548,6 +662,14 @@ void rbm_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
   double2* theta = (double2*)ws_take(ctx, sizeof(double2) * chunk * m->Nh);
   for (int64_t b0 = 0; b0 < B; b0 += chunk) {
     const int64_t nb = std::min(chunk, B - b0);
+    // in registers where 32 samples per group give every compute unit one (N = 64, N_h =
+    // 256: 8 192 samples 40 against 53 us) and the weights' offsets fit 31 bits
+    if (nb >= 32 * (int64_t)cu_count(ctx) && (int64_t)(m->N + 64) * m->Nh * 16 < (int64_t)1 << 31) {
+      k_logpsi_mfma<<<(unsigned)((nb + 31) / 32), 256, sizeof(uint64_t) * 32 * m->W, ctx->stream>>>(
+          m->params, m->Wt, s + b0 * m->W, nb, m->N, m->W, m->Nh, logpsi + b0);
+      VMC_HIP(hipGetLastError());
+      continue;
+    }
     const theta_src th = take_theta(m, s + b0 * m->W, nb, theta);
     k_logpsi<<<(unsigned)nb, 64, 0, ctx->stream>>>(m->params, th, s + b0 * m->W, nb, m->N, m->W, m->Nh, logpsi + b0);
     VMC_HIP(hipGetLastError());
