@@ -6,12 +6,12 @@
 //   k_chol_diag   one work-group factors the diagonal block in registers,
 //                 writes L_bb, inverts it and writes L_bb^{-1} (dense
 //                 64 x 64) to the Linv buffer;
-//   k_zmfma<0>    rows below: L_rb = A_rb L_bb^{-H}, a complex GEMM on the
+//   k_zprod SOLVE rows below: L_rb = A_rb L_bb^{-H}, a complex GEMM on the
 //                 float64 matrix cores (in place, one 64-row block per group);
-//   k_zmfma<2>    the rest of the panel's columns: A_rc -= L_rb L_cb^H.
+//   k_zprod RECT  the rest of the panel's columns: A_rc -= L_rb L_cb^H.
 // Per panel p, once its four blocks are done:
-//   k_zmfma<2>    lookahead: the next panel's columns -= L_rp L_cp^H;
-//   k_zmfma<1>    trailing update A_rc -= L_rp L_cp^H (reduction depth 256) on
+//   k_zprod RECT  lookahead: the next panel's columns -= L_rp L_cp^H;
+//   k_zprod TRI   trailing update A_rc -= L_rp L_cp^H (reduction depth 256) on
 //                 the lower 64 x 64 tiles of the rest of the trailing matrix,
 //                 on a second stream, overlapping the next panel's
 //                 factorisation; the trailing matrix is read and written once
@@ -182,46 +182,64 @@ struct zargs {
   int depth;     // valid panel columns (reduction length)
   int64_t rbase; // first output row
   int64_t cbase; // first output column
-  int64_t cend;  // one past the last output column (MODE 2)
-  int nct;       // column tiles (MODE 2)
+  int64_t cend;  // one past the last output column (RECT)
+  int nct;       // column tiles (RECT); tile rows of the triangle (TRI)
+  int sd;        // side of the squares of tiles (TRI)
   const double2* Linv;
-  int64_t ntiles;
   const long long* fail;
 };
 
-// MODE 0 (panel solve):   S[R][kb0 + c] = sum_m S[R][kb0 + m] conj(Linv[c][m]),  R = rbase + 64 b + r
-// MODE 1 (trailing):      S[R][C] -= sum_m S[R][kb0 + m] conj(S[C][kb0 + m]) on lower 64x64 tiles of
-//                         the square region starting at (rbase, rbase), C <= R
-// MODE 2 (inside panel):  as MODE 1 for R >= rbase, cbase <= C < cend, C <= R (rectangular tile grid)
-// The reduction is staged 16 columns at a time through double-buffered LDS.
+// The panel's and the trailing matrix' products on 64 x 64 tiles:
+//   SOLVE  S[R][kb0 + c] = sum_m S[R][kb0 + m] conj(Linv[c][m]), R >= rbase (in place; depth 64)
+//   RECT   S[R][C] -= sum_m S[R][kb0 + m] conj(S[C][kb0 + m]), R >= rbase, cbase <= C < cend, C <= R
+//   TRI    the same for the lower triangle from (rbase, rbase) on
+// The operands go straight from memory to LDS, eight columns a stage, two stages: row r of a
+// tile is 128 bytes, its 16-byte entry of column m at place m ^ ((r / 2) % 8), so that the 16
+// rows a fragment reads at one column fall on 16 different groups of banks.  A stage's
+// fragments are read before the next stage's loads are issued: the compiler makes an LDS read
+// wait for every load into LDS before it.  TRI tiles go out in squares of sd x sd per XCD,
+// whose 2 sd operand rows meet in its L2.
+// Bound: the matrix cores (62 ms of products at K = 16 704), and towards the end the panel's
+// chain, whose kernels wait for a place beside the TRI launch.  Without staging registers
+// three groups fit a compute unit, in any mix of the modes.  K = 16 704: all TRI launches 88
+// -> 74 ms, the whole factorisation 95.1 -> 81.7 ms; K = 1 529 1.89 -> 1.68 ms (operands
+// through registers, two groups per compute unit, one row of tiles after the other per XCD
+// before).  TRI held to two groups per compute unit, to leave a place for the panel: 84.4 ms.
+constexpr int ZS = 8;  // columns per stage
+
+typedef __attribute__((address_space(3))) void* lptr_t;
+
+enum { SOLVE, RECT, TRI };
+
 template <int MODE>
-__global__ __launch_bounds__(256, 2) void k_zmfma(zargs a) {
-  __shared__ double2 Ps[2][16][CB + 1];
-  __shared__ double2 Qs[2][16][CB + 1];
+__global__ __launch_bounds__(256, 3) void k_zprod(zargs a) {
+  __shared__ double2 Ps[2][CB * ZS];
+  __shared__ double2 Qs[2][CB * ZS];
   if (*a.fail >= 0) return;
   const int64_t K = a.K;
   int64_t r0, c0;
-  if (MODE == 0) {
+  if (MODE == SOLVE) {
     r0 = a.rbase + (int64_t)blockIdx.x * CB;
     c0 = 0;
-  } else if (MODE == 1) {
-    const int64_t per = (a.ntiles + 7) / 8;
-    const int64_t lin = (blockIdx.x % 8) * per + blockIdx.x / 8;
-    if (lin >= a.ntiles) return;
-    int tr = (int)((sqrt(8.0 * (double)lin + 1.0) - 1.0) * 0.5);
-    while ((int64_t)(tr + 1) * (tr + 2) / 2 <= lin) ++tr;
-    while ((int64_t)tr * (tr + 1) / 2 > lin) --tr;
-    const int tc = (int)(lin - (int64_t)tr * (tr + 1) / 2);
-    r0 = a.rbase + (int64_t)tr * CB;
-    c0 = a.rbase + (int64_t)tc * CB;
-  } else {
+  } else if (MODE == RECT) {
     r0 = a.rbase + (int64_t)(blockIdx.x / a.nct) * CB;
     c0 = a.cbase + (int64_t)(blockIdx.x % a.nct) * CB;
+  } else {
+    const int sd = a.sd, j = blockIdx.x / 8;
+    const int64_t sq = (int64_t)(j / (sd * sd)) * 8 + blockIdx.x % 8;
+    int sr = (int)((sqrt(8.0 * (double)sq + 1.0) - 1.0) * 0.5);
+    while ((int64_t)(sr + 1) * (sr + 2) / 2 <= sq) ++sr;
+    while ((int64_t)sr * (sr + 1) / 2 > sq) --sr;
+    const int sc = (int)(sq - (int64_t)sr * (sr + 1) / 2), in = j % (sd * sd);
+    const int tr = sr * sd + in / sd, tc = sc * sd + in % sd;
+    if (tr >= a.nct || tc > tr) return;
+    r0 = a.rbase + (int64_t)tr * CB;
+    c0 = a.rbase + (int64_t)tc * CB;
   }
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave >> 1, wc = wave & 1;
   const int li = lane & 15, lk = lane >> 4;
-
   doublex4 acc[2][2][3];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -230,64 +248,68 @@ __global__ __launch_bounds__(256, 2) void k_zmfma(zargs a) {
 #pragma unroll
       for (int q = 0; q < 3; ++q) acc[i][j][q] = doublex4{0.0, 0.0, 0.0, 0.0};
 
-  double2 rp[4], rq[4];
-  auto gload = [&](int m0) {
+  // wave w loads rows 16 w .. 16 w + 15 of both tiles, eight rows per instruction; rows past
+  // the matrix repeat its last one (their products are not written)
+  const auto sp = __builtin_amdgcn_make_buffer_rsrc((void*)(a.S + r0 * K + a.kb0), 0, -1, 0x00027000);
+  const auto sq = __builtin_amdgcn_make_buffer_rsrc(MODE == SOLVE ? (void*)a.Linv : (void*)(a.S + c0 * K + a.kb0), 0,
+                                                    -1, 0x00027000);
+  int vp[2], vq[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int q = tid + 256 * j;
-      const int r = q >> 4, mm = q & 15;
-      const int m = m0 + mm;
-      const int64_t R = r0 + r;
-      rp[j] = (R < K && m < a.depth) ? a.S[R * K + a.kb0 + m] : make_double2(0.0, 0.0);
-      if (MODE == 0) {
-        rq[j] = a.Linv[r * CB + m];
-      } else {
-        const int64_t C = c0 + r;
-        rq[j] = (C < K && m < a.depth) ? a.S[C * K + a.kb0 + m] : make_double2(0.0, 0.0);
+  for (int t = 0; t < 2; ++t) {
+    const int r = 16 * wave + 8 * t + (lane >> 3), m = (lane & 7) ^ ((r >> 1) & 7);
+    vp[t] = ((int)min((int64_t)r, K - 1 - r0) * (int)K + m) * 16;
+    vq[t] = MODE == SOLVE ? (r * CB + m) * 16 : ((int)min((int64_t)r, K - 1 - c0) * (int)K + m) * 16;
+  }
+  auto load = [&](int st, int buf) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(sp, (lptr_t)(Ps[buf] + (16 * wave + 8 * t) * ZS), 16, vp[t],
+                                               st * ZS * 16, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(sq, (lptr_t)(Qs[buf] + (16 * wave + 8 * t) * ZS), 16, vq[t],
+                                               st * ZS * 16, 0, 0);
+    }
+  };
+  const int nst = a.depth / ZS;
+  load(0, 0);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  auto stage = [&](int st, auto bufc) {
+    constexpr int buf = decltype(bufc)::value;
+    double2 fa[2][2], fb[2][2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int at = (4 * ks + lk) ^ ((li >> 1) & 7);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        fa[ks][i] = Ps[buf][(wr * 32 + i * 16 + li) * ZS + at];
+        fb[ks][i] = Qs[buf][(wc * 32 + i * 16 + li) * ZS + at];
       }
     }
-  };
-  auto sstore = [&](int buf) {
+    if (st + 1 < nst) load(st + 1, buf ^ 1);  // released by every wave at the last barrier
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int q = tid + 256 * j;
-      Ps[buf][q & 15][q >> 4] = rp[j];
-      Qs[buf][q & 15][q >> 4] = rq[j];
-    }
-  };
-  const int nst = (a.depth + 15) / 16;
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  for (int st = 0; st < nst; ++st) {
-    const int buf = st & 1;
-    if (st + 1 < nst) gload((st + 1) * 16);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int m = ks * 4 + lk;
-      double2 fa[2], fb[2];
+    for (int ks = 0; ks < 2; ++ks) {
       double sa[2], db[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        fa[i] = Ps[buf][m][wr * 32 + i * 16 + li];
-        sa[i] = fa[i].x + fa[i].y;
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        fb[j] = Qs[buf][m][wc * 32 + j * 16 + li];
-        db[j] = fb[j].x - fb[j].y;
+        sa[i] = fa[ks][i].x + fa[ks][i].y;
+        db[i] = fb[ks][i].x - fb[ks][i].y;
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          acc[i][j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i].x, fb[j].x, acc[i][j][0], 0, 0, 0);
-          acc[i][j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i].y, fb[j].y, acc[i][j][1], 0, 0, 0);
+          acc[i][j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[ks][i].x, fb[ks][j].x, acc[i][j][0], 0, 0, 0);
+          acc[i][j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[ks][i].y, fb[ks][j].y, acc[i][j][1], 0, 0, 0);
           acc[i][j][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[i], db[j], acc[i][j][2], 0, 0, 0);
         }
     }
-    if (st + 1 < nst) sstore(buf ^ 1);
-    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);  // the wait stays after the products
+    __builtin_amdgcn_s_waitcnt(0);      // this wave's rows of the next stage have landed
+    __syncthreads();                    // and every wave is done with this one
+  };
+  for (int st = 0; st < nst; st += 2) {
+    stage(st, std::integral_constant<int, 0>{});
+    if (st + 1 < nst) stage(st + 1, std::integral_constant<int, 1>{});
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -295,22 +317,14 @@ __global__ __launch_bounds__(256, 2) void k_zmfma(zargs a) {
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        // float64 MFMA accumulators interleave rows: register r of lane l holds
-        // D[l / 16 + 4 r][l % 16] (float32 holds D[4 (l / 16) + r][l % 16])
-        const int row = wr * 32 + i * 16 + lk + 4 * r;
-        const int col = wc * 32 + j * 16 + li;
+        const int64_t R = r0 + wr * 32 + i * 16 + lk + 4 * r, C = c0 + wc * 32 + j * 16 + li;
         const double re = acc[i][j][0][r] + acc[i][j][1][r];
         const double im = (acc[i][j][2][r] - acc[i][j][0][r]) + acc[i][j][1][r];
-        const int64_t R = r0 + row;
-        if (R >= K) continue;
-        if (MODE == 0) {
-          if (col < a.depth) a.S[R * K + a.kb0 + col] = make_double2(re, im);
-        } else {
-          const int64_t C = c0 + col;
-          if (C < K && C <= R && (MODE == 1 || C < a.cend)) {
-            const double2 v = a.S[R * K + C];
-            a.S[R * K + C] = make_double2(v.x - re, v.y - im);
-          }
+        if (MODE == SOLVE) {
+          if (R < K) a.S[R * K + a.kb0 + C] = make_double2(re, im);
+        } else if (R < K && C <= R && (MODE == TRI || C < a.cend)) {
+          const double2 v = a.S[R * K + C];
+          a.S[R * K + C] = make_double2(v.x - re, v.y - im);
         }
       }
 }
@@ -550,13 +564,13 @@ void chol_factor(vmc_ctx* ctx, double2* S, int64_t K, double2* Linv, long long* 
       a.rbase = c0 + nb;
       a.Linv = Lb;
       a.fail = fail;
-      k_zmfma<0><<<(unsigned)((rest + CB - 1) / CB), 256, 0, st>>>(a);
+      k_zprod<SOLVE><<<(unsigned)((rest + CB - 1) / CB), 256, 0, st>>>(a);
       if (c0 + nb < pend) {  // remaining columns of this panel
         a.cbase = c0 + nb;
         a.cend = pend;
         a.nct = (int)((pend - a.cbase + CB - 1) / CB);
         const int64_t nrt = (rest + CB - 1) / CB;
-        k_zmfma<2><<<(unsigned)(nrt * a.nct), 256, 0, st>>>(a);
+        k_zprod<RECT><<<(unsigned)(nrt * a.nct), 256, 0, st>>>(a);
       }
     }
     if (pend >= K) break;
@@ -576,7 +590,7 @@ void chol_factor(vmc_ctx* ctx, double2* S, int64_t K, double2* Linv, long long* 
       a.nct = (int)((pend2 - pend + CB - 1) / CB);
       a.fail = fail;
       const int64_t nrt = (K - pend + CB - 1) / CB;
-      k_zmfma<2><<<(unsigned)(nrt * a.nct), 256, 0, st>>>(a);
+      k_zprod<RECT><<<(unsigned)(nrt * a.nct), 256, 0, st>>>(a);
     }
     // the rest of the trailing matrix on the auxiliary stream
     if (pend2 < K) {
@@ -588,9 +602,12 @@ void chol_factor(vmc_ctx* ctx, double2* S, int64_t K, double2* Linv, long long* 
       a.depth = (int)(pend - p0);
       a.rbase = pend2;
       a.fail = fail;
-      const int64_t nt = (K - pend2 + CB - 1) / CB;
-      a.ntiles = nt * (nt + 1) / 2;
-      k_zmfma<1><<<(unsigned)(((a.ntiles + 7) / 8) * 8), 256, 0, aux>>>(a);
+      a.nct = (int)((K - pend2 + CB - 1) / CB);
+      // squares of eight tile rows where every XCD gets many of them (at least 8 each), of
+      // four or single tiles below, where whole squares would leave XCDs idle
+      a.sd = a.nct >= 96 ? 8 : a.nct >= 48 ? 4 : 1;
+      const int64_t nsr = (a.nct + a.sd - 1) / a.sd, nsq = nsr * (nsr + 1) / 2;
+      k_zprod<TRI><<<(unsigned)((nsq + 7) / 8 * 8 * a.sd * a.sd), 256, 0, aux>>>(a);
       VMC_HIP(hipEventRecord(ctx->ev_aux, aux));
       aux_busy = true;
     }

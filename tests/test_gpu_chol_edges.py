@@ -42,3 +42,18 @@ def test_solve_at_block_edges(K, real):
         O0[:, k] = 0.0
         x0, info0 = V.sr_solve(ctx, torch.from_numpy(O0).to(DEV), de, nu_rel=0.0, mode=mode, raise_on_error=False)
         assert x0 is None and info0["status"] == "NOT_PD" and info0["fail_index"] == k
+
+
+# the trailing update's squares of 4 x 4 and 8 x 8 tiles, with a ragged last square and row
+@pytest.mark.parametrize("K", [3650, 6721])
+def test_solve_large(K):
+    flush(f"chol K={K}")
+    ctx = V.Context(0)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    O = torch.randn(K + 8, K, dtype=torch.complex64, device=DEV, generator=gen)
+    e = torch.randn(K + 8, dtype=torch.complex128, device=DEV, generator=gen)
+    S, F, _ = V.sr_fisher(ctx, O, e, nu_rel=1e-1)
+    x, _ = V.sr_solve(ctx, O, e, nu_rel=1e-1)
+    r = torch.linalg.vector_norm(S @ x + F).item()
+    scale = (torch.linalg.vector_norm(S) * torch.linalg.vector_norm(x) + torch.linalg.vector_norm(F)).item()
+    assert r <= 8 * K * 2.0 ** -52 * scale, (r, scale)
