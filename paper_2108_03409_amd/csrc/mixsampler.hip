@@ -489,6 +489,12 @@ void mix_global_step(vmc_sampler* S, uint64_t g) {
   // (the acceptance of step g - 1) precedes this point of the main stream
   VMC_HIP(hipEventRecord(S->mix_ev_main, st));
   VMC_HIP(hipStreamWaitEvent(S->mix_side, S->mix_ev_main, 0));
+  // the flips that follow on the main stream wait until the side stream has come this far,
+  // so that k_made_block's one group per compute unit finds its place before the flips'
+  // groups fill the chip (20 x 20, 4 096 chains: it ends after 0.75 instead of 2.5 ms, and
+  // the sweep after 2.62 instead of 2.78)
+  VMC_HIP(hipEventRecord(S->mix_ev_prop[b ^ 1], S->mix_side));
+  VMC_HIP(hipStreamWaitEvent(st, S->mix_ev_prop[b ^ 1], 0));
   mix_proposals(S, g + 1, b ^ 1, S->mix_side);
   VMC_HIP(hipEventRecord(S->mix_ev_prop[b ^ 1], S->mix_side));
   S->mix_side_buf = b ^ 1;
