@@ -168,6 +168,7 @@ struct vmc_model {
   int lowp_prec = -1;
   float2* Wt32 = nullptr;   // [N][N_h]
   float2* ab32 = nullptr;   // [N + N_h]: a then b
+  void* Wb16 = nullptr;        // bfloat16: W as [2 N_h][N up to a multiple of 32]
   struct lowp_tables {
     uint64_t version = 0;
     int prec = -1, n_moves = 0;
@@ -315,6 +316,22 @@ __device__ __forceinline__ double2 ctanh(double2 z) {
   double2 w = make_double2(e * c, e * s);
   double2 r = cdiv(make_double2(1.0 - w.x, -w.y), make_double2(1.0 + w.x, w.y));
   return neg ? make_double2(-r.x, -r.y) : r;
+}
+
+// tanh z and the summable log cosh z (clogcosh's branch) from one exponential and one
+// sine / cosine pair: with w = e^{-2 z'}, z' = +-z and Re z' >= 0,
+//   tanh z' = (1 - w) / (1 + w),  log cosh z = z' - log 2 + log(1 + w)
+template <bool LIB = true>
+__device__ __forceinline__ void ctanh_logcosh(double2 z, double2& t, double2& l) {
+  const bool neg = z.x < 0.0;
+  if (neg) z = make_double2(-z.x, -z.y);
+  double e = m64::fexp_neg(2.0 * z.x), s, c;
+  m64::fsincos<LIB>(-2.0 * z.y, &s, &c);
+  const double er = e * c, ei = e * s;
+  const double2 r = cdiv(make_double2(1.0 - er, -ei), make_double2(1.0 + er, ei));
+  t = neg ? make_double2(-r.x, -r.y) : r;
+  const double lr = 0.5 * m64::flog1p(2.0 * er + er * er + ei * ei);
+  l = make_double2(z.x - 0.69314718055994530942 + lr, z.y + m64::fatan2(ei, 1.0 + er));
 }
 
 // float32 complex helpers (low-precision network evaluation)
