@@ -64,7 +64,7 @@ struct sampler_args {
 // two-wave groups of few chains are held to two, without which the dispatcher
 // leaves three on some SIMDs and one on others (Heisenberg 10 x 10: 0.92 instead of 0.79 ms).
 // 20 x 20, N_h = 800, 4 096 chains: 8.25 -> 1.8 ms a sweep; Heisenberg 10 x 10,
-// N_h = 400, 1 024 chains x 8 sweeps 1.13 -> 0.79 ms, 4 096 chains x 4 sweeps
+// N_h = 400, 1 024 chains x 8 sweeps 1.13 -> 0.75 ms, 4 096 chains x 4 sweeps
 // 2.36 -> 1.0 ms (theta in LDS, rows of T and D per proposal, step tables in LDS,
 // one wave of 16 slots per chain above 512 units before).
 template <int Q, int NW, bool TRACK>
@@ -146,25 +146,26 @@ __attribute__((amdgpu_waves_per_eu(TRACK || Q > 7 || (NW == 2 && Q <= 4) ? 2 : 3
   } else {
     build_theta();
   }
-  // t = tanh theta, and the sum of log cosh theta over the lane's units if it is asked for:
+  // t = tanh theta, and the sum of log cosh theta over the lane's units:
   // one unit at a time through lane-private LDS slots, so that the elementary functions
   // stand in the code once and the loop over the proposals stays in the instruction cache
   __shared__ double2 ths[NW][Q][64];
-  auto tanh_theta = [&](bool logs) {
+  auto tanh_theta = [&] {
     double2 lp = make_double2(0.0, 0.0);
 #pragma unroll
     for (int q = 0; q < Q; ++q) ths[wv][q][lane] = th[q];
 #pragma unroll 1
     for (int q = 0; q < Q; ++q) {
-      const double2 v = ths[wv][q][lane];
-      if (logs && jb + lane + 64 * q < Nh) lp = cadd(lp, clogcosh(v));
-      ths[wv][q][lane] = ctanh(v);
+      double2 t, l;
+      ctanh_logcosh(ths[wv][q][lane], t, l);
+      if (jb + lane + 64 * q < Nh) lp = cadd(lp, l);
+      ths[wv][q][lane] = t;
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q) tt[q] = ths[wv][q][lane];
     return lp;
   };
-  tanh_theta(false);
+  tanh_theta();
 
   unsigned long long accepted = 0;
   const int64_t total = a.therm_steps + a.n_record * a.sweep;
@@ -337,7 +338,7 @@ __attribute__((amdgpu_waves_per_eu(TRACK || Q > 7 || (NW == 2 && Q <= 4) ? 2 : 3
         for (int q = 0; q < Q; ++q)
           th[q] = make_double2(fma(-dsg, DP[q].x, th[q].x), fma(-dsg, DP[q].y, th[q].y));
         dsg = 0.0;
-        double2 lp = tanh_theta(true);
+        double2 lp = tanh_theta();
         if (wv == 0)
           for (int i = lane; i - lane < N; i += 64) {  // word i / 64 is the same in all lanes
             const uint32_t lo = (uint32_t)rl((int)cl, (i - lane) >> 6);
@@ -442,6 +443,19 @@ void sampler_run(vmc_sampler* S, int64_t n_per_chain, uint64_t* s_out, double2* 
     a.n_record = n_per_chain;
     a.s_out = s_out;
     a.logpsi_out = logpsi_out;
+    // theta of the chains' spins by the matrix cores where the kernel's own serial sum over
+    // the sites costs more than a launch (100 sites, 400 units, 1 024 chains: 40 against
+    // 10 us a call); the first call draws its spins in the kernel and keeps that sum
+    if (!a.init && m->N >= 48) {
+      if (!S->mix_theta && hipMalloc(&S->mix_theta, sizeof(double2) * (size_t)nc * m->Nh) != hipSuccess) {
+        (void)hipGetLastError();
+        S->mix_theta = nullptr;
+      }
+      if (S->mix_theta) {
+        rbm_theta(m, S->bits, nc, S->mix_theta);
+        a.theta = S->mix_theta;
+      }
+    }
     launch<true>(S->ctx, a, st);
     S->t += (uint64_t)(a.therm_steps + a.n_record * a.sweep);
     S->thermalized = 1;
