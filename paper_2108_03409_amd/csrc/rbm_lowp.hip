@@ -82,7 +82,8 @@ __global__ __launch_bounds__(256) void k_theta_mfma(const float* __restrict__ Wf
         const int k = k0 + 4 * q + lk;
         const float a = k < N ? ((w >> (4 * q + lk)) & 1u ? 1.f : -1.f) : 0.f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b[q][j], acc[j], 0, 0, 0);
+        for (int j = 0; j < 4; ++j)  // past N zero (a weight rounded to infinity times zero is NaN)
+          acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, k < N ? b[q][j] : 0.f, acc[j], 0, 0, 0);
       }
     } else {
       bf16x8 b[4];

@@ -28,7 +28,8 @@ def _model(N, Nh, seed):
 
 
 @pytest.mark.parametrize("N,Nh,B", [(3, 1, 8192), (16, 15, 8193), (17, 16, 8223), (63, 17, 8192), (64, 63, 8224),
-                                    (65, 64, 8200), (100, 65, 8192), (128, 33, 8192), (129, 5, 8192), (66, 130, 8191)])
+                                    (65, 64, 8200), (100, 65, 8192), (128, 33, 8192), (129, 5, 8192), (66, 130, 8191),
+                                    (4096, 2, 8192), (4097, 2, 8192)])
 def test_log_psi_many(N, Nh, B):
     flush(f"log psi N={N} Nh={Nh} B={B}")
     m, p = _model(N, Nh, N + Nh)
@@ -55,3 +56,31 @@ def test_vjp_edges(N, Nh, B):
     ref, scale = O.conj().T @ g, np.abs(O).T @ np.abs(g)
     x = m.log_psi_vjp(s, dg).cpu().numpy()
     assert np.all(np.abs(x - ref) <= (B + 64) * 2.0 ** -50 * scale)
+
+
+# a weight beyond float32: theta_0 = +-1e300 (infinite in float32), so tanh theta_0 = +-1 and
+# every other unit stays finite; N leaves the last product step partly filled; few and many
+# samples, every route of theta
+@pytest.mark.parametrize("N,B", [(5, 40), (65, 40), (70, 9000), (131, 40)])
+@pytest.mark.parametrize("at", [0, -1])
+def test_huge_weight(N, B, at):
+    flush(f"huge weight N={N} B={B} at={at}")
+    Nh = 3
+    ctx = V.Context(0)
+    p = si.rbm_params(N, Nh, std=0.1, is_complex=True, seed=N)
+    W = p[N + Nh:].reshape(Nh, N)
+    W[0, at] = 1e300
+    m = V.Model.rbm(ctx, N, Nh, True)
+    m.set_params(dev_c128(p))
+    bits = si.random_bits(B, N, seed=1)
+    s = dev_bits(si.pack_bits(bits))
+    sg = 2.0 * bits - 1.0
+    O = m.grad_log_psi(s, dtype=torch.complex128).cpu().numpy()
+    assert np.allclose(O[:, N], sg[:, at], atol=1e-12)
+    assert np.all(np.isfinite(O))
+    g = np.ones(B)
+    x = m.log_psi_vjp(s, torch.from_numpy(g + 0j).to(DEV)).cpu().numpy()
+    assert abs(x[N] - sg[:, at].sum()) <= 1e-9 and np.all(np.isfinite(x))
+    assert np.allclose(m.log_psi(s).cpu().numpy().real, 1e300)
+    m.set_precision(V.VMC_F32)
+    assert np.all(np.isposinf(m.log_psi(s).cpu().numpy().real))
