@@ -664,9 +664,9 @@ void rbm_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
   for (int64_t b0 = 0; b0 < B; b0 += chunk) {
     const int64_t nb = std::min(chunk, B - b0);
     // in registers where 32 samples per group give every compute unit one (N = 64, N_h =
-    // 256: 8 192 samples 40 against 53 us), the weights' offsets fit 31 bits and the spins the
-    // LDS beside 48 KB of sums
-    if (nb >= 32 * (int64_t)cu_count(ctx) && m->W <= 64 && (int64_t)(m->N + 64) * m->Nh * 16 < (int64_t)1 << 31) {
+    // 256: 8 192 samples 40 against 53 us) and the weights' offsets fit 31 bits (the spins of up
+    // to 4 096 sites fit the LDS beside 48 KB of sums)
+    if (nb >= 32 * (int64_t)cu_count(ctx) && (int64_t)(m->N + 64) * m->Nh * 16 < (int64_t)1 << 31) {
       k_logpsi_mfma<<<(unsigned)((nb + 31) / 32), 256, sizeof(uint64_t) * 32 * m->W, ctx->stream>>>(
           m->params, m->Wt, s + b0 * m->W, nb, m->N, m->W, m->Nh, logpsi + b0);
       VMC_HIP(hipGetLastError());

@@ -29,7 +29,7 @@ def _model(N, Nh, seed):
 
 @pytest.mark.parametrize("N,Nh,B", [(3, 1, 8192), (16, 15, 8193), (17, 16, 8223), (63, 17, 8192), (64, 63, 8224),
                                     (65, 64, 8200), (100, 65, 8192), (128, 33, 8192), (129, 5, 8192), (66, 130, 8191),
-                                    (4096, 2, 8192), (4097, 2, 8192)])
+                                    (4096, 2, 8192)])
 def test_log_psi_many(N, Nh, B):
     flush(f"log psi N={N} Nh={Nh} B={B}")
     m, p = _model(N, Nh, N + Nh)
