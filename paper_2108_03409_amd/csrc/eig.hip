@@ -89,22 +89,31 @@ struct jrot {
   bool active;
 };
 
+__device__ __forceinline__ double max_abs(double v) { return fabs(v); }
+__device__ __forceinline__ double max_abs(double2 v) { return fmax(fabs(v.x), fabs(v.y)); }
+__device__ __forceinline__ double shifted(double v, int e) { return ldexp(v, e); }
+__device__ __forceinline__ double2 shifted(double2 v, int e) { return make_double2(ldexp(v.x, e), ldexp(v.y, e)); }
+
 // Rotation that zeroes z = M_pq between a = M_pp and b = M_qq: with d = (b - a) / 2,
 // r = sqrt(d^2 + |z|^2): c^2 = (1 + |d| / r) / 2, s = sgn(d) conj(z) / (2 r c) (the smaller
 // of the two angles), and a, b move by -+ sgn(d) |z|^2 / (|d| + r).  Two reciprocal square
-// roots are its whole dependent chain.
+// roots are its whole dependent chain.  d and z are brought to a largest entry in [1/2, 1)
+// by a power of two first, so that their squares stay in range whatever the matrix' scale.
 template <typename T>
 __device__ __forceinline__ jrot<T> make_rot(double a, double b, T z) {
-  const double h2 = norm2(z), d = 0.5 * (b - a), r2 = fma(d, d, h2);
+  const double az = max_abs(z), d0 = 0.5 * (b - a);
+  const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(d0), az));
+  const T zs = shifted(z, -e);
+  const double h2 = norm2(zs), d = ldexp(d0, -e), r2 = fma(d, d, h2);
   jrot<T> R;
   // negligible coupling: no rotation (also for the decoupled padding indices)
-  R.active = h2 > 1e-34 * fabs(a) * fabs(b) && h2 > 0.0 && r2 > 1e-290;
+  R.active = az > 1e-300 && h2 > 1e-34 * fabs(ldexp(a, -e)) * fabs(ldexp(b, -e));
   const double q = rsqrt_nr(R.active ? r2 : 1.0), ad = fabs(d);
   const double c2 = fma(0.5 * ad, q, 0.5), ci = rsqrt_nr(c2);
   const double sg = d >= 0.0 ? 1.0 : -1.0;
-  const double t = sg * m64::fdiv(h2, fma(r2, q, ad));
+  const double t = sg * ldexp(m64::fdiv(h2, fma(r2, q, ad)), e);
   R.c = R.active ? c2 * ci : 1.0;
-  R.s = scaled(conj_of(z), R.active ? 0.5 * sg * q * ci : 0.0);
+  R.s = scaled(conj_of(zs), R.active ? 0.5 * sg * q * ci : 0.0);
   R.a_new = R.active ? a - t : a;
   R.b_new = R.active ? b + t : b;
   return R;
