@@ -454,6 +454,17 @@ __device__ __forceinline__ double row16_prod(double v) {
   v *= dpp_f64<0x140>(v);
   return v;
 }
+// prod (1 + v) - 1 over a row of 16 lanes
+__device__ __forceinline__ double row16_excess(double v) {
+  double o = dpp_f64<0xB1>(v);
+  v = v + fma(v, o, o);
+  o = dpp_f64<0x4E>(v);
+  v = v + fma(v, o, o);
+  o = dpp_f64<0x141>(v);
+  v = v + fma(v, o, o);
+  o = dpp_f64<0x140>(v);
+  return v + fma(v, o, o);
+}
 // Sum over the wavefront, returned wave-uniform to every lane.
 __device__ __forceinline__ double wave_sum_uniform(double v) {
   v = row16_sum(v);
