@@ -365,8 +365,13 @@ __global__ __launch_bounds__(64) void k_eloc(theta_src theta, const uint64_t* __
               P[q] = cmul(P[q], make_double2(fma(-sg[q], tt.x, 1.0), -sg[q] * tt.y));
             }
         }
-        // keep |P| near 1: exact power-of-two rescaling
-        if (j0 & 16)
+        // keep |P| within 2^-64 .. 2^64 (from there sixteen factors of 1e-18 to 1e18 stay in
+        // range): exact power-of-two rescaling of the wave's products once one has left it
+        bool far = false;
+#pragma unroll
+        for (int q = 0; q < S; ++q)
+          far |= (uint32_t)__double2hiint(fmax(fabs(P[q].x), fabs(P[q].y))) - ((1023u - 64u) << 20) > 128u << 20;
+        if (__ballot(far))
 #pragma unroll
           for (int q = 0; q < S; ++q) {
             const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(P[q].x), fabs(P[q].y)));
