@@ -391,7 +391,7 @@ __global__ __launch_bounds__(AB_NT, 4) void k_ar_log_psi16(ar_net d, const uint6
       for (int r = 0; r < 4; ++r) {
         const double x = ar_bit(d, L, lk + 4 * r, min(i, d.N - 1));
         lin[r] += i < d.N ? x * l[r] - fmax(l[r], 0.0) : 0.0;
-        const double e = m64::fexp_neg(l[r]);
+        const double e = m64::fexp_neg0(l[r]);
         q[r] = i < d.N ? q[r] + fma(q[r], e, e) : q[r];
       }
     }
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(AB_NT, 4) void k_ar_eloc16(ar_net d, const uint64_t
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         L.l[(lk + 4 * r) * d.Ns + 16 * nt + li] = l[r];
-        L.x2[(lk + 4 * r) * d.Ns + 16 * nt + li] = 1.0 + m64::fexp_neg(l[r]);
+        L.x2[(lk + 4 * r) * d.Ns + 16 * nt + li] = 1.0 + m64::fexp_neg0(l[r]);
       }
     }
     __syncthreads();
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(AB_NT, 4) void k_ar_eloc16(ar_net d, const uint64_t
               const double lp = acc[j][r], xp = (i == r0[r] || i == r1[r]) ? 1.0 - x : x;
               lin[r] += in ? (xp * lp - fmax(lp, 0.0)) - t : 0.0;
               if (ke > ks) {
-                num[r] *= in ? 1.0 + m64::fexp_neg(lp) : 1.0;
+                num[r] *= in ? 1.0 + m64::fexp_neg0(lp) : 1.0;
                 den[r] *= in ? q : 1.0;
               }
             }

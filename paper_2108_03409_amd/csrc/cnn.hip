@@ -467,7 +467,7 @@ constexpr int EL_F = 16;  // flips per pass: the columns of one matrix-core oper
 // 1 + e^{-2 z~} with z~ = +-z, Re z~ >= 0 (cosh z = e^{z~} (1 + e^{-2 z~}) / 2); zt receives z~
 __device__ __forceinline__ double2 cosh_factor(double2 z, double2& zt) {
   zt = z.x < 0.0 ? make_double2(-z.x, -z.y) : z;
-  const double e = m64::fexp_neg(2.0 * zt.x);
+  const double e = m64::fexp_neg0(2.0 * zt.x);
   double s, c;
   m64::fsincos<false>(-2.0 * zt.y, &s, &c);
   return make_double2(fma(e, c, 1.0), e * s);
