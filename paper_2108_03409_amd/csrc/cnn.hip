@@ -286,7 +286,7 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 4 : 2) void k_cnn_net(
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int c = rt * 16 + lk + 4 * r, p = pt * 16 + li;
-        if (c < C && p < N) A[c * ld + p] = clogcosh_pv<false>(make_double2(re[r], im[r]));
+        if (c < C && p < N) A[c * ld + p] = clogcosh_pv(make_double2(re[r], im[r]));
       }
     }
     __syncthreads();
@@ -311,9 +311,9 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 4 : 2) void k_cnn_net(
           if (c < C && p < N) {
             const double2 z = make_double2(re[j][r], im[j][r]);
             if constexpr (MODE == NET_LOGPSI)
-              lp = cadd(lp, clogcosh<false>(z));
+              lp = cadd(lp, clogcosh(z));
             else
-              G2[c * ld + p] = ctanh<false>(z);
+              G2[c * ld + p] = ctanh(z);
           }
         }
     }
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 4 : 2) void k_cnn_net(
         for (int r = 0; r < 4; ++r) {
           const int c = rt * 16 + lk + 4 * r, p = (pt + j) * 16 + li;
           if (c < C && p < N)
-            A[c * ld + p] = cmul(make_double2(re[j][r], im[j][r]), ctanh<false>(make_double2(zr[r], zi[r])));
+            A[c * ld + p] = cmul(make_double2(re[j][r], im[j][r]), ctanh(make_double2(zr[r], zi[r])));
         }
       }
     }
@@ -469,7 +469,7 @@ __device__ __forceinline__ double2 cosh_factor(double2 z, double2& zt) {
   zt = z.x < 0.0 ? make_double2(-z.x, -z.y) : z;
   const double e = m64::fexp_neg0(2.0 * zt.x);
   double s, c;
-  m64::fsincos<false>(-2.0 * zt.y, &s, &c);
+  m64::fsincos(-2.0 * zt.y, &s, &c);
   return make_double2(fma(e, c, 1.0), e * s);
 }
 
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(EL_NT, 4) void k_cnn_eloc64(cnn_geom g, const uint6
       for (int r = 0; r < 4; ++r) {
         const int c = rt * 16 + lk + 4 * r, p = pt * 16 + li;
         if (c < C && p < N) {
-          const double2 z = make_double2(re[r], im[r]), a = clogcosh_pv<false>(z);
+          const double2 z = make_double2(re[r], im[r]), a = clogcosh_pv(z);
           DA[c * ld + p] = a;
           z1g[c * N + p] = z;
           a1g[c * N + p] = a;
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(EL_NT, 4) void k_cnn_eloc64(cnn_geom g, const uint6
         const int p = y * g.Lx + x;
         const double ds = -2.0 * sig_at(sb, f);
         const double2 z = z1g[c * N + p], w = g.W1[c * kk + t];
-        DA[e] = csub(clogcosh_pv<false>(make_double2(fma(ds, w.x, z.x), fma(ds, w.y, z.y))), a1g[c * N + p]);
+        DA[e] = csub(clogcosh_pv(make_double2(fma(ds, w.x, z.x), fma(ds, w.y, z.y))), a1g[c * N + p]);
       }
       __syncthreads();
       int fy, fx;
@@ -965,7 +965,7 @@ __global__ __launch_bounds__(MH_NT, 4) void k_cnn_mh64(cnn_geom g, int n_chains,
     for (int r = 0; r < 4; ++r) {
       const int ch = lk + 4 * r, p = pt * 16 + li;
       if (ch < C && p < N) {
-        const double2 z = make_double2(re[r], im[r]), a = clogcosh_pv<false>(z);
+        const double2 z = make_double2(re[r], im[r]), a = clogcosh_pv(z);
         P[ch * ld + p] = a;
         Z1[p * C + ch] = z;
         A1[p * C + ch] = a;
@@ -1079,7 +1079,7 @@ __global__ __launch_bounds__(MH_NT, 4) void k_cnn_mh64(cnn_geom g, int n_chains,
       at1 = (y * g.Lx + x) * C + c1;
       const double2 z = Z1[at1], a = A1[at1];
       z1n = make_double2(fma(ds, w1.x, z.x), fma(ds, w1.y, z.y));
-      a1n = clogcosh_pv<false>(z1n);
+      a1n = clogcosh_pv(z1n);
       DAs[t1 * 17 + c1] = csub(a1n, a);
     }
     __syncthreads();
@@ -1156,7 +1156,7 @@ __global__ __launch_bounds__(MH_NT, 4) void k_cnn_mh64(cnn_geom g, int n_chains,
       for (int w = tid; w < g.W; w += MH_NT) s_out[row * g.W + w] = cb[w];
       if (logpsi_out) {
         double2 lp = make_double2(0.0, 0.0);
-        for (int e = tid; e < CN; e += MH_NT) lp = cadd(lp, clogcosh<false>(Z2[e]));
+        for (int e = tid; e < CN; e += MH_NT) lp = cadd(lp, clogcosh(Z2[e]));
         lp = block_sum(lp, red2);
         if (tid == 0) logpsi_out[row] = lp;
       }

@@ -284,11 +284,10 @@ __device__ __forceinline__ double2 clog(double2 z) {
 
 // log cosh z without overflow: with z~ = +-z such that Re z~ >= 0,
 //   log cosh z = z~ - ln 2 + log(1 + e^{-2 z~})   (mod 2 pi i).
-template <bool LIB = true>
 __device__ __forceinline__ double2 clogcosh(double2 z) {
   if (z.x < 0.0) z = make_double2(-z.x, -z.y);
   double e = m64::fexp_neg(2.0 * z.x), s, c;
-  m64::fsincos<LIB>(-2.0 * z.y, &s, &c);
+  m64::fsincos(-2.0 * z.y, &s, &c);
   double er = e * c, ei = e * s;  // e^{-2 z~}
   // log|1 + w| = 0.5 log1p(2 Re w + |w|^2)
   double lr = 0.5 * m64::flog1p(2.0 * er + er * er + ei * ei);
@@ -299,20 +298,18 @@ __device__ __forceinline__ double2 clogcosh(double2 z) {
 // log cosh z on the principal branch of the logarithm (imaginary part in
 // [-pi, pi]); a hidden layer's activation feeds a further linear layer, where
 // a shift by 2 pi i would change the result.
-template <bool LIB = true>
 __device__ __forceinline__ double2 clogcosh_pv(double2 z) {
-  double2 r = clogcosh<LIB>(z);
+  double2 r = clogcosh(z);
   r.y = m64::wrap_2pi(r.y);
   return r;
 }
 
 // tanh z = (1 - e^{-2z})/(1 + e^{-2z}) for Re z >= 0; odd in z.
-template <bool LIB = true>
 __device__ __forceinline__ double2 ctanh(double2 z) {
   bool neg = z.x < 0.0;
   if (neg) z = make_double2(-z.x, -z.y);
   double e = m64::fexp(-2.0 * z.x), s, c;
-  m64::fsincos<LIB>(-2.0 * z.y, &s, &c);
+  m64::fsincos(-2.0 * z.y, &s, &c);
   double2 w = make_double2(e * c, e * s);
   double2 r = cdiv(make_double2(1.0 - w.x, -w.y), make_double2(1.0 + w.x, w.y));
   return neg ? make_double2(-r.x, -r.y) : r;
@@ -321,12 +318,11 @@ __device__ __forceinline__ double2 ctanh(double2 z) {
 // tanh z and the summable log cosh z (clogcosh's branch) from one exponential and one
 // sine / cosine pair: with w = e^{-2 z'}, z' = +-z and Re z' >= 0,
 //   tanh z' = (1 - w) / (1 + w),  log cosh z = z' - log 2 + log(1 + w)
-template <bool LIB = true>
 __device__ __forceinline__ void ctanh_logcosh(double2 z, double2& t, double2& l) {
   const bool neg = z.x < 0.0;
   if (neg) z = make_double2(-z.x, -z.y);
   double e = m64::fexp_neg(2.0 * z.x), s, c;
-  m64::fsincos<LIB>(-2.0 * z.y, &s, &c);
+  m64::fsincos(-2.0 * z.y, &s, &c);
   const double er = e * c, ei = e * s;
   const double2 r = cdiv(make_double2(1.0 - er, -ei), make_double2(1.0 + er, ei));
   t = neg ? make_double2(-r.x, -r.y) : r;

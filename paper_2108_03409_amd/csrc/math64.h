@@ -3,7 +3,7 @@
 // for 155, log 43 for 98, log1p 52 for 135, atan2 64 for 105, remainder by 2 pi 4 for 60).  Polynomials interpolate the reduced
 // functions at Chebyshev nodes (approximation error below 2e-17 of the result);
 // measured against 113-bit arithmetic over 4 million arguments: exp 1.1 ulp, log 0.9, log1p
-// 1.3, atan2 2.2, sine and cosine 1.2e-16 absolute for |x| < 1e5 and 1.7e-16 for |x| < 2^53.  Zeros, infinities and
+// 1.3, atan2 2.2, sine and cosine 1.2e-16 absolute for |x| < 1e5 and from 2^54 on, 1.9e-16 between.  Zeros, infinities and
 // NaN follow the C library.
 // log psi of an RBM (N = 64, N_h = 256, 16 384 samples, theta included) 88.7 -> 76.8 us,
 // CNN log psi (16 x 16, C = 16, k = 4, 1 024 samples) 258 -> 233 us, its local energies
@@ -16,12 +16,14 @@
 #define M64_MANT(x) __builtin_amdgcn_frexp_mant(x)
 #define M64_EXPO(x) __builtin_amdgcn_frexp_exp(x)
 #define M64_RCP(x) __builtin_amdgcn_rcp(x)
+#define M64_MULHI(a, b) __umul64hi(a, b)
 #else
 inline double m64_mant_host(double x) { int e; return std::frexp(x, &e); }
 inline int m64_expo_host(double x) { int e; std::frexp(x, &e); return std::isfinite(x) ? e : 0; }
 #define M64_MANT(x) m64_mant_host(x)
 #define M64_EXPO(x) m64_expo_host(x)
 #define M64_RCP(x) ((double)(1.0f / (float)(x)))
+#define M64_MULHI(a, b) ((unsigned long long)(((unsigned __int128)(a) * (b)) >> 64))
 #endif
 #ifndef M64_FN
 #define M64_FN __host__ __device__ __forceinline__
@@ -80,13 +82,39 @@ M64_FN double fexp_neg(double x) {
   return x != x ? x : v;
 }
 
+// x - n pi/2 and n mod 4 for |x| >= 2^54 (Payne and Hanek's reduction): with |x| = m 2^k, m a
+// 53-bit integer, the bits of 2 / pi above weight 2^(1 - k) give multiples of 4 in |x| 2 / pi;
+// the product with 192 bits from there on, 128 of its bits kept, is right to 2^-123, and the
+// reduced argument, 2^-62 at least, to one rounding.  NaN for an infinite x.
+M64_FN double reduce_big(double x, int* q) {
+  static constexpr unsigned long long two_over_pi[20] = {
+      0xa2f9836e4e441529ull, 0xfc2757d1f534ddc0ull, 0xdb6295993c439041ull, 0xfe5163abdebbc561ull,
+      0xb7246e3a424dd2e0ull, 0x06492eea09d1921cull, 0xfe1deb1cb129a73eull, 0xe88235f52ebb4484ull,
+      0xe99c7026b45f7e41ull, 0x3991d639835339f4ull, 0x9c845f8bbdf9283bull, 0x1ff897ffde05980full,
+      0xef2f118b5a0a6d1full, 0x6d367ecf27cb09b7ull, 0x4f463f669e5fea2dull, 0x7527bac7ebe5f17bull,
+      0x3d0739f78a5292eaull, 0x6bfb5fb11f8d5d08ull, 0x56033046fc7b6babull, 0xf0cfbc209af4361dull,
+  };
+  const int k = M64_EXPO(x) - 53, at = k > 2 ? k - 2 : 0, sh = at & 63;
+  const unsigned long long m = (unsigned long long)(fabs(M64_MANT(x)) * 0x1p53);
+  const unsigned long long* p = two_over_pi + (at >> 6);
+  unsigned long long w[3];
+  for (int i = 0; i < 3; ++i) w[i] = sh ? p[i] << sh | p[i + 1] >> (64 - sh) : p[i];
+  const unsigned long long c2 = M64_MULHI(m, w[2]), lo = m * w[1] + c2;
+  const unsigned long long hi = m * w[0] + M64_MULHI(m, w[1]) + (lo < c2 ? 1 : 0);  // 4 hi.lo / 2^64 = |x| 2 / pi mod 4
+  const long long f = (long long)(hi << 2 | lo >> 62);  // the fraction, in [-1/2, 1/2)
+  int n = (int)(hi >> 62) + (f < 0 ? 1 : 0);
+  const double fh = (double)(f & ~0x7ffll) * 0x1p-64;
+  const double fl = fma((double)(lo << 2), 0x1p-128, (double)(f & 0x7ffll) * 0x1p-64);
+  double r = fma(fh, 0x1.921fb54442d18p+0, fma(fh, 0x1.1a62633145c07p-54, fl * 0x1.921fb54442d18p+0));
+  *q = x < 0.0 ? -n : n;
+  r = x < 0.0 ? -r : r;
+  return fabs(x) < INFINITY ? r : NAN;
+}
+
 // sin and cos of x through r = x - n pi/2, |r| <= pi/4, n = rint(2 x / pi).  x - n P1
 // with P1 = fl(pi/2) is exact (both are multiples of 2^-52 and the difference is below
 // 2), so the remaining error is that of n (pi/2 - P1).  From 1e5 on the rounding of
-// 2 x / pi can be off by an integer, which a second step takes back; LIB: from
-// 2^54 on the library's sincos (its reduction keeps many registers in use); otherwise, as
-// neighbouring arguments are then 4 or more apart, a multiple of pi/2 next to x stands for x.
-template <bool LIB = true>
+// 2 x / pi can be off by an integer, which a second step takes back.
 M64_FN void fsincos(double x, double* sp, double* cp) {
   double n = rint(x * 0.63661977236758134);
   double r = fma(n, -0x1.921fb54442d18p+0, x);
@@ -97,14 +125,8 @@ M64_FN void fsincos(double x, double* sp, double* cp) {
     const double n2 = rint(r * 0.63661977236758134);
     r = fma(n2, -0x1.921fb54442d18p+0, r);
     r = fma(n2, -0x1.1a62633145c07p-54, r);
-    if (!(fabs(x) < 0x1p54)) {
-      if (LIB) {
-        ::sincos(x, sp, cp);
-        return;
-      }
-      r = x - x;  // 0, or NaN for an infinite x
-    }
     q = (int)(n - 4.0 * floor(0.25 * n)) + (int)n2;
+    if (!(fabs(x) < 0x1p54)) r = reduce_big(x, &q);
   }
   const double z = r * r;
   double s = 0x1.5e0b05bff20f2p-33;

@@ -1,5 +1,9 @@
-"""The exponentials of csrc/math64.h, compiled for the host, against extended
-precision.  Bound: 1.5 ulp (the reduced argument and the last two steps round)."""
+"""The exponentials of csrc/math64.h, and its sine and cosine at
+large arguments, compiled for the host, against extended precision (arguments
+reduced with integers where that does not reach).  Bounds: exponential 1.5 ulp (the
+reduced argument and the last two steps round); sine and cosine 2.5 units of 2^-53
+from 1e5 to 2^54, where two of the reduction's sums round near pi / 2, and 1.5 beyond,
+where the reduced argument rounds once."""
 import ctypes
 import math
 import os
@@ -15,6 +19,7 @@ SRC = r"""
 #include "math64.h"
 extern "C" void run(int f, const double* a, double* o, double* p, long n) {
   for (long i = 0; i < n; ++i) switch (f) {
+    case 0: m64::fsincos(a[i], o + i, p + i); break;
     case 1: o[i] = m64::fexp(a[i]); break;
     case 2: o[i] = m64::fexp_neg(a[i]); break;
   }
@@ -40,6 +45,18 @@ def lib(tmp_path_factory):
     return run
 
 
+def _pi(bits):
+    def atan_inv(n):
+        t = s = (1 << bits) // n
+        k = 1
+        while t:
+            t //= n * n
+            k += 2
+            s += -(t // k) if k // 2 % 2 else t // k
+        return s
+    return 4 * (4 * atan_inv(5) - atan_inv(239))
+
+
 def _ulps(got, ref):
     return np.abs(got.astype(np.longdouble) - ref) / np.spacing(np.abs(ref.astype(np.float64)))
 
@@ -63,3 +80,28 @@ def test_exponential_special_values(lib):
     with np.errstate(all="ignore"):
         assert np.array_equal(lib(1, sp), np.exp(sp), equal_nan=True)
         assert np.array_equal(lib(2, sp), np.exp(-np.abs(sp)), equal_nan=True)
+
+
+def test_sine_and_cosine_of_large_arguments(lib):
+    rng = np.random.default_rng(2)
+    x = np.concatenate([2.0 ** rng.uniform(17, 54, 3000), 2.0 ** rng.uniform(54, 1023.9, 3000),
+                        2.0 ** np.arange(17, 1024), [np.finfo(np.float64).max, 6381956970095103.0 * 2.0 ** 797]])
+    x *= np.where(rng.random(x.size) < 0.5, -1.0, 1.0)
+    s, c = lib(0, x)
+    bits, sc = 2400, 64
+    two_pi = 2 * _pi(bits)
+    for v, sv, cv in zip(x, s, c):
+        n, d = v.as_integer_ratio()  # d is a power of two
+        r = ((n << bits) // d) % two_pi
+        q, r = divmod(r, two_pi // 4)
+        # the fraction of the quadrant as the sum of two extended numbers
+        h = r >> (bits - sc)
+        lo = (r - (h << (bits - sc))) >> (bits - 2 * sc)
+        t = np.longdouble(h) / np.longdouble(2 ** sc) + np.longdouble(lo) / np.longdouble(2 ** sc) ** 2
+        S, C = np.sin(t), np.cos(t)
+        rs, rc = ((S, C), (C, -S), (-S, -C), (-C, S))[q & 3]
+        tol = (1.5 if abs(v) >= 2.0 ** 54 else 2.5) * 2.0 ** -53
+        assert abs(sv - rs) <= tol and abs(cv - rc) <= tol, v
+    with np.errstate(all="ignore"):
+        s, c = lib(0, np.array([np.inf, -np.inf, np.nan]))
+    assert np.isnan(s).all() and np.isnan(c).all()
