@@ -215,7 +215,15 @@ M64_FN double fatan2(double y, double x) {
   return (x != x || y != y) ? x + y : a;
 }
 
-// y - 2 pi rint(y / 2 pi) with 2 pi rounded to float64 (as remainder(y, 2 pi)), exact for |y| < 2^50
-M64_FN double wrap_2pi(double y) { return fma(-rint(y * 0.15915494309189535), 6.283185307179586477, y); }
+// remainder(y, 2 pi) with 2 pi rounded to float64: y - 2 pi rint(y / 2 pi), an exact difference
+// for |y| < 2^50.  From 2^30 on, where the rounded quotient can be off by one near its halves,
+// multiples 2^e n of 2 pi, n < 2^48, are taken off first, exactly as well.
+M64_FN double wrap_2pi(double y) {
+  while (fabs(y) >= 0x1p30 && fabs(y) < INFINITY) {
+    const int x = M64_EXPO(y) - 50, e = x > 0 ? x : 0;
+    y = fma(-rint(ldexp(y, -e) * 0.15915494309189535), ldexp(6.283185307179586477, e), y);
+  }
+  return fma(-rint(y * 0.15915494309189535), 6.283185307179586477, y);
+}
 
 }  // namespace m64

@@ -1,9 +1,9 @@
-"""The exponentials of csrc/math64.h, and its sine and cosine at
+"""The exponentials of csrc/math64.h, and its sine, cosine and remainder by 2 pi at
 large arguments, compiled for the host, against extended precision (arguments
 reduced with integers where that does not reach).  Bounds: exponential 1.5 ulp (the
 reduced argument and the last two steps round); sine and cosine 2.5 units of 2^-53
 from 1e5 to 2^54, where two of the reduction's sums round near pi / 2, and 1.5 beyond,
-where the reduced argument rounds once."""
+where the reduced argument rounds once; the remainder is exact."""
 import ctypes
 import math
 import os
@@ -22,6 +22,7 @@ extern "C" void run(int f, const double* a, double* o, double* p, long n) {
     case 0: m64::fsincos(a[i], o + i, p + i); break;
     case 1: o[i] = m64::fexp(a[i]); break;
     case 2: o[i] = m64::fexp_neg(a[i]); break;
+    case 3: o[i] = m64::wrap_2pi(a[i]); break;
   }
 }
 """
@@ -105,3 +106,12 @@ def test_sine_and_cosine_of_large_arguments(lib):
     with np.errstate(all="ignore"):
         s, c = lib(0, np.array([np.inf, -np.inf, np.nan]))
     assert np.isnan(s).all() and np.isnan(c).all()
+
+
+def test_remainder_of_large_arguments(lib):
+    rng = np.random.default_rng(3)
+    y = np.concatenate([2.0 ** rng.uniform(-3, 1023.9, 5000), 2.0 ** np.arange(40, 1024), [np.finfo(np.float64).max]])
+    y *= np.where(rng.random(y.size) < 0.5, -1.0, 1.0)
+    assert np.array_equal(lib(3, y), np.array([math.remainder(v, 6.283185307179586477) for v in y]))
+    with np.errstate(all="ignore"):
+        assert np.isnan(lib(3, np.array([np.inf, -np.inf, np.nan]))).all()
