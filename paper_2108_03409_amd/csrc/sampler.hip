@@ -6,9 +6,9 @@
 //   2 Re(log psi(s') - log psi(s)) = 2 Re(-2 sigma_m alpha_m + LC_m)
 //                                    + sum_j log|1 - sigma_m t_j T_jm|^2.
 // On acceptance t_j follows the tanh addition rule
-// t' = (t - sigma T) / (1 - sigma t T); theta itself is not carried along: it is
-// rebuilt from the spins at the start of every call and, with t, at every
-// recorded sample.
+// t' = (t - sigma T) / (1 - sigma t T).  With flips and exchanges theta is formed from
+// the spins at the start of a call and then follows the accepted moves in registers to its
+// end; every record forms t and log psi anew from it.
 //
 // VMC_PROP_MADE_MIX: each sweep starts with global Metropolis-Hastings steps
 // made by all chains together (mixsampler.hip; the proposals of the next step
@@ -406,6 +406,21 @@ void launch(vmc_ctx* ctx, const sampler_args& a, hipStream_t st) {
   VMC_HIP(hipGetLastError());
 }
 
+// [nc][Nh] theta for the duration of a call, from the context's workspace: up to 1 GiB (what
+// log psi of 65 536 configurations of 1 024 units takes) and within its limit; otherwise
+// NULL, and the kernel forms theta itself
+double2* scratch_theta(vmc_ctx* ctx, int64_t nc, int Nh) {
+  const size_t bytes = ws_round(sizeof(double2) * (size_t)nc * Nh);
+  if (bytes > (size_t)1 << 30 || (ctx->ws_limit && bytes > ctx->ws_limit)) return nullptr;
+  try {
+    ws_reserve(ctx, bytes);
+  } catch (const vmc_error& e) {
+    if (e.code != VMC_ERR_OOM) throw;
+    return nullptr;
+  }
+  return (double2*)ws_take(ctx, bytes);
+}
+
 }  // namespace
 
 void sampler_run(vmc_sampler* S, int64_t n_per_chain, uint64_t* s_out, double2* logpsi_out) {
@@ -444,16 +459,14 @@ void sampler_run(vmc_sampler* S, int64_t n_per_chain, uint64_t* s_out, double2* 
     a.s_out = s_out;
     a.logpsi_out = logpsi_out;
     // theta of the chains' spins by the matrix cores where the kernel's own serial sum over
-    // the sites costs more than a launch (100 sites, 400 units, 1 024 chains: 40 against
-    // 10 us a call); the first call draws its spins in the kernel and keeps that sum
+    // the sites costs more than a launch (a call of 16 proposals, 1 024 chains: 100 sites, 400
+    // units 79 against 66 us; 64 sites, 256 units 55 against 54; 48 sites, 192 units equal; 64
+    // chains of 64 sites and units 38 against 41); the first call draws its spins in the
+    // kernel and keeps that sum
     if (!a.init && m->N >= 48) {
-      if (!S->mix_theta && hipMalloc(&S->mix_theta, sizeof(double2) * (size_t)nc * m->Nh) != hipSuccess) {
-        (void)hipGetLastError();
-        S->mix_theta = nullptr;
-      }
-      if (S->mix_theta) {
-        rbm_theta(m, S->bits, nc, S->mix_theta);
-        a.theta = S->mix_theta;
+      if (double2* theta = scratch_theta(S->ctx, nc, m->Nh)) {
+        rbm_theta(m, S->bits, nc, theta);
+        a.theta = theta;
       }
     }
     launch<true>(S->ctx, a, st);
