@@ -1283,6 +1283,7 @@ std::vector<int> cnn_eloc_units(const vmc_model* m) {
 }
 
 namespace {
+constexpr size_t kEl64Fixed = sizeof(double2) * EL_NW * EL_F + sizeof(int) * EL_NW;  // k_cnn_eloc64's own arrays
 size_t eloc64_lds(const cnn_geom& g) {
   return sizeof(double2) * (size_t)g.C * ((g.N + 1) + std::max(g.N + 1, g.k * g.k * EL_F));
 }
@@ -1292,7 +1293,7 @@ size_t eloc64_lds(const cnn_geom& g) {
 bool eloc64_run(vmc_model* m, vmc_ham* H, const cnn_geom& g, const uint64_t* s, int64_t B, double2* eloc) {
   vmc_ctx* ctx = m->ctx;
   const size_t lds = eloc64_lds(g);
-  if (lds + 4096 > lds_limit()) return false;
+  if (lds + kEl64Fixed > lds_limit()) return false;
   const int ncu = cu_count(ctx), npass = (g.N + EL_F - 1) / EL_F;
   // one work-group per compute unit; a sample's passes are split over several groups while
   // that fills idle units: rounds of groups x (the forward pass, about one pass, + passes)
