@@ -182,24 +182,25 @@ __global__ __launch_bounds__(256, 2) void k_herk_mfma_f32(herk_args a) {
 
   // global -> register staging of one stage: A SK x BM, B SK x BN float2, by buffer
   // loads from the stage's first row: samples past the last read zero (out of the
-  // buffer's range), columns past K read the next row and feed only outputs that are
-  // never written.  Lane addresses are the same in every stage.
+  // buffer's range, which the hardware checks as lane offset against range - scalar
+  // offset, so that the scalar one stops at the range), columns past K read the next row
+  // and feed only outputs that are never written.  Lane addresses are the same in every stage.
   float2 ra[NA], rb[NB];
   const int va = (tid / BM * (int)K + tid % BM) * 8, vb = (tid / BN * (int)K + tid % BN) * 8;
   auto gload = [&](int64_t n0) {
     const int64_t left = max((int64_t)0, (N - n0) * K);  // entries from sample n0 on
-    auto range = [&](int64_t c0) {
-      return __builtin_amdgcn_make_buffer_rsrc((void*)(a.X + n0 * K + c0), 0,
-                                               (int)(uint32_t)min(max((int64_t)0, left - c0) * 8, (int64_t)0xfffffff8),
-                                               0x00027000);
-    };
-    const auto sa = range(row0), sb = range(col0);
+    auto bytes = [&](int64_t c0) { return (uint32_t)min(max((int64_t)0, left - c0) * 8, (int64_t)0xfffffff8); };
+    const uint32_t na = bytes(row0), nb = bytes(col0);
+    const auto sa = __builtin_amdgcn_make_buffer_rsrc((void*)(a.X + n0 * K + row0), 0, (int)na, 0x00027000);
+    const auto sb = __builtin_amdgcn_make_buffer_rsrc((void*)(a.X + n0 * K + col0), 0, (int)nb, 0x00027000);
 #pragma unroll
     for (int r = 0; r < NA; ++r)
-      ra[r] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(sa, va, r * (256 / BM) * (int)K * 8, 0));
+      ra[r] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(
+                                             sa, va, (int)min((uint32_t)(r * (256 / BM) * (int)K * 8), na), 0));
 #pragma unroll
     for (int r = 0; r < NB; ++r)
-      rb[r] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(sb, vb, r * (256 / BN) * (int)K * 8, 0));
+      rb[r] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(
+                                             sb, vb, (int)min((uint32_t)(r * (256 / BN) * (int)K * 8), nb), 0));
   };
   auto sstore = [&](int buf) {
 #pragma unroll

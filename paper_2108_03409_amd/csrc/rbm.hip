@@ -148,8 +148,9 @@ __global__ __launch_bounds__(256, 2) void k_logpsi_mfma(const double2* __restric
   const int64_t n0 = (int64_t)blockIdx.x * 32;
   for (int e = tid; e < 32 * W; e += 256) bits[e] = n0 + e / W < B ? s[n0 * W + e] : 0ull;
   __syncthreads();
-  // entry (site, unit) of the weights; sites past N read zero (out of the buffer's range),
-  // units past N_h the next site's (their log cosh is left out)
+  // entry (site, unit) of the weights; sites past N read zero, units past N_h the next site's
+  // (their log cosh is left out).  The hardware takes a lane's offset as out of range from
+  // (range - scalar offset) on: the scalar one may not pass the range itself
   const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Wt, 0, N * Nh * 16, 0x00027000);
   double2 v[16];
   auto load = [&](int ut, int w) {
@@ -157,7 +158,7 @@ __global__ __launch_bounds__(256, 2) void k_logpsi_mfma(const double2* __restric
 #pragma unroll
     for (int q = 0; q < 16; ++q)
       v[q] = __builtin_bit_cast(double2,
-                                __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, (64 * w + 4 * q) * Nh * 16, 0));
+                                __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, min(64 * w + 4 * q, N) * Nh * 16, 0));
   };
   const int ntile = (Nh + 15) / 16;
 #pragma unroll

@@ -187,8 +187,9 @@ __attribute__((amdgpu_waves_per_eu(TRACK || Q > 7 || (NW == 2 && Q <= 4) ? 2 : 3
     int n2[2];
   };
   // entries of the lane's units in row m of a [n_moves][N_h] table, zero past N_h
-  // (out of the buffer's range: a unit past N_h has t = 0 and T = 0, hence f = 1
-  // and no change)
+  // (out of the buffer's range, which the hardware checks as lane offset against range -
+  // scalar offset, 1024 q being below the range: a unit past N_h has t = 0 and T = 0, hence
+  // f = 1 and no change)
   auto load_row = [&](const double2* tab, int m, double2(&r)[Q]) {
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(tab + (int64_t)m * Nh), 0, Nh * 16, 0x00027000);
 #pragma unroll
