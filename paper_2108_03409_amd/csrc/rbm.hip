@@ -281,6 +281,15 @@ __global__ __launch_bounds__(64) void k_tables(const double2* __restrict__ param
   }
 }
 
+// Entry (unit, move) of the move table T [Nhp][n_moves] (at most 2^23 entries): the unit's row
+// as scalar offset, the move as lane offset, so that a row costs no vector arithmetic
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t table_rsrc(const double2* T, int Nhp, int n_moves) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)T, 0, Nhp * n_moves * 16, 0x00027000);
+}
+__device__ __forceinline__ double2 table_at(__amdgpu_buffer_rsrc_t rsrc, int unit, int n_moves, int m) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(rsrc, m * 16, unit * n_moves * 16, 0));
+}
+
 // Local energies, S samples per wavefront, for move sets shared by all samples
 // (single-spin flips of the TFIM; the kernel also accepts bonds, masked per
 // sample to the anti-aligned ones).  Lanes run over the moves, and every table
@@ -290,10 +299,10 @@ __global__ __launch_bounds__(64) void k_tables(const double2* __restrict__ param
 // power-of-two rescaling, and
 //   E_loc = diag + mel * sum_m exp(-2 sigma_m alpha_m + LC_m + log prod).
 // Bound: float64 vector work, ten instructions per (unit, move).  The padded table and
-// operands need no bounds, and its rows are addressed from scalar registers: N = 64,
-// N_h = 256, 16 384 samples with theta 237 -> 204 us.
-template <int S>
-__global__ __launch_bounds__(64) void k_eloc(theta_src theta, const uint64_t* __restrict__ s,
+// operands need no bounds, and its rows are addressed from scalar registers, U of them in
+// flight: N = 64, N_h = 256, 16 384 samples with theta 237 -> 204 us.
+template <int S, int U>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(U == 16 ? 2 : 1, U == 16 ? 2 : 8))) void k_eloc(theta_src theta, const uint64_t* __restrict__ s,
                                              int64_t B, int N, int W, int Nh, int ham_kind, double J, double h,
                                              const int2* __restrict__ bonds, int n_bonds,
                                              const double2* __restrict__ T, const double2* __restrict__ LC,
@@ -325,6 +334,7 @@ __global__ __launch_bounds__(64) void k_eloc(theta_src theta, const uint64_t* __
     diag[q] = ham_kind == HAM_TFIM ? -J * (double)(n_al - n_anti) : J * (double)(n_al - n_anti);
   }
   __syncthreads();
+  const auto rsrc = table_rsrc(T, Nhp, n_moves);
   const double mel = ham_kind == HAM_TFIM ? -h : 2.0 * J;
   const bool off = ham_kind == HAM_TFIM ? h != 0.0 : J != 0.0;
   double2 acc[S];
@@ -352,14 +362,13 @@ __global__ __launch_bounds__(64) void k_eloc(theta_src theta, const uint64_t* __
       }
       for (int j0 = 0; j0 < Nhp; j0 += 16) {  // T and tl are 0 past N_h
 #pragma unroll
-        for (int jb = j0; jb < j0 + 16; jb += 8) {
-          // eight table loads in flight before the products that use them
-          const double2* Tj = T + jb * n_moves;  // the same row for every lane
-          double2 Tv[8];
+        for (int jb = j0; jb < j0 + 16; jb += U) {
+          double2 Tv[U];  // U rows in flight before the products that use them
 #pragma unroll
-          for (int u = 0; u < 8; ++u) Tv[u] = Tj[u * n_moves + m];
+          for (int u = 0; u < U; ++u) Tv[u] = table_at(rsrc, jb + u, n_moves, m);
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int u = 0; u < 8; ++u)
+          for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int q = 0; q < S; ++q) {
               const double2 tt = cmul(tl[q * Nhp + jb + u], Tv[u]);
@@ -385,8 +394,10 @@ __global__ __launch_bounds__(64) void k_eloc(theta_src theta, const uint64_t* __
       for (int q = 0; q < S; ++q) {
         if (!active[q]) continue;
         double2 lr = cadd(cscale(al, -2.0 * sg[q]), lcm);
-        const double2 lp = clog(P[q]);
-        lr.x += lp.x + (double)e2[q] * 0.69314718055994530942;
+        // log |P| = log of the mantissa + exponent log 2
+        const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(P[q].x), fabs(P[q].y)));
+        const double2 lp = clog(make_double2(ldexp(P[q].x, -e), ldexp(P[q].y, -e)));
+        lr.x += lp.x + (double)(e2[q] + e) * 0.69314718055994530942;
         lr.y += lp.y;
         acc[q] = cadd(acc[q], cscale(cexp(lr), mel));
       }
@@ -715,13 +726,19 @@ void rbm_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, do
       continue;
     }
     const unsigned grid = (unsigned)((nb + S - 1) / S);
-#define ELOC_LAUNCH(SS)                                                                                             \
-  k_eloc<SS><<<grid, 64, lds, ctx->stream>>>(th, s + b0 * m->W, nb, m->N, m->W, m->Nh, H->kind, H->J, H->h,     \
-                                             H->bonds, H->n_bonds, tb.T, tb.LC, tb.alpha, tb.n_moves, Nhp, eloc + b0)
+    // rows of T in flight: eight, and sixteen above 512 units, where the LDS leaves a SIMD two
+    // or three waves (400 sites, 800 units, 4 096 samples 990 against 1 066 us; 100 sites, 400
+    // units 176 against 170)
+#define ELOC_LAUNCH(SS, UU)                                                                                        \
+  k_eloc<SS, UU><<<grid, 64, lds, ctx->stream>>>(th, s + b0 * m->W, nb, m->N, m->W, m->Nh, H->kind, H->J, H->h,    \
+                                                 H->bonds, H->n_bonds, tb.T, tb.LC, tb.alpha, tb.n_moves, Nhp,     \
+                                                 eloc + b0)
     if (S == 4)
-      ELOC_LAUNCH(4);
+      ELOC_LAUNCH(4, 8);
+    else if (Nhp <= 512)
+      ELOC_LAUNCH(1, 8);
     else
-      ELOC_LAUNCH(1);
+      ELOC_LAUNCH(1, 16);
 #undef ELOC_LAUNCH
     VMC_HIP(hipGetLastError());
   }
