@@ -411,8 +411,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(U == 16 ? 2 
 
 // Fused enumeration + evaluation + reduction of E_loc, one wave per sample, for
 // move sets that depend on the sample (exchanges of anti-aligned bonds).
+// Bound: the table reads' latency and float64 vector work.  U rows and operands are in
+// flight before their products; 4 096 samples, ring of 64 sites: 256 units 75 us with eight,
+// 78 with sixteen, 600 units 161 and 141, 1 024 units 318 and 287 (reads interleaved by the
+// compiler, about eight in flight: 78, 178 and 379).
 // LDS: t_j (Nh complex) and the compacted move list (<= n_moves ints).
-__global__ __launch_bounds__(64) void k_eloc_compact(theta_src theta, const uint64_t* __restrict__ s,
+template <int U>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(U == 16 ? 2 : 1, U == 16 ? 2 : 8))) void k_eloc_compact(theta_src theta, const uint64_t* __restrict__ s,
                                              int64_t B, int N, int W, int Nh, int ham_kind, double J, double h,
                                              const int2* __restrict__ bonds, int n_bonds,
                                              const double2* __restrict__ T, const double2* __restrict__ LC,
@@ -434,6 +439,7 @@ __global__ __launch_bounds__(64) void k_eloc_compact(theta_src theta, const uint
     tpm[Nhp + j] = tj;
   }
 
+  const auto rsrc = table_rsrc(T, Nhp, n_moves);
   // diagonal element: coupling * (n_aligned - n_anti), exact integer count
   int n_al = 0;
   for (int b = lane; b < n_bonds; b += 64) {
@@ -484,16 +490,18 @@ __global__ __launch_bounds__(64) void k_eloc_compact(theta_src theta, const uint
       const double2* st = tpm + (up ? Nhp : 0);  // sigma t of this slot's spin
       double2 P = make_double2(1.0, 0.0);
       int e2 = 0;
-      const double2* Tm = T + m;  // column m; rows n_moves apart (fewer than 2^31 entries)
       for (int j0 = 0; j0 < Nhp; j0 += 16) {
 #pragma unroll
-        for (int jb = j0; jb < j0 + 16; jb += 8) {
-          double2 Tv[8];  // eight table loads in flight before their products
+        for (int jb = j0; jb < j0 + 16; jb += U) {
+          double2 Tv[U], tv[U];  // U rows and operands in flight before their products
 #pragma unroll
-          for (int u = 0; u < 8; ++u) Tv[u] = Tm[(jb + u) * n_moves];
+          for (int u = 0; u < U; ++u) Tv[u] = table_at(rsrc, jb + u, n_moves, m);
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const double2 tt = cmul(st[jb + u], Tv[u]);  // sigma t_j T_jm
+          for (int u = 0; u < U; ++u) tv[u] = st[jb + u];
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const double2 tt = cmul(tv[u], Tv[u]);  // sigma t_j T_jm
             P = cmul(P, make_double2(1.0 - tt.x, -tt.y));
           }
         }
@@ -719,9 +727,17 @@ void rbm_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, do
     const int64_t nb = std::min(chunk, B - b0);
     const theta_src th = take_theta(m, s + b0 * m->W, nb, theta);
     if (move_kind == 1) {
-      k_eloc_compact<<<(unsigned)nb, 64, lds1, ctx->stream>>>(th, s + b0 * m->W, nb, m->N, m->W, m->Nh, H->kind,
-                                                              H->J, H->h, H->bonds, H->n_bonds, tb.T, tb.LC, tb.alpha,
-                                                              tb.n_moves, Nhp, eloc + b0);
+      // rows of T in flight: eight, and sixteen above 256 units, where the LDS rather than the
+      // registers limits the waves and the reads' latency shows
+#define COMPACT_LAUNCH(UU)                                                                                          \
+  k_eloc_compact<UU><<<(unsigned)nb, 64, lds1, ctx->stream>>>(th, s + b0 * m->W, nb, m->N, m->W, m->Nh, H->kind,    \
+                                                              H->J, H->h, H->bonds, H->n_bonds, tb.T, tb.LC,        \
+                                                              tb.alpha, tb.n_moves, Nhp, eloc + b0)
+      if (Nhp <= 256)
+        COMPACT_LAUNCH(8);
+      else
+        COMPACT_LAUNCH(16);
+#undef COMPACT_LAUNCH
       VMC_HIP(hipGetLastError());
       continue;
     }
