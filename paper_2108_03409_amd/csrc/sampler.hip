@@ -63,13 +63,16 @@ struct sampler_args {
 // registers allow (20 x 20: 11.1 ms for 4 sweeps instead of 12.1 with two); the
 // two-wave groups of few chains are held to two, without which the dispatcher
 // leaves three on some SIMDs and one on others (Heisenberg 10 x 10: 0.92 instead of 0.79 ms).
+// Eight slots with TRACK have one wave per SIMD, whose 512 registers hold them: held to two
+// they kept 84 of theirs in scratch memory (64 sites, flips, 512 units, 4 096 chains x 2
+// sweeps 1.10 instead of 0.64 ms; 1 024 units, 1 024 chains, one sweep 0.40 instead of 0.23).
 // 20 x 20, N_h = 800, 4 096 chains: 8.25 -> 1.8 ms a sweep; Heisenberg 10 x 10,
 // N_h = 400, 1 024 chains x 8 sweeps 1.13 -> 0.75 ms, 4 096 chains x 4 sweeps
 // 2.36 -> 1.0 ms (theta in LDS, rows of T and D per proposal, step tables in LDS,
 // one wave of 16 slots per chain above 512 units before).
 template <int Q, int NW, bool TRACK>
 __global__ __launch_bounds__(64 * NW)
-__attribute__((amdgpu_waves_per_eu(TRACK || Q > 7 || (NW == 2 && Q <= 4) ? 2 : 3,
+__attribute__((amdgpu_waves_per_eu(TRACK && Q > 7 ? 1 : TRACK || Q > 7 || (NW == 2 && Q <= 4) ? 2 : 3,
                                    NW == 2 && (TRACK || Q <= 4) ? 2 : 8))) void k_metropolis(sampler_args a) {
   __shared__ uint64_t cbs[NW][64];  // chain configuration, W <= 64 words (one copy per wave)
   __shared__ double pm_s[2][NW];  // partial ratios of the waves, alternating over the exchanges
