@@ -798,7 +798,13 @@ void ar_set_params(vmc_model* m) {
 void ar_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* out) {
   const ar_net d = net_of(m);
   const size_t lw = sizeof(double) * (d.w_doubles() + (d.N + 2) / 2 + (size_t)AB_WAVES * AB * (d.W + d.Hs));
-  if (d.N <= 512 && lw <= kArBatchLds) {
+  // few configurations: a group each (a batch's wave goes through all sites on its own while
+  // most of the chip idles).  Both cost the same near 1 000 + 50 N configurations up to 160 sites,
+  // where the general kernel's time per configuration stops growing with N: 10 sites, 8 units,
+  // 1 024 configurations 16.4 against 17.1 us; 50, 29: 1 024 18 against 26, 8 192 35 against 26;
+  // 128, 32: 4 096 31 against 38, 12 288 58 against 39
+  const bool many = B >= 1024 + 48 * (int64_t)std::min(d.N, 160);
+  if (many && d.N <= 512 && lw <= kArBatchLds) {
     batch_allow(k_ar_log_psi16, lw);
     k_ar_log_psi16<<<batch_groups(m->ctx, (B + AB_WAVES - 1) / AB_WAVES, lw), AB_NT, lw, m->ctx->stream>>>(d, s, B, out);
     VMC_HIP(hipGetLastError());

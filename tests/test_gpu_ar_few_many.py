@@ -1,0 +1,35 @@
+"""Autoregressive log psi on both sides of the number of configurations from which
+a wave takes 16 of them: the same values against the oracle, batches that end
+inside a block among them."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import arnqs
+from gpu_common import DEV, dev_bits, flush
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2108_03409_amd import nqsvmc as V  # noqa: E402
+
+
+# edges of the batch kernel's tiles and words; the last ones do not fit it. Float64 sums of
+# N + N H terms: 1e-12 as in the other parity tests
+@pytest.mark.parametrize("N,H", [(2, 1), (3, 1), (15, 16), (16, 17), (33, 17), (64, 50), (65, 66), (161, 5), (96, 120)])
+@pytest.mark.parametrize("off", [-1, 0, 21])
+def test_log_psi_at_the_line(N, H, off):
+    B = 1024 + 48 * min(N, 160) + off
+    flush(f"ar log psi N={N} H={H} B={B}")
+    ctx = V.Context(0)
+    th = si.ar_params(N, H, seed=N + H, std=0.4)
+    m = V.Model.autoregressive(ctx, N, H)
+    m.set_params(torch.from_numpy(th).to(DEV))
+    x = si.random_bits(B, N, seed=N)
+    lp = m.log_psi(dev_bits(si.pack_bits(x))).cpu().numpy()
+    ref = arnqs.log_psi(th, x, N, H)
+    assert np.all(lp.imag == 0.0)
+    assert np.max(np.abs(lp.real - ref)) < 1e-12 * max(1.0, np.abs(ref).max())
