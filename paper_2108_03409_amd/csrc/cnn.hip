@@ -9,12 +9,19 @@
 //                  work-group per sample, activations in LDS, the convolutions
 //                  as matrix products on the float64 matrix cores; both layers
 //                  recomputed per sample (no activations stored between calls)
-//   k_cnn_eloc     local energies of the TFIM: for a flip of site s only the
-//                  k x k layer-1 positions p with p + t = s change, and only the
-//                  (2k-1) x (2k-1) layer-2 positions that read them, so each
-//                  connected configuration costs C*C*k^4 complex multiply-adds
-//                  instead of a full evaluation (requires Lx, Ly >= 2k - 1;
-//                  smaller tori re-evaluate layer 2 in full per slot).
+//   k_cnn_forward  log psi of networks too small for those products
+//   k_cnn_eloc64   local energies of the TFIM on tori of at least 2k - 1 sites a
+//                  side: for a flip of site s only the k x k layer-1 positions p
+//                  with p + t = s change, and only the (2k-1) x (2k-1) layer-2
+//                  positions that read them, so each connected configuration
+//                  costs C*C*k^4 complex multiply-adds instead of a full
+//                  evaluation; 16 flips at a time as matrix products
+//   k_cnn_eloc     the same without matrix products, where a sample does not fit
+//                  k_cnn_eloc64's LDS or its scratch the workspace limit;
+//                  smaller tori re-evaluate layer 2 in full per slot
+//   k_cnn_mh64     Metropolis chains, the window's change of a proposal as a
+//                  matrix product (up to 16 channels and 4 x 4 taps)
+//   k_cnn_metropolis  the chains of larger networks
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -219,6 +226,26 @@ __device__ __forceinline__ void conv_tiles(const cnn_geom& g, const double2* __r
     }
 }
 
+// log psi, a work-group per sample and a thread per output at a time, for networks that would
+// fill little of the matrix cores' operands (net_direct).  LDS: a1 [C][N], four partial sums.
+// Bound: latency, and index arithmetic with every term.
+__global__ __launch_bounds__(256) void k_cnn_forward(cnn_geom g, const uint64_t* __restrict__ s, int64_t B,
+                                                     double2* __restrict__ logpsi) {
+  extern __shared__ double2 sm[];
+  const int64_t b = blockIdx.x;
+  if (b >= B) return;
+  const int CN = g.C * g.N;
+  double2* a1 = sm;
+  double2* red = sm + CN;
+  const uint64_t* sb = s + b * g.W;
+  for (int e = threadIdx.x; e < CN; e += 256) a1[e] = clogcosh_pv(z1_at(g, sb, e / g.N, e % g.N));
+  __syncthreads();
+  double2 acc = make_double2(0.0, 0.0);
+  for (int e = threadIdx.x; e < CN; e += 256) acc = cadd(acc, clogcosh(z2_at(g, a1, e / g.N, e % g.N)));
+  acc = block_sum(acc, red);
+  if (threadIdx.x == 0) logpsi[b] = acc;
+}
+
 constexpr int NET_NT = 512;
 constexpr int NET_NW = NET_NT / 64;
 constexpr int NP = 2;  // tiles of a wave that share an operand
@@ -249,7 +276,7 @@ enum { NET_LOGPSI = 0, NET_ROWS = 1, NET_VJP = 2 };
 // 1 024 samples, 16 x 16, C = 16, k = 4: log psi 1.53 -> 0.21 ms, O_k (complex64)
 // 7.92 -> 0.60 ms, reverse-mode product 7.86 -> 0.66 ms.
 template <int MODE, typename OutT>
-__global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 4 : 2) void k_cnn_net(
+__global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
     cnn_geom g, const uint64_t* __restrict__ s, int64_t B, int64_t K, OutT* __restrict__ O,
     const double2* __restrict__ gv, double2* __restrict__ part, double2* __restrict__ logpsi) {
   extern __shared__ double2 sm[];
@@ -1214,6 +1241,18 @@ void cnn_set_params(vmc_model* m) {
 }
 
 namespace {
+// Networks whose log psi takes less time output by output than as matrix products: one or two
+// channels, and samples of at most 256 outputs (one per thread) of which the products, padded
+// to 16 channels x 4 input channels x 32 positions, would use less than four elevenths; of few
+// samples, where an output's serial sum shows, only those of at most 32 weights per input
+// channel.  1 024 samples: 16 x 16, C = 1, k = 4 30 against 76 us, C = 2 52 against 77; 7 x 7,
+// C = 5, k = 3 37 against 48; on the other side 16 x 16, C = 4, k = 4 1.6 times, 5 x 5, C = 8,
+// k = 4 1.2 times as long output by output.  16 samples: 5 x 5, C = 4, k = 4 28 against 24 us.
+bool net_direct(const cnn_geom& g, int64_t B) {
+  const int64_t used = (int64_t)g.C * g.C * g.N, padded = 16ll * g.RT * 4 * g.KS * ((g.N + 31) / 32 * 32);
+  return g.C <= 2 || (g.C * g.N <= 256 && 4 * padded >= 11 * used && (B >= 512 || g.C * g.k * g.k <= 32));
+}
+
 size_t net_lds(const cnn_geom& g, int mode) {
   return sizeof(double2) * (size_t)(mode == NET_LOGPSI ? 1 : 2) * g.C * (g.N + 1);
 }
@@ -1221,6 +1260,13 @@ size_t net_lds(const cnn_geom& g, int mode) {
 
 void cnn_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
   const cnn_geom g = geom(m);
+  if (net_direct(g, B)) {
+    const size_t lds = sizeof(double2) * ((size_t)g.C * g.N + 4);
+    allow_lds(k_cnn_forward, lds);
+    k_cnn_forward<<<(unsigned)B, 256, lds, m->ctx->stream>>>(g, s, B, logpsi);
+    VMC_HIP(hipGetLastError());
+    return;
+  }
   const size_t lds = net_lds(g, NET_LOGPSI);
   auto k = k_cnn_net<NET_LOGPSI, double2>;
   allow_lds(k, lds);
