@@ -5,11 +5,11 @@
 // with p + t the periodic shift of position p by tap t = (dy, dx).
 //
 // Kernels:
-//   k_cnn_net      log psi, O_k rows or the reverse-mode product: one 512-thread
+//   k_cnn_net      log psi, O_k rows or the reverse-mode product: one
 //                  work-group per sample, activations in LDS, the convolutions
 //                  as matrix products on the float64 matrix cores; both layers
 //                  recomputed per sample (no activations stored between calls)
-//   k_cnn_forward  log psi of networks too small for those products
+//   k_cnn_forward  log psi of small networks, output by output
 //   k_cnn_eloc64   local energies of the TFIM on tori of at least 2k - 1 sites a
 //                  side: for a flip of site s only the k x k layer-1 positions p
 //                  with p + t = s change, and only the (2k-1) x (2k-1) layer-2
@@ -227,7 +227,7 @@ __device__ __forceinline__ void conv_tiles(const cnn_geom& g, const double2* __r
 }
 
 // log psi, a work-group per sample and a thread per output at a time, for networks that would
-// fill little of the matrix cores' operands (net_direct).  LDS: a1 [C][N], four partial sums.
+// fill little of the matrix cores' operands.  LDS: a1 [C][N], four partial sums.
 // Bound: latency, and index arithmetic with every term.
 __global__ __launch_bounds__(256) void k_cnn_forward(cnn_geom g, const uint64_t* __restrict__ s, int64_t B,
                                                      double2* __restrict__ logpsi) {
@@ -246,8 +246,7 @@ __global__ __launch_bounds__(256) void k_cnn_forward(cnn_geom g, const uint64_t*
   if (threadIdx.x == 0) logpsi[b] = acc;
 }
 
-constexpr int NET_NT = 512;
-constexpr int NET_NW = NET_NT / 64;
+constexpr int NET_NT = 512;  // threads of a sample's work-group, at most (net_threads)
 constexpr int NP = 2;  // tiles of a wave that share an operand
 enum { NET_LOGPSI = 0, NET_ROWS = 1, NET_VJP = 2 };
 
@@ -275,12 +274,13 @@ enum { NET_LOGPSI = 0, NET_ROWS = 1, NET_VJP = 2 };
 // arithmetic and serial sums.
 // 1 024 samples, 16 x 16, C = 16, k = 4: log psi 1.53 -> 0.21 ms, O_k (complex64)
 // 7.92 -> 0.60 ms, reverse-mode product 7.86 -> 0.66 ms.
-template <int MODE, typename OutT>
-__global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
+template <int MODE, int NT, typename OutT>
+__global__ __launch_bounds__(NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
     cnn_geom g, const uint64_t* __restrict__ s, int64_t B, int64_t K, OutT* __restrict__ O,
     const double2* __restrict__ gv, double2* __restrict__ part, double2* __restrict__ logpsi) {
+  constexpr int NW = NT / 64;
   extern __shared__ double2 sm[];
-  __shared__ double2 red[NET_NW];
+  __shared__ double2 red[NW];
   const int C = g.C, N = g.N, ld = N + 1, kk = g.k * g.k;
   double2* A = sm;
   double2* G2 = sm + C * ld;
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
       }
     };
     __syncthreads();  // the previous sample's last LDS reads are done
-    for (int u = wave; u < g.RT * PT; u += NET_NW) {
+    for (int u = wave; u < g.RT * PT; u += NW) {
       const int rt = u / PT, pt = u - rt * PT;
       doublex4 re, im;
       z1_tile(g, sb, rt, pt, lane, re, im);
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
     }
     __syncthreads();
     double2 lp = make_double2(0.0, 0.0);
-    for (int u = wave; u < g.RT * PP; u += NET_NW) {
+    for (int u = wave; u < g.RT * PP; u += NW) {
       const int rt = u / PP, pt = NP * (u - rt * PP);
       doublex4 re[NP], im[NP];
 #pragma unroll
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
       __syncthreads();
       if (tid == 0) {
         double2 t = make_double2(0.0, 0.0);
-        for (int w = 0; w < NET_NW; ++w) t = cadd(t, red[w]);
+        for (int w = 0; w < NW; ++w) t = cadd(t, red[w]);
         logpsi[b] = t;
       }
       continue;
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
     __syncthreads();
     // dW2: two tiles of 16 columns (c', t) share the rows g2
     const int CT = (C * kk + 15) / 16, CP = (CT + NP - 1) / NP;
-    for (int u = wave; u < g.RT * CP; u += NET_NW) {
+    for (int u = wave; u < g.RT * CP; u += NW) {
       const int rt = u / CP, ct = NP * (u - rt * CP);
       const double2* arow = G2 + min(rt * 16 + li, C - 1) * ld;
       const double2* brow[NP];
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
           if (c < C && n < C * kk) put(off_W2 + (int64_t)c * C * kk + n, make_double2(re[j][r], im[j][r]));
         }
     }
-    for (int c = wave; c < C; c += NET_NW) {
+    for (int c = wave; c < C; c += NW) {
       double2 acc = make_double2(0.0, 0.0);
       for (int p = lane; p < N; p += 64) acc = cadd(acc, G2[c * ld + p]);
       acc = wave_sum(acc);
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
     }
     __syncthreads();  // a1 is no longer read
     // g1 = tanh(z1) d log psi / d a1 -> A
-    for (int u = wave; u < g.RT * PP; u += NET_NW) {
+    for (int u = wave; u < g.RT * PP; u += NW) {
       const int rt = u / PP, pt = NP * (u - rt * PP);
       doublex4 re[NP], im[NP];
       for (int j = 0; j < NP; ++j) re[j] = im[j] = doublex4{0.0, 0.0, 0.0, 0.0};
@@ -437,9 +437,9 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
     // the waves and the partial sums in G2 allow), added in a fixed order
     const int TT = (kk + 15) / 16, nt = g.RT * TT;
     int ns = 1;
-    while (ns < NET_NW && 2 * ns * nt * 256 <= C * ld) ns *= 2;
+    while (ns < NW && 2 * ns * nt * 256 <= C * ld) ns *= 2;
     const int per = ((N + ns - 1) / ns + 3) / 4 * 4;
-    for (int u = wave; u < nt * ns; u += NET_NW) {
+    for (int u = wave; u < nt * ns; u += NW) {
       const int tile = u / ns, z = u - tile * ns, rt = tile / TT, t0 = 16 * (tile - rt * TT);
       const double2* arow = A + min(rt * 16 + li, C - 1) * ld;
       const int t = min(t0 + li, kk - 1), dy = t / g.k, dx = t - dy * g.k;
@@ -467,7 +467,7 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
           put(c * kk + t0 + li, make_double2(re[r], im[r]));
       }
     }
-    for (int c = wave; c < C; c += NET_NW) {
+    for (int c = wave; c < C; c += NW) {
       double2 acc = make_double2(0.0, 0.0);
       for (int p = lane; p < N; p += 64) acc = cadd(acc, A[c * ld + p]);
       acc = wave_sum(acc);
@@ -475,7 +475,7 @@ __global__ __launch_bounds__(NET_NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
     }
     if (ns > 1) {
       __syncthreads();
-      for (int e = tid; e < nt * 256; e += NET_NT) {
+      for (int e = tid; e < nt * 256; e += NT) {
         const int tile = e >> 8, rt = tile / TT, c = rt * 16 + ((e >> 4) & 15), t = 16 * (tile - rt * TT) + (e & 15);
         if (c < C && t < kk) {
           double2 acc = make_double2(0.0, 0.0);
@@ -1241,16 +1241,16 @@ void cnn_set_params(vmc_model* m) {
 }
 
 namespace {
-// Networks whose log psi takes less time output by output than as matrix products: one or two
-// channels, and samples of at most 256 outputs (one per thread) of which the products, padded
-// to 16 channels x 4 input channels x 32 positions, would use less than four elevenths; of few
-// samples, where an output's serial sum shows, only those of at most 32 weights per input
-// channel.  1 024 samples: 16 x 16, C = 1, k = 4 30 against 76 us, C = 2 52 against 77; 7 x 7,
-// C = 5, k = 3 37 against 48; on the other side 16 x 16, C = 4, k = 4 1.6 times, 5 x 5, C = 8,
-// k = 4 1.2 times as long output by output.  16 samples: 5 x 5, C = 4, k = 4 28 against 24 us.
-bool net_direct(const cnn_geom& g, int64_t B) {
-  const int64_t used = (int64_t)g.C * g.C * g.N, padded = 16ll * g.RT * 4 * g.KS * ((g.N + 31) / 32 * 32);
-  return g.C <= 2 || (g.C * g.N <= 256 && 4 * padded >= 11 * used && (B >= 512 || g.C * g.k * g.k <= 32));
+// Threads of a sample's work-group: two or four waves where layer 2 has as many units (or O_k
+// has one channel), so that small samples run several groups for each one of eight waves, most
+// of which would idle; all eight for few samples, where the latency counts, and for larger
+// ones, of which the LDS holds two or three.  8 192 samples, 7 x 7, C = 5, k = 3, log psi 258
+// us with eight waves, 150 with two; O_k of 4 096 samples 5 x 7, C = 5, k = 3 273 and 156; 16 x
+// 16, C = 8, k = 1 577 with eight, 798 with two.
+int net_threads(const cnn_geom& g, int64_t B, bool rows) {
+  const int u = g.RT * ((g.N + 31) / 32);
+  if (B < 512) return NET_NT;
+  return u <= 2 || (rows && g.C == 1) ? 128 : u <= 4 ? 256 : NET_NT;
 }
 
 size_t net_lds(const cnn_geom& g, int mode) {
@@ -1260,7 +1260,11 @@ size_t net_lds(const cnn_geom& g, int mode) {
 
 void cnn_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
   const cnn_geom g = geom(m);
-  if (net_direct(g, B)) {
+  // output by output: one or two channels, which would use a 64th or a 16th of the products (1
+  // 024 samples, 16 x 16, k = 4: C = 1 30 against 76 us, C = 2 52 against 77), and few samples
+  // of an output a thread whose serial sum is short (16 samples, 5 x 5, C = 9, k = 1 19 against
+  // 24 us; 5 x 5, C = 4, k = 4 28 against 24)
+  if (g.C <= 2 || (B < 512 && g.C * g.N <= 256 && g.C * g.k * g.k <= 32)) {
     const size_t lds = sizeof(double2) * ((size_t)g.C * g.N + 4);
     allow_lds(k_cnn_forward, lds);
     k_cnn_forward<<<(unsigned)B, 256, lds, m->ctx->stream>>>(g, s, B, logpsi);
@@ -1268,31 +1272,47 @@ void cnn_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
     return;
   }
   const size_t lds = net_lds(g, NET_LOGPSI);
-  auto k = k_cnn_net<NET_LOGPSI, double2>;
-  allow_lds(k, lds);
-  k<<<(unsigned)B, NET_NT, lds, m->ctx->stream>>>(g, s, B, m->K, nullptr, nullptr, nullptr, logpsi);
-  VMC_HIP(hipGetLastError());
+  auto run = [&](auto k, int nt) {
+    allow_lds(k, lds);
+    k<<<(unsigned)B, nt, lds, m->ctx->stream>>>(g, s, B, m->K, nullptr, nullptr, nullptr, logpsi);
+    VMC_HIP(hipGetLastError());
+  };
+  switch (net_threads(g, B, false)) {
+    case 128: return run(k_cnn_net<NET_LOGPSI, 128, double2>, 128);
+    case 256: return run(k_cnn_net<NET_LOGPSI, 256, double2>, 256);
+    default: return run(k_cnn_net<NET_LOGPSI, NET_NT, double2>, NET_NT);
+  }
 }
 
-void cnn_grad(vmc_model* m, const uint64_t* s, int64_t B, void* O, int dtype) {
+namespace {
+template <typename OutT>
+void grad_rows(vmc_model* m, const uint64_t* s, int64_t B, OutT* O) {
   const cnn_geom g = geom(m);
   const size_t lds = net_lds(g, NET_ROWS);
-  if (dtype == VMC_DT_C128) {
-    auto k = k_cnn_net<NET_ROWS, double2>;
+  auto run = [&](auto k, int nt) {
     allow_lds(k, lds);
-    k<<<(unsigned)B, NET_NT, lds, m->ctx->stream>>>(g, s, B, m->K, (double2*)O, nullptr, nullptr, nullptr);
-  } else {
-    auto k = k_cnn_net<NET_ROWS, float2>;
-    allow_lds(k, lds);
-    k<<<(unsigned)B, NET_NT, lds, m->ctx->stream>>>(g, s, B, m->K, (float2*)O, nullptr, nullptr, nullptr);
+    k<<<(unsigned)B, nt, lds, m->ctx->stream>>>(g, s, B, m->K, O, nullptr, nullptr, nullptr);
+    VMC_HIP(hipGetLastError());
+  };
+  switch (net_threads(g, B, true)) {
+    case 128: return run(k_cnn_net<NET_ROWS, 128, OutT>, 128);
+    case 256: return run(k_cnn_net<NET_ROWS, 256, OutT>, 256);
+    default: return run(k_cnn_net<NET_ROWS, NET_NT, OutT>, NET_NT);
   }
-  VMC_HIP(hipGetLastError());
+}
+}  // namespace
+
+void cnn_grad(vmc_model* m, const uint64_t* s, int64_t B, void* O, int dtype) {
+  if (dtype == VMC_DT_C128)
+    grad_rows(m, s, B, (double2*)O);
+  else
+    grad_rows(m, s, B, (float2*)O);
 }
 
 void cnn_vjp_partial(vmc_model* m, const uint64_t* s, int64_t B, const double2* gv, int groups, double2* part) {
   const cnn_geom g = geom(m);
   const size_t lds = net_lds(g, NET_VJP);
-  auto k = k_cnn_net<NET_VJP, double2>;
+  auto k = k_cnn_net<NET_VJP, NET_NT, double2>;
   allow_lds(k, lds);
   k<<<(unsigned)groups, NET_NT, lds, m->ctx->stream>>>(g, s, B, m->K, nullptr, gv, part, nullptr);
   VMC_HIP(hipGetLastError());
