@@ -1241,16 +1241,16 @@ void cnn_set_params(vmc_model* m) {
 }
 
 namespace {
-// Threads of a sample's work-group: two or four waves where layer 2 has as many units (or O_k
-// has one channel), so that small samples run several groups for each one of eight waves, most
+// Threads of a sample's work-group: two or four waves where layer 2 has as many units (two for
+// O_k of one channel up to 256 sites), so that small samples run several groups for each one of eight waves, most
 // of which would idle; all eight for few samples, where the latency counts, and for larger
 // ones, of which the LDS holds two or three.  8 192 samples, 7 x 7, C = 5, k = 3, log psi 258
 // us with eight waves, 150 with two; O_k of 4 096 samples 5 x 7, C = 5, k = 3 273 and 156; 16 x
-// 16, C = 8, k = 1 577 with eight, 798 with two.
+// 16, C = 8, k = 1 577 with eight, 798 with two; 64 x 64, C = 1, k = 3, 1 024 samples 2.8 and 5.2 ms.
 int net_threads(const cnn_geom& g, int64_t B, bool rows) {
   const int u = g.RT * ((g.N + 31) / 32);
   if (B < 512) return NET_NT;
-  return u <= 2 || (rows && g.C == 1) ? 128 : u <= 4 ? 256 : NET_NT;
+  return u <= 2 || (rows && g.C == 1 && u <= 8) ? 128 : u <= 4 ? 256 : NET_NT;
 }
 
 size_t net_lds(const cnn_geom& g, int mode) {
