@@ -256,6 +256,75 @@ __global__ __launch_bounds__(AR_NT) void k_ar_grad(const uint64_t* __restrict__ 
   }
 }
 
+// O_k with the weights in LDS and a configuration per wave, for networks that fit 64 KB: a
+// wave writes whole rows and needs no other wave.  Bound: the serial sums of its hidden units.
+template <typename OutT>
+__global__ __launch_bounds__(AR_NT) void k_ar_grad_w(const uint64_t* __restrict__ s, int64_t B, int N, int H, int W,
+                                                     const double* __restrict__ W1mT,
+                                                     const double* __restrict__ W2t, const double* __restrict__ b1,
+                                                     const double* __restrict__ b2, const int2* __restrict__ idx,
+                                                     int64_t r1, int64_t r2, int64_t r3, int64_t K,
+                                                     OutT* __restrict__ O) {
+  extern __shared__ double lds[];
+  double* W1s = lds;          // [N][H]
+  double* W2s = W1s + N * H;  // [H][N]
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double* x = W2s + H * N + wave * (2 * N + 2 * H);
+  double* gl = x + N;   // logits, then s_i - sigmoid(l_i)
+  double* hh = gl + N;  // ReLU(a), with a kept as the sign of the gate below
+  double* gh = hh + H;
+  for (int e = threadIdx.x; e < N * H; e += AR_NT) {
+    W1s[e] = W1mT[e];
+    W2s[e] = W2t[e];
+  }
+  __syncthreads();
+  for (int64_t b = (int64_t)blockIdx.x * AR_WAVES + wave; b < B; b += (int64_t)gridDim.x * AR_WAVES) {
+    const uint64_t* srow = s + b * W;
+    for (int i = lane; i < N; i += 64) x[i] = (double)((srow[i >> 6] >> (i & 63)) & 1ull);
+    wave_sync();
+    for (int k = lane; k < H; k += 64) {
+      double acc = b1[k];
+      for (int d = 0; d < N; ++d) acc = fma(W1s[d * H + k], x[d], acc);
+      hh[k] = fmax(acc, 0.0);
+      gh[k] = acc > 0.0 ? 1.0 : 0.0;  // ReLU gate
+    }
+    wave_sync();
+    for (int i = lane; i < N; i += 64) {
+      double acc = b2[i];
+      for (int k = 0; k < H; ++k) acc = fma(W2s[k * N + i], hh[k], acc);
+      gl[i] = x[i] - 1.0 / (1.0 + exp(-acc));
+    }
+    wave_sync();
+    for (int k = lane; k < H; k += 64) {
+      double acc = 0.0;
+      for (int i = ar_deg(k, N); i < N; ++i) acc = fma(W2s[k * N + i], gl[i], acc);
+      gh[k] *= acc;
+    }
+    wave_sync();
+    OutT* row = O + b * K;
+    for (int64_t j = lane; j < K; j += 64) {
+      const int2 pr = idx[j];
+      double v;
+      if (j < r1)
+        v = gh[pr.x] * x[pr.y];
+      else if (j < r2)
+        v = gh[pr.x];
+      else if (j < r3)
+        v = gl[pr.x] * hh[pr.y];
+      else
+        v = gl[pr.x];
+      v *= 0.5;
+      if constexpr (std::is_same<OutT, double2>::value)
+        row[j] = make_double2(v, 0.0);
+      else if constexpr (std::is_same<OutT, float2>::value)
+        row[j] = make_float2((float)v, 0.0f);
+      else
+        row[j] = (OutT)v;
+    }
+    wave_sync();
+  }
+}
+
 // ---- 16 configurations per work-group on the float64 matrix cores -----------
 // The network of a batch of 16 configurations is three small products on 16 x 16 x 4
 // operands (lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and, in register r,
@@ -859,7 +928,36 @@ void ar_local_energy(vmc_model* m, vmc_ham* H, const uint64_t* s, int64_t B, dou
 void ar_grad(vmc_model* m, const uint64_t* s, int64_t B, void* O, int dtype) {
   const ar_ptrs p = ptrs(m);
   const ar_net d = net_of(m);
-  if (const size_t lb = batch_lds(d, d.Hs)) {
+  const size_t lb = batch_lds(d, d.Hs);
+  const size_t lw = sizeof(double) * (2 * (size_t)m->N * m->Nh + (size_t)AR_WAVES * (2 * (size_t)m->N + 2 * m->Nh));
+  // a configuration per wave where the network fits it and does not fill the 16 x 16 operands
+  // (fewer than 128 parameters: 10 sites, 8 units, 512 configurations 18 against 21 us, 131 072 88
+  // against 104), has too many sites for the padded weights (350 sites, 3 units, 8 192 105 against
+  // the general kernel's 240 us), is small and comes with few configurations (30 sites, 20 units,
+  // 512 22.6 against 24 us; one alone 21 against 19) or writes long complex128 rows, which a
+  // wave finishes on its own (50 sites, 29 units, 32 768 185 against 198 us; 64 sites, 50 units
+  // 466 against 392)
+  const bool wide = dtype == VMC_DT_C128 && B >= 16384 && m->K >= 512 && m->K < 2048;
+  if (lw <= kArLdsMax && ((!lb && B >= AR_WAVES) || m->K < 128 || (m->K < 1024 && B >= 16 && B <= 512) || wide)) {
+    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)(160 * 1024) / (int64_t)lw));
+    const unsigned g = (unsigned)std::min<int64_t>((B + AR_WAVES - 1) / AR_WAVES, cu_count(m->ctx) * per_cu);
+    auto run = [&](auto* o) {
+      using T = std::remove_pointer_t<decltype(o)>;
+      k_ar_grad_w<T><<<g, AR_NT, lw, m->ctx->stream>>>(s, B, m->N, m->Nh, m->W, p.W1mT, m->ar_w2t, p.b1, p.b2,
+                                                       m->ar_idx, m->ar_r1, m->ar_r2, m->ar_r3, m->K, o);
+      VMC_HIP(hipGetLastError());
+    };
+    if (dtype == VMC_DT_C128)
+      run((double2*)O);
+    else if (dtype == VMC_DT_C64)
+      run((float2*)O);
+    else if (dtype == VMC_DT_F64)
+      run((double*)O);
+    else
+      run((float*)O);
+    return;
+  }
+  if (lb) {
     auto run = [&](auto* o) {
       using T = std::remove_pointer_t<decltype(o)>;
       batch_allow(k_ar_grad16<T>, lb);
