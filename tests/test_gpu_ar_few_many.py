@@ -1,11 +1,11 @@
-"""Autoregressive log psi on both sides of the number of configurations from which
+"""Autoregressive log psi and local energies on both sides of the number of configurations from which
 a wave takes 16 of them: the same values against the oracle, batches that end
 inside a block among them."""
 import numpy as np
 import pytest
 
 import synth_inputs as si
-from oracle import arnqs
+from oracle import arnqs, eloc
 from gpu_common import DEV, dev_bits, flush
 
 pytestmark = pytest.mark.gpu
@@ -33,3 +33,22 @@ def test_log_psi_at_the_line(N, H, off):
     ref = arnqs.log_psi(th, x, N, H)
     assert np.all(lp.imag == 0.0)
     assert np.max(np.abs(lp.real - ref)) < 1e-12 * max(1.0, np.abs(ref).max())
+
+
+@pytest.mark.parametrize("Lx,Ly,H,B", [(3, 1, 1, 2048), (3, 1, 1, 2049), (10, 1, 8, 668), (10, 1, 8, 669), (10, 1, 8, 15), (10, 1, 8, 16), (5, 1, 12, 1), (5, 1, 12, 800), (5, 1, 12, 900),
+                                       (3, 4, 19, 9), (8, 8, 50, 17)])
+@pytest.mark.parametrize("kind", ["tfim", "heisenberg"])
+def test_local_energy_at_the_line(Lx, Ly, H, B, kind):
+    N = Lx * Ly
+    flush(f"ar local energies N={N} H={H} B={B} {kind}")
+    ctx = V.Context(0)
+    th = si.ar_params(N, H, seed=N + H, std=0.4)
+    m = V.Model.autoregressive(ctx, N, H)
+    m.set_params(torch.from_numpy(th).to(DEV))
+    few = si.random_bits(min(B, 13), N, seed=N)
+    ham = V.Hamiltonian.tfim(ctx, Lx, Ly, True, 1.0, 0.9) if kind == "tfim" else \
+        V.Hamiltonian.heisenberg(ctx, Lx, Ly, True, 1.0)
+    got = m.local_energy(ham, dev_bits(si.pack_bits(np.resize(few, (B, N))))).cpu().numpy()
+    ref = eloc.local_energy(lambda X: arnqs.log_psi(th, X, N, H).astype(np.complex128), kind, few, Lx, Ly, True, 1.0, 0.9)
+    assert np.all(got.imag == 0.0)
+    assert np.max(np.abs(got - np.resize(ref, B)) / np.maximum(1.0, np.abs(np.resize(ref, B)))) < 1e-10
