@@ -1241,15 +1241,20 @@ void cnn_set_params(vmc_model* m) {
 }
 
 namespace {
+// Whether B samples keep the chip busy for more than one round of the work-groups of eight
+// waves that the registers leave a compute unit (three of log psi, two of O_k).
+bool net_many(const vmc_model* m, int64_t B, bool rows) { return B > (rows ? 2 : 3) * (int64_t)cu_count(m->ctx); }
+
 // Threads of a sample's work-group: two or four waves where layer 2 has as many units (two for
-// O_k of one channel up to 256 sites), so that small samples run several groups for each one of eight waves, most
-// of which would idle; all eight for few samples, where the latency counts, and for larger
-// ones, of which the LDS holds two or three.  8 192 samples, 7 x 7, C = 5, k = 3, log psi 258
-// us with eight waves, 150 with two; O_k of 4 096 samples 5 x 7, C = 5, k = 3 273 and 156; 16 x
-// 16, C = 8, k = 1 577 with eight, 798 with two; 64 x 64, C = 1, k = 3, 1 024 samples 2.8 and 5.2 ms.
-int net_threads(const cnn_geom& g, int64_t B, bool rows) {
+// O_k of one channel up to 256 sites), so that small samples run several groups for each one
+// of eight waves, most of which would idle; all eight for few samples, where the latency counts,
+// and for larger ones, of which the LDS holds two or three.  8 192 samples, 7 x 7, C = 5, k = 3,
+// log psi 258 us with eight waves, 150 with two; O_k of 4 096 samples 5 x 7, C = 5, k = 3 273 and
+// 156; 16 x 16, C = 8, k = 1 577 with eight, 798 with two; 64 x 64, C = 1, k = 3, 1 024 samples
+// 2.8 and 5.2 ms.
+int net_threads(const vmc_model* m, const cnn_geom& g, int64_t B, bool rows) {
   const int u = g.RT * ((g.N + 31) / 32);
-  if (B < 512) return NET_NT;
+  if (!net_many(m, B, rows)) return NET_NT;
   return u <= 2 || (rows && g.C == 1 && u <= 8) ? 128 : u <= 4 ? 256 : NET_NT;
 }
 
@@ -1264,7 +1269,7 @@ void cnn_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
   // 024 samples, 16 x 16, k = 4: C = 1 30 against 76 us, C = 2 52 against 77), and few samples
   // of an output a thread whose serial sum is short (16 samples, 5 x 5, C = 9, k = 1 19 against
   // 24 us; 5 x 5, C = 4, k = 4 28 against 24)
-  if (g.C <= 2 || (B < 512 && g.C * g.N <= 256 && g.C * g.k * g.k <= 32)) {
+  if (g.C <= 2 || (!net_many(m, B, false) && g.C * g.N <= 256 && g.C * g.k * g.k <= 24)) {
     const size_t lds = sizeof(double2) * ((size_t)g.C * g.N + 4);
     allow_lds(k_cnn_forward, lds);
     k_cnn_forward<<<(unsigned)B, 256, lds, m->ctx->stream>>>(g, s, B, logpsi);
@@ -1277,7 +1282,7 @@ void cnn_log_psi(vmc_model* m, const uint64_t* s, int64_t B, double2* logpsi) {
     k<<<(unsigned)B, nt, lds, m->ctx->stream>>>(g, s, B, m->K, nullptr, nullptr, nullptr, logpsi);
     VMC_HIP(hipGetLastError());
   };
-  switch (net_threads(g, B, false)) {
+  switch (net_threads(m, g, B, false)) {
     case 128: return run(k_cnn_net<NET_LOGPSI, 128, double2>, 128);
     case 256: return run(k_cnn_net<NET_LOGPSI, 256, double2>, 256);
     default: return run(k_cnn_net<NET_LOGPSI, NET_NT, double2>, NET_NT);
@@ -1294,7 +1299,7 @@ void grad_rows(vmc_model* m, const uint64_t* s, int64_t B, OutT* O) {
     k<<<(unsigned)B, nt, lds, m->ctx->stream>>>(g, s, B, m->K, O, nullptr, nullptr, nullptr);
     VMC_HIP(hipGetLastError());
   };
-  switch (net_threads(g, B, true)) {
+  switch (net_threads(m, g, B, true)) {
     case 128: return run(k_cnn_net<NET_ROWS, 128, OutT>, 128);
     case 256: return run(k_cnn_net<NET_ROWS, 256, OutT>, 256);
     default: return run(k_cnn_net<NET_ROWS, NET_NT, OutT>, NET_NT);

@@ -1,6 +1,6 @@
 """Float64 CNN log psi on both sides of the line between one thread per output and
 matrix products: channels 1 to 16, samples of at most and more than 256 outputs, few
-samples and 512."""
+samples and more than three a compute unit."""
 import numpy as np
 import pytest
 
@@ -20,7 +20,7 @@ from paper_2108_03409_amd import nqsvmc as V  # noqa: E402
 @pytest.mark.parametrize("Lx,Ly,C,k", [(1, 1, 1, 1), (16, 16, 1, 1), (64, 64, 1, 3), (43, 58, 2, 8), (5, 3, 2, 3), (17, 5, 3, 2),
                                        (43, 2, 3, 2), (16, 4, 4, 4), (13, 5, 4, 2), (7, 7, 5, 4), (13, 4, 5, 3), (5, 5, 8, 3),
                                        (5, 5, 9, 2), (7, 4, 9, 2), (29, 1, 9, 1), (4, 4, 16, 2)])
-@pytest.mark.parametrize("B", [5, 511, 512])
+@pytest.mark.parametrize("B", [5, 768, 769])
 def test_log_psi_at_the_line(Lx, Ly, C, k, B):
     if B > 5 and Lx * Ly > 300:
         B = 6
@@ -43,10 +43,10 @@ def test_rows_of_many_samples(Lx, Ly, C, k, dtype):
     m = V.Model.cnn(V.Context(0), Lx, Ly, C, k)
     m.set_params(dev_c128(p))
     few = si.random_bits(4, Lx * Ly, seed=8)
-    s = dev_bits(si.pack_bits(np.resize(few, (513, Lx * Ly))))
+    s = dev_bits(si.pack_bits(np.resize(few, (900, Lx * Ly))))
     O = m.grad_log_psi(s, getattr(torch, dtype)).cpu().numpy()
     ref = ocnn.grad_log_psi(p, few, Lx, Ly, C, k)
     scale = max(1.0, np.abs(ref).max())
     assert np.max(np.abs(O - np.resize(ref, O.shape))) <= (1e-10 if dtype == "complex128" else 2.0 ** -23) * scale
     lp = m.log_psi(s).cpu().numpy()
-    assert_logpsi_close(lp, np.resize(ocnn.log_psi(p, few, Lx, Ly, C, k), 513), 1e-10)
+    assert_logpsi_close(lp, np.resize(ocnn.log_psi(p, few, Lx, Ly, C, k), 900), 1e-10)
