@@ -268,12 +268,13 @@ enum { NET_LOGPSI = 0, NET_ROWS = 1, NET_VJP = 2 };
 // Bound: the float64 matrix cores (12 C^2 k^2 N real multiply-adds for the three
 // layer-2 products: 83 us a sample and compute unit at C = 16, k = 4, N = 256 at
 // the full rate, 0.33 of the 0.60 ms below); the rest is the transcendental
-// functions of the two activations and the operand latency of two waves per SIMD
-// (16 waves a group with one tile each: 0.61 ms).  The loops over
+// functions of the two activations and the operand latency of two groups a compute unit
+// (16 waves a group with one tile each: 0.61 ms).  Log psi is held to 80 registers, which leave
+// three groups a compute unit.  The loops over
 // taps and positions per output that this replaces spent their time on index
 // arithmetic and serial sums.
-// 1 024 samples, 16 x 16, C = 16, k = 4: log psi 1.53 -> 0.21 ms, O_k (complex64)
-// 7.92 -> 0.60 ms, reverse-mode product 7.86 -> 0.66 ms.
+// 1 024 samples, 16 x 16, C = 16, k = 4: log psi 1.53 -> 0.23 ms, O_k (complex64)
+// 7.92 -> 0.60 ms, reverse-mode product 7.86 -> 0.67 ms.
 template <int MODE, int NT, typename OutT>
 __global__ __launch_bounds__(NT, MODE == NET_LOGPSI ? 6 : 2) void k_cnn_net(
     cnn_geom g, const uint64_t* __restrict__ s, int64_t B, int64_t K, OutT* __restrict__ O,
@@ -516,10 +517,10 @@ __device__ __forceinline__ double2 cosh_factor(double2 z, double2& zt) {
 // 1 / (1 + e^{-2 z~}) of the work-group's sample in global scratch.
 //
 // Bound: the float64 matrix cores and the float64 vector work of the factors, which
-// hardly overlap: the matrix pipe is busy 50% of the cycles (4 C^2 k^4 N real
+// hardly overlap: the matrix pipe is busy 51% of the cycles (4 C^2 k^4 N real
 // multiply-adds a sample, 443 us a compute unit at C = 16, k = 4, N = 256), vector
-// issue takes 44% (counters).  512 samples of that network: 25.2 -> 1.92 ms (2.03 ms
-// with 8 instead of 16 waves a group).
+// instructions issue in 40% (counters).  512 samples of that network: 25.2 -> 1.81 ms (with
+// 8 instead of 16 waves a group 6% more).
 template <int KSC>
 __global__ __launch_bounds__(EL_NT, 4) void k_cnn_eloc64(cnn_geom g, const uint64_t* __restrict__ s, int64_t B,
                                                          int nsplit, double J, double h,
@@ -932,7 +933,7 @@ constexpr int MH_OUT = 2; // window outputs per thread, at most: C (2k-1)^2 <= 7
 // z2 at f - t1 - t2; its layer-2 change is one small matrix product
 //   P[t1][t2, c] = sum_{c'} dA[t1][c'] W2[c][c'][t2]
 // (rows t1, columns (t2, c), no entry wasted at 16 channels and 16 taps) on the float64
-// matrix cores, the weights held in registers for the whole launch, followed by the
+// matrix cores, the weights loaded once for the whole launch, followed by the
 // window sums dz[c][e] = sum_{t1 + t2 = e} P[t1][t2, c] from LDS.  The acceptance uses
 //   Re(log psi' - log psi) = sum (|x'| - |x|) + log(prod q' / prod q) / 2,
 //   q = |1 + e^{-2 z~}|^2, z = x + iy, z~ = +-z with real part |x|,
@@ -942,10 +943,13 @@ constexpr int MH_OUT = 2; // window outputs per thread, at most: C (2k-1)^2 <= 7
 // configuration, and sites and log u of 64 steps drawn at once.
 //
 // Bound: the latency of four barrier-separated phases per step, with two work-groups on
-// a compute unit (their 66 KB of P); the matrix pipe is busy 28% of the cycles, vector
-// issue takes 36% (counters).  1 024 chains x 256 steps, 16 x 16, C = 16, k = 4:
-// 84.6 -> 6.36 ms; with four waves a chain, whose weights and outputs do not fit their
-// registers, 9.1 ms.
+// a compute unit (their 66 KB of P): the waves wait 48% of their time, the matrix pipe is
+// busy 30% of the cycles, vector instructions issue in 38%, and the chains' state moves 22 GB
+// through memory, 3.3 TB/s (counters).  The 128 registers of four waves per SIMD do not hold
+// everything: 62 of them, with values that a step does not change, lie in scratch memory (140
+// bytes a lane) and are read back by up to 18 loads in a step's loop.
+// 1 024 chains x 256 steps, 16 x 16, C = 16, k = 4: 84.6 -> 6.52 ms; with four waves a chain,
+// whose weights and outputs fit their registers less still, 9.1 ms.
 __global__ __launch_bounds__(MH_NT, 4) void k_cnn_mh64(cnn_geom g, int n_chains, int chain0, uint64_t* __restrict__ bits,
                                                      uint2 key, uint64_t t0, int init, int64_t therm_steps,
                                                      int64_t n_record, int sweep, uint64_t* __restrict__ s_out,

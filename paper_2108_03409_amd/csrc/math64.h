@@ -1,13 +1,16 @@
 // Float64 elementary functions for kernels whose time is elementary functions:
-// straight-line code with fewer vector instructions than the device library's (exp 27 for 42, sincos 61
-// for 155, log 43 for 98, log1p 52 for 135, atan2 64 for 105, remainder by 2 pi 4 for 60).  Polynomials interpolate the reduced
+// fewer vector instructions than the device library's (exp 27 for 42, sincos 45 for 155, log 43
+// for 98, log1p 52 for 135, atan2 64 for 105, remainder by 2 pi 6 for 60), straight-line but for
+// sine and cosine from 1e5 and the remainder from 2^30 on.  Polynomials interpolate the reduced
 // functions at Chebyshev nodes (approximation error below 2e-17 of the result);
 // measured against 113-bit arithmetic over 4 million arguments: exp 1.1 ulp, log 0.9, log1p
-// 1.3, atan2 2.2, sine and cosine 1.2e-16 absolute for |x| < 1e5 and from 2^54 on, 1.9e-16 between.  Zeros, infinities and
-// NaN follow the C library.
-// log psi of an RBM (N = 64, N_h = 256, 16 384 samples, theta included) 88.7 -> 76.8 us,
-// CNN log psi (16 x 16, C = 16, k = 4, 1 024 samples) 258 -> 233 us, its local energies
-// (512 samples) 2.15 -> 2.07 ms.
+// 1.3, atan2 2.2, sine and cosine 1.2e-16 absolute for |x| < 1e5 and from 2^54 on, 1.9e-16
+// between; the remainder is exact.  Zeros, infinities and NaN follow the C library.
+// What the functions alone gave, in the kernels they came into: log psi of an RBM (N = 64, N_h =
+// 256, 16 384 samples, theta included) 88.7 -> 76.8 us, CNN log psi (16 x 16, C = 16, k = 4,
+// 1 024 samples) 258 -> 233 us, its local energies (512 samples) 2.15 -> 2.07 ms.  The exact
+// reductions of large arguments cost the same CNN's chains 2% (6.41 -> 6.52 ms), its local
+// energies 0.6% and log psi 1%.
 #pragma once
 
 #include <cmath>

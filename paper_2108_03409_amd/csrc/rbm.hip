@@ -300,7 +300,7 @@ __device__ __forceinline__ double2 table_at(__amdgpu_buffer_rsrc_t rsrc, int uni
 //   E_loc = diag + mel * sum_m exp(-2 sigma_m alpha_m + LC_m + log prod).
 // Bound: float64 vector work, ten instructions per (unit, move).  The padded table and
 // operands need no bounds, and its rows are addressed from scalar registers, U of them in
-// flight: N = 64, N_h = 256, 16 384 samples with theta 237 -> 204 us.
+// flight: N = 64, N_h = 256, 16 384 samples with theta 237 -> 200 us.
 template <int S, int U>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(U == 16 ? 2 : 1, U == 16 ? 2 : 8))) void k_eloc(theta_src theta, const uint64_t* __restrict__ s,
                                              int64_t B, int N, int W, int Nh, int ham_kind, double J, double h,

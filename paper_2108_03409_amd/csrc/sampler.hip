@@ -60,7 +60,8 @@ struct sampler_args {
 // Bound: the dependent path of ratio, reduction, decision and update at one or two
 // waves per SIMD; with many chains the vector instructions and the row of T (12.8 KB
 // a proposal at N_h = 800) from L2.  Waves per SIMD: without TRACK three where the
-// registers allow (20 x 20: 11.1 ms for 4 sweeps instead of 12.1 with two); the
+// registers allow (20 x 20: 11.1 ms for 4 sweeps instead of 12.1 with two; seven slots spill
+// 8 to 11 registers with and without TRACK); the
 // two-wave groups of few chains are held to two, without which the dispatcher
 // leaves three on some SIMDs and one on others (Heisenberg 10 x 10: 0.92 instead of 0.79 ms).
 // Eight slots with TRACK have one wave per SIMD, whose 512 registers hold them: held to two
